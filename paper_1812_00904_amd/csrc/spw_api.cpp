@@ -68,6 +68,35 @@ void parallel_for(int64_t n, F &&f)
     });
 }
 
+// Calls f(i) for every i < n on host threads, i dealt round-robin.
+template <typename F>
+void parallel_ranges(int64_t n, F &&f)
+{
+    const int64_t nt = std::min<int64_t>(n, std::min<unsigned>(16u, std::max(1u, std::thread::hardware_concurrency())));
+    run_parts(nt, [&](int64_t t) {
+        for (int64_t i = t; i < n; i += nt) f(i);
+    });
+}
+
+// Nonzeros per row.
+std::vector<int64_t> count_rows(int64_t rows, int64_t nnz, const int32_t *rowi)
+{
+    std::vector<int64_t> total((size_t)rows, 0);
+    if (rows > (int64_t)1 << 20 || nnz < (int64_t)1 << 18) {
+        for (int64_t p = 0; p < nnz; ++p) total[(size_t)rowi[p]]++;
+        return total;
+    }
+    const int64_t nt = 8;
+    std::vector<std::vector<int64_t>> part((size_t)nt);
+    run_parts(nt, [&](int64_t t) {
+        part[(size_t)t].assign((size_t)rows, 0);
+        for (int64_t p = nnz * t / nt; p < nnz * (t + 1) / nt; ++p) part[(size_t)t][(size_t)rowi[p]]++;
+    });
+    for (const auto &c : part)
+        for (int64_t r = 0; r < rows; ++r) total[(size_t)r] += c[(size_t)r];
+    return total;
+}
+
 spw_status fail(spw_status s, const std::string &msg)
 {
     set_error(msg);
@@ -607,6 +636,34 @@ spw_status plan_workers(spw_matrix_s &A, ColDot &C, const int64_t *ptr, spw_part
     return SPW_OK;
 }
 
+// The number of row panels of the scatter product.  P panels read x P times
+// (cols * 8 bytes each, mostly from the Infinity Cache or an XCD's L2), and the one
+// workgroup per CU leaves CUs * rows / P partial sums that are written and read
+// (16 bytes each, after the products, where nothing hides them): a partial byte
+// costs about three times an x byte on this chip, so the sum of the two is least at
+// P = sqrt(3 * 16 * CUs * rows / (8 * cols)), about 3 for 50,000 x 2e7 (measured, us
+// at 3 / 4 / 6 / 8 panels: 429 / 448 / 485 / 528), 2.5 for 20,000 x 5e6 (1 / 2 / 3 / 4 / 6:
+// 127 / 117 / 113 / 119 / 128) and 5 for 19,996 x 1.36e6 (1 / 2 / 4 / 8: 48 / 40 / 38 / 38).
+// Panels small enough that two, three or four columns' sums fit the LDS together let
+// the multi-column product take them at once, so the next such count is taken where it
+// is at most 1.7 times the best one (20,000 x 5e6: four panels, 6 us of a single
+// product for a four-column block at a third of its time).
+int64_t mv_auto_panels(int64_t rows, int64_t cols, int64_t limit)
+{
+    const double best = std::sqrt(6.0 * 256.0 * (double)rows / (double)std::max<int64_t>(cols, 1));
+    const int64_t least = std::max<int64_t>(1, (rows + limit - 1) / limit);
+    int64_t P = std::max<int64_t>(least, (int64_t)std::llround(std::min(best, 64.0)));
+    for (int64_t together = 4; together >= 2; --together) {
+        const int64_t q = (rows * together + limit - 1) / limit;
+        if (q <= P) break;
+        if ((double)q <= 1.7 * best) {
+            P = q;
+            break;
+        }
+    }
+    return std::min(P, std::max<int64_t>(rows, 1));
+}
+
 // Row panels, wave row sets and blocks of the scatter product (see
 // spw_internal.h and the scatter kernel).  rowi holds the internal
 // (renumbered) rows.
@@ -621,56 +678,70 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     const int64_t SPAN = 65536;                 // columns a block may span (16-bit offsets)
     const int64_t limit = mv_lds_rows_limit(SPW_F64, 1);
     int64_t R = rows;
-    if (panel_rows_opt > 0) R = std::min<int64_t>(panel_rows_opt, limit);
-    else if (rows > limit) {
-        const int64_t P = (rows + limit - 1) / limit;
-        R = (rows + P - 1) / P;
+    if (panel_rows_opt > 0) {
+        R = std::min<int64_t>(panel_rows_opt, limit);
+    } else {
+        const int64_t want = mv_auto_panels(rows, cols, limit);
+        R = (rows + want - 1) / want;
     }
     R = std::max<int64_t>(std::min(R, rows), 1);
     const int64_t P = (rows + R - 1) / R;
     A.panel_rows = R;
     A.n_panels = P;
-    auto row_of = [&](int64_t p) -> int64_t { return (int64_t)rowi[p]; };
-
-    // 1. Column-major order inside each panel: (panel, column) counts, then a
-    //    stable scatter of the source positions.
-    std::vector<int64_t> pptr((size_t)(P * (cols + 1)), 0);
-    std::vector<int64_t> order;
+    // 1. Nonzeros of every panel before each block of CB columns (the panels' own
+    //    column-ordered positions are found from these by scanning one block).
+    const int64_t CB = 1024, ncb = (cols + CB - 1) / CB;
+    std::vector<int32_t> panel_of;              // of a row (one panel: unused)
+    std::vector<int64_t> before_cb((size_t)((ncb + 1) * P), 0);   // [block * P + panel]
     if (P == 1) {
-        for (int64_t j = 0; j <= cols; ++j) pptr[(size_t)j] = ptr[j];
+        for (int64_t c = 0; c <= ncb; ++c) before_cb[(size_t)c] = ptr[std::min(c * CB, cols)];
     } else {
-        std::vector<int32_t> cnt((size_t)(P * cols), 0);
-        parallel_for(cols, [&](int64_t a, int64_t b) {
-            for (int64_t j = a; j < b; ++j)
-                for (int64_t p = ptr[j]; p < ptr[j + 1]; ++p) cnt[(size_t)(row_of(p) % P * cols + j)]++;
-        });
-        int64_t run = 0;
-        for (int64_t q = 0; q < P; ++q) {
-            int64_t *pp = pptr.data() + q * (cols + 1);
-            for (int64_t j = 0; j < cols; ++j) {
-                pp[j] = run;
-                run += cnt[(size_t)(q * cols + j)];
-            }
-            pp[cols] = run;
-        }
-        cnt.clear();
-        cnt.shrink_to_fit();
-        order.resize((size_t)nnz);
-        parallel_for(cols, [&](int64_t a, int64_t b) {
-            std::vector<int64_t> cur((size_t)P);
-            for (int64_t j = a; j < b; ++j) {
-                for (int64_t q = 0; q < P; ++q) cur[(size_t)q] = pptr[(size_t)(q * (cols + 1) + j)];
-                for (int64_t p = ptr[j]; p < ptr[j + 1]; ++p) order[(size_t)cur[(size_t)(row_of(p) % P)]++] = p;
+        panel_of.resize((size_t)rows);
+        for (int64_t r = 0; r < rows; ++r) panel_of[(size_t)r] = (int32_t)(r % P);
+        parallel_for(ncb * CB, [&](int64_t a, int64_t b) {
+            for (int64_t c = (a + CB - 1) / CB; c < (b + CB - 1) / CB; ++c) {
+                int64_t *cnt = &before_cb[(size_t)((c + 1) * P)];
+                for (int64_t p = ptr[c * CB]; p < ptr[std::min((c + 1) * CB, cols)]; ++p)
+                    ++cnt[panel_of[(size_t)rowi[p]]];
             }
         });
+        for (int64_t c = 0; c < ncb; ++c)
+            for (int64_t q = 0; q < P; ++q)
+                before_cb[(size_t)((c + 1) * P + q)] += before_cb[(size_t)(c * P + q)];
     }
-    auto src_of = [&](int64_t pos) -> int64_t { return P == 1 ? pos : order[(size_t)pos]; };
+    auto in_panel = [&](int64_t p, int64_t q) { return P == 1 || panel_of[(size_t)rowi[p]] == q; };
+    auto panel_nnz = [&](int64_t q) { return before_cb[(size_t)(ncb * P + q)]; };
+    // nonzeros of panel q in columns before j
+    auto before = [&](int64_t q, int64_t j) -> int64_t {
+        if (P == 1) return ptr[j];
+        const int64_t c = j / CB;
+        int64_t n = before_cb[(size_t)(c * P + q)];
+        if (c * CB < j)
+            for (int64_t p = ptr[c * CB]; p < ptr[j]; ++p) n += in_panel(p, q);
+        return n;
+    };
+    // (column, position) of nonzero number t of panel q
+    struct At {
+        int64_t j, p;
+    };
+    auto locate = [&](int64_t q, int64_t t) -> At {
+        if (P == 1) return At{std::upper_bound(ptr, ptr + cols + 1, t) - ptr - 1, t};
+        int64_t lo = 0, hi = ncb;               // the last block with at most t nonzeros of q before it
+        while (hi - lo > 1) {
+            const int64_t mid = (lo + hi) / 2;
+            if (before_cb[(size_t)(mid * P + q)] <= t) lo = mid;
+            else hi = mid;
+        }
+        int64_t p = ptr[lo * CB];
+        for (int64_t n = before_cb[(size_t)(lo * P + q)];; ++p)
+            if (in_panel(p, q) && n++ == t) break;
+        return At{std::upper_bound(ptr, ptr + cols + 1, p) - ptr - 1, p};
+    };
 
     // 2. Deal each panel's rows to the NB waves, heaviest first onto the lightest wave.
     std::vector<uint8_t> wave_of((size_t)rows, 0);
     {
-        std::vector<int64_t> rc((size_t)rows, 0);
-        for (int64_t p = 0; p < nnz; ++p) rc[(size_t)row_of(p)]++;
+        const std::vector<int64_t> rc = count_rows(rows, nnz, rowi);
         for (int64_t q = 0; q < P; ++q) {
             std::vector<int32_t> rs;
             for (int64_t r = q; r < rows; r += P) rs.push_back((int32_t)r);
@@ -684,14 +755,16 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
         }
     }
 
-    // 3. Workgroups: contiguous runs of one panel's column-ordered nonzeros, as
-    //    many in total as the chip runs at once.
-    const int cus = device_cu_count(A.device);
-    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, (160 * 1024) / std::max<int64_t>(R * 8 + 256, 1)));
-    const int64_t target = (int64_t)cus * per_cu;
+    // 3. Workgroups: contiguous runs of one panel's column-ordered nonzeros, one
+    //    per CU in total.  Two per CU where the panels are small enough were no
+    //    faster anywhere: they double the partial sums (1,000 x 1e5 with 1e6
+    //    nonzeros 18.6 us at two, 13.3 us at one; 20,000 x 5e6 with 5e7 nonzeros
+    //    in four panels 131 and 119 us).
+    const int64_t target = device_cu_count(A.device);
     struct WgRange {
         int32_t panel;
         int64_t a, b;      // panel-ordered positions
+        At start;          // column and position of the first
     };
     std::vector<WgRange> wr;
     A.panels.clear();
@@ -703,7 +776,7 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
         std::vector<std::pair<double, int64_t>> rem;
         int64_t used = 0;
         for (int64_t q = 0; q < P; ++q) {
-            const int64_t qn = pptr[(size_t)(q * (cols + 1) + cols)] - pptr[(size_t)(q * (cols + 1))];
+            const int64_t qn = panel_nnz(q);
             if (qn == 0) continue;
             const double share = (double)target * (double)qn / (double)std::max<int64_t>(nnz, 1);
             pnw[(size_t)q] = std::max<int64_t>(1, (int64_t)share);
@@ -714,22 +787,21 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
         for (size_t i = 0; i < rem.size() && used < target; ++i, ++used) pnw[(size_t)rem[i].second]++;
     }
     for (int64_t q = 0; q < P; ++q) {
-        const int64_t qa = pptr[(size_t)(q * (cols + 1))], qb = pptr[(size_t)(q * (cols + 1) + cols)];
+        const int64_t qn = panel_nnz(q);
         PanelDesc pd;
         pd.row0 = (int32_t)q;
         pd.rows = (int32_t)((rows - q + P - 1) / P);
         pd.wg0 = (int32_t)wr.size();
-        if (qb > qa) {
+        if (qn > 0) {
             const int64_t nw = pnw[(size_t)q];
-            const int64_t *pq = pptr.data() + q * (cols + 1);
             int64_t j0 = 0;
             for (int64_t w = 0; w < nw; ++w) {
                 int64_t a, b;
                 if (A.partition == SPW_PART_COLUMN) {
                     // equal numbers of columns, the first cols mod nw one more
                     const int64_t j1 = j0 + cols / nw + (w < cols % nw ? 1 : 0);
-                    a = pq[j0];
-                    b = pq[j1];
+                    a = before(q, j0);
+                    b = before(q, j1);
                     j0 = j1;
                 } else if (A.partition == SPW_PART_MERGE) {
                     // merge path over (columns, nonzeros): range w starts at
@@ -737,114 +809,139 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
                     // and d - i nonzeros lie before it, with i the largest
                     // count of whole columns that fits
                     auto split = [&](int64_t ww) -> int64_t {
-                        const int64_t d = (cols + (qb - qa)) * ww / nw;
-                        int64_t lo = 0, hi = cols;        // largest i with (pq[i] - qa) + i <= d
+                        const int64_t d = (cols + qn) * ww / nw;
+                        int64_t lo = 0, hi = cols;        // largest i with before(i) + i <= d
                         while (lo < hi) {
                             const int64_t mid = (lo + hi + 1) / 2;
-                            if (pq[mid] - qa + mid <= d) lo = mid;
+                            if (before(q, mid) + mid <= d) lo = mid;
                             else hi = mid - 1;
                         }
-                        const int64_t k = std::min(std::max(d - lo, pq[lo] - qa),
-                                                   (lo < cols ? pq[lo + 1] : pq[cols]) - qa);
-                        return qa + k;
+                        return std::min(std::max(d - lo, before(q, lo)), before(q, std::min(lo + 1, cols)));
                     };
                     a = split(w);
                     b = split(w + 1);
                 } else {
-                    a = qa + (qb - qa) * w / nw;
-                    b = qa + (qb - qa) * (w + 1) / nw;
+                    a = qn * w / nw;
+                    b = qn * (w + 1) / nw;
                 }
-                if (b > a) wr.push_back(WgRange{(int32_t)q, a, b});
+                if (b > a) wr.push_back(WgRange{(int32_t)q, a, b, At{0, 0}});
             }
         }
         pd.nwg = (int32_t)(wr.size() - (size_t)pd.wg0);
         A.panels.push_back(pd);
     }
     const int64_t W = (int64_t)wr.size();
+    parallel_ranges(W, [&](int64_t w) { wr[(size_t)w].start = locate(wr[(size_t)w].panel, wr[(size_t)w].a); });
+    // Launch order: the ranges by their first column, so that the panels of one
+    // column region are neighbours, and the x-th eighth of that sequence on XCD x
+    // (workgroup ids are dealt to the 8 XCDs round-robin): the panels of a region then
+    // read its entries of x through one L2 at about the same time.
+    std::vector<int32_t> wg_order((size_t)std::max<int64_t>(W, 1), 0);
+    {
+        std::vector<int32_t> seq((size_t)W);
+        std::iota(seq.begin(), seq.end(), 0);
+        std::stable_sort(seq.begin(), seq.end(), [&](int32_t a, int32_t b) {
+            return wr[(size_t)a].start.j < wr[(size_t)b].start.j;
+        });
+        size_t next = 0;
+        for (int64_t x = 0; x < 8; ++x)
+            for (int64_t b = x; b < W; b += 8) wg_order[(size_t)b] = seq[next++];
+    }
 
     // 4. Blocks per (workgroup, wave): nonzeros of that wave's rows in column
-    //    order, at most BLK per block and spanning fewer than SPAN columns.
-    struct Blk {
-        int32_t col_base, count;
-        uint32_t packed[1024];
-        double val[1024];
-    };
+    //    order, at most BLK per block and spanning fewer than SPAN columns.  One
+    //    walk over every range counts its blocks, a second one fills them.
     if (BLK > 1024 || BLK % 256) return fail(SPW_ERR_UNSUPPORTED, "scatter block size mismatch");
-    std::vector<std::vector<std::vector<Blk>>> wblocks((size_t)W);
-    parallel_for(W, [&](int64_t wa, int64_t wb) {
-        for (int64_t w = wa; w < wb; ++w) {
-            const WgRange &g = wr[(size_t)w];
-            const int64_t *pp = pptr.data() + (int64_t)g.panel * (cols + 1);
-            std::vector<std::vector<Blk>> &bl = wblocks[(size_t)w];
-            bl.assign((size_t)NB, {});
-            int64_t j = std::upper_bound(pp, pp + cols + 1, g.a) - pp - 1;
-            for (int64_t pos = g.a; pos < g.b; ++pos) {
-                while (pp[j + 1] <= pos) ++j;
-                const int64_t sp = src_of(pos);
-                const int64_t r = row_of(sp);
-                std::vector<Blk> &v = bl[wave_of[(size_t)r]];
-                if (v.empty() || v.back().count == BLK || j - v.back().col_base >= SPAN) {
-                    v.emplace_back();
-                    Blk &nb = v.back();
-                    nb.col_base = (int32_t)j;
-                    nb.count = 0;
-                    std::memset(nb.packed, 0, (size_t)BLK * sizeof(uint32_t));
-                    std::memset(nb.val, 0, (size_t)BLK * sizeof(double));
-                }
-                Blk &cb = v.back();
-                // logical nonzero l = jj*64 + ln goes to the interleaved slots the kernel reads
-                const int32_t l = cb.count++;
-                const int32_t jj = l / 64, ln = l % 64;
-                cb.packed[((jj / 4) * 64 + ln) * 4 + jj % 4] =
-                    ((uint32_t)(r / P) << 16) | (uint32_t)(j - cb.col_base);
-                cb.val[((jj / GV) * 64 + ln) * GV + jj % GV] = val[sp];
+    if (NB > 8) return fail(SPW_ERR_UNSUPPORTED, "scatter wave count mismatch");
+    std::vector<uint32_t> local_of((size_t)rows);           // panel-local row, as the words hold it
+    for (int64_t r = 0; r < rows; ++r) local_of[(size_t)r] = (uint32_t)(r / P) << 16;
+    // Calls open(wave, column) when a block of that wave begins and put(wave, column
+    // offset, position) for every nonzero of range w.
+    auto walk = [&](int64_t w, auto &&open, auto &&put) {
+        const WgRange &g = wr[(size_t)w];
+        int64_t base[8], count[8];
+        for (int64_t v = 0; v < NB; ++v) {
+            base[v] = 0;
+            count[v] = BLK;                                 // no block yet
+        }
+        int64_t j = g.start.j, p = g.start.p;
+        for (int64_t left = g.b - g.a; left > 0; ++p) {
+            if (!in_panel(p, g.panel)) continue;
+            while (ptr[j + 1] <= p) ++j;
+            const int v = wave_of[(size_t)rowi[p]];
+            if (count[v] == BLK || j - base[v] >= SPAN) {
+                base[v] = j;
+                count[v] = 0;
+                open(v, j);
             }
+            ++count[v];
+            put(v, j - base[v], p);
+            --left;
         }
-    });
-    order.clear();
-    order.shrink_to_fit();
+    };
     std::vector<int32_t> wg_blk((size_t)(W * (NB + 1)), 0);
+    parallel_ranges(W, [&](int64_t w) {
+        walk(w, [&](int v, int64_t) { ++wg_blk[(size_t)(w * (NB + 1) + v + 1)]; }, [](int, int64_t, int64_t) {});
+    });
     int64_t nblk = 0;
-    for (int64_t w = 0; w < W; ++w)
-        for (int64_t b = 0; b < NB; ++b) {
-            wg_blk[(size_t)(w * (NB + 1) + b)] = (int32_t)nblk;
-            nblk += (int64_t)wblocks[(size_t)w][(size_t)b].size();
-            wg_blk[(size_t)(w * (NB + 1) + b + 1)] = (int32_t)nblk;
+    for (int64_t w = 0; w < W; ++w) {
+        wg_blk[(size_t)(w * (NB + 1))] = (int32_t)nblk;
+        for (int64_t v = 0; v < NB; ++v) {
+            nblk += wg_blk[(size_t)(w * (NB + 1) + v + 1)];
+            wg_blk[(size_t)(w * (NB + 1) + v + 1)] = (int32_t)nblk;
         }
+        if (nblk * BLK >= ((int64_t)1 << 31)) break;
+    }
     if (nblk * BLK >= ((int64_t)1 << 31)) return fail(SPW_ERR_UNSUPPORTED, "scatter-product storage exceeds 2^31 slots");
     const int64_t nslots = std::max<int64_t>(nblk, 1) * BLK;
-    std::vector<uint32_t> packed((size_t)nslots, 0u);
-    std::vector<uint8_t> mval((size_t)(nslots * es), 0);
+    // not cleared here: every block is cleared by the thread that fills it
+    std::unique_ptr<uint32_t[]> packed(new uint32_t[(size_t)nslots]);
+    std::unique_ptr<uint8_t[]> mval(new uint8_t[(size_t)(nslots * es)]);
     std::vector<int32_t> bdesc((size_t)(2 * std::max<int64_t>(nblk, 1)), 0);
-    parallel_for(W, [&](int64_t wa, int64_t wb) {
-        for (int64_t w = wa; w < wb; ++w)
-            for (int64_t b = 0; b < NB; ++b) {
-                int64_t id = wg_blk[(size_t)(w * (NB + 1) + b)];
-                for (const Blk &bk : wblocks[(size_t)w][(size_t)b]) {
-                    bdesc[(size_t)(2 * id)] = bk.col_base;
-                    bdesc[(size_t)(2 * id + 1)] = bk.count;
-                    std::memcpy(&packed[(size_t)(id * BLK)], bk.packed, (size_t)BLK * sizeof(uint32_t));
-                    for (int64_t q = 0; q < BLK; ++q) put_value(storage, mval.data(), id * BLK + q, bk.val[q]);
-                    ++id;
-                }
-            }
+    if (nblk == 0) {
+        std::memset(packed.get(), 0, (size_t)nslots * 4);
+        std::memset(mval.get(), 0, (size_t)(nslots * es));
+    }
+    parallel_ranges(W, [&](int64_t w) {
+        int64_t id[8];
+        int32_t count[8] = {};
+        for (int64_t v = 0; v < NB; ++v) id[v] = wg_blk[(size_t)(w * (NB + 1) + v)] - 1;
+        walk(
+            w,
+            [&](int v, int64_t j) {
+                ++id[v];
+                count[v] = 0;
+                bdesc[(size_t)(2 * id[v])] = (int32_t)j;
+                std::memset(packed.get() + id[v] * BLK, 0, (size_t)BLK * sizeof(uint32_t));
+                std::memset(mval.get() + id[v] * BLK * es, 0, (size_t)(BLK * es));
+            },
+            [&](int v, int64_t off, int64_t p) {
+                // logical nonzero l = jj*64 + ln goes to the interleaved slots the kernel reads
+                const int32_t l = count[v]++;
+                const int32_t jj = l / 64, ln = l % 64;
+                const int64_t at = id[v] * BLK;
+                packed[(size_t)(at + ((jj / 4) * 64 + ln) * 4 + jj % 4)] = local_of[(size_t)rowi[p]] | (uint32_t)off;
+                put_value(storage, mval.get(), at + ((jj / GV) * 64 + ln) * GV + jj % GV, val[p]);
+                bdesc[(size_t)(2 * id[v] + 1)] = count[v];
+            });
     });
-    wblocks.clear();
     A.n_mblocks = nblk;
     A.mv_wgs = W;
     spw_status st;
     if ((st = dev_alloc(A, &A.d_mpacked, nslots, "block words"))) return st;
-    if ((st = h2d(A.d_mpacked, packed.data(), (size_t)nslots * 4, "block words"))) return st;
+    if ((st = h2d(A.d_mpacked, packed.get(), (size_t)nslots * 4, "block words"))) return st;
     {
         uint8_t *d = nullptr;
         if ((st = dev_alloc(A, &d, nslots * es, "block values"))) return st;
-        if ((st = h2d(d, mval.data(), mval.size(), "block values"))) return st;
+        if ((st = h2d(d, mval.get(), (size_t)(nslots * es), "block values"))) return st;
         A.d_mval = d;
     }
     if ((st = dev_alloc(A, &A.d_mblocks, (int64_t)bdesc.size(), "block table"))) return st;
     if ((st = h2d(A.d_mblocks, bdesc.data(), bdesc.size() * 4, "block table"))) return st;
     if ((st = dev_alloc(A, &A.d_wg_blk, std::max<int64_t>((int64_t)wg_blk.size(), 1), "workgroup table"))) return st;
     if ((st = h2d(A.d_wg_blk, wg_blk.data(), wg_blk.size() * 4, "workgroup table"))) return st;
+    if ((st = dev_alloc(A, &A.d_wg_order, (int64_t)wg_order.size(), "workgroup order"))) return st;
+    if ((st = h2d(A.d_wg_order, wg_order.data(), wg_order.size() * 4, "workgroup order"))) return st;
     if ((st = dev_alloc(A, &A.d_panels, P, "panels"))) return st;
     if ((st = h2d(A.d_panels, A.panels.data(), A.panels.size() * sizeof(PanelDesc), "panels"))) return st;
     return SPW_OK;
@@ -1307,8 +1404,7 @@ static spw_status spw_create_impl(spw_matrix *out, spw_format fmt, int64_t m, in
     // entries of the short vector are adjacent.
     std::vector<int32_t> rank, inv;
     if (A->relabeled) {
-        std::vector<int64_t> cnt((size_t)rows, 0);
-        for (int64_t p = 0; p < nnz; ++p) cnt[(size_t)idx[p]]++;
+        const std::vector<int64_t> cnt = count_rows(rows, nnz, idx);
         inv.resize((size_t)rows);
         std::iota(inv.begin(), inv.end(), 0);
         std::stable_sort(inv.begin(), inv.end(), [&](int32_t a, int32_t b) { return cnt[(size_t)a] > cnt[(size_t)b]; });

@@ -158,6 +158,11 @@ template <int N> struct IdxRaw<int32_t, N> {     // N 4-byte indices
     __device__ __forceinline__ int get(int i) const { return (int)w[i]; }
 };
 
+// A compile-time integer passed as a value (to pick a template in a lambda).
+template <int N> struct IntC {
+    static constexpr int value = N;
+};
+
 // Output columns of a multi-vector pass, each with its own base and stride
 // (the columns may belong to different requests).
 constexpr int MULTI_MAX = 8;

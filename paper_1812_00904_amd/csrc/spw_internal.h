@@ -137,6 +137,7 @@ struct spw_matrix_s {
     void *d_mval = nullptr;             // values in the storage type, interleaved like d_mpacked
     int32_t *d_mblocks = nullptr;       // per block: column base, count
     int32_t *d_wg_blk = nullptr;        // per workgroup: waves+1 offsets into the blocks
+    int32_t *d_wg_order = nullptr;      // per launch slot: its workgroup range (ranges of one column region share an XCD)
     int64_t n_mblocks = 0;
     std::vector<spw::PanelDesc> panels;
     spw::PanelDesc *d_panels = nullptr;

@@ -262,8 +262,7 @@ __device__ __forceinline__ void mv_load(MvBlk<ValT> &B, const uint32_t *__restri
 }
 
 // One workgroup range of the scatter product into the LDS panel ypan, written
-// to out (panel_rows doubles).  Ends with a workgroup barrier, so the panel
-// can be reused at once.
+// to out (panel_rows doubles).
 template <int BLOCK, typename ValT, typename VecT, bool NT>
 __device__ __forceinline__ void mv_range(const uint32_t *__restrict__ packed, const ValT *__restrict__ val,
                                          const int2 *__restrict__ blocks, const int32_t *__restrict__ wg_blk,
@@ -355,100 +354,357 @@ __device__ __forceinline__ void mv_range(const uint32_t *__restrict__ packed, co
     }
     __syncthreads();
     for (int i = tid; i < panel_rows; i += BLOCK) out[i] = ypan[i];
-    __syncthreads();
 }
 
 template <int BLOCK, typename ValT, typename VecT>
 __global__ __launch_bounds__(BLOCK) void mv_bucket(
     const uint32_t *__restrict__ packed, const ValT *__restrict__ val, const int2 *__restrict__ blocks,
-    const int32_t *__restrict__ wg_blk, const VecT *__restrict__ x, int64_t ldx, double *__restrict__ partial,
-    int panel_rows)
+    const int32_t *__restrict__ wg_blk, const int32_t *__restrict__ wg_order, const VecT *__restrict__ x, int64_t ldx,
+    double *__restrict__ partial, int panel_rows)
 {
     extern __shared__ double ypan[];
-    mv_range<BLOCK, ValT, VecT, true>(packed, val, blocks, wg_blk, blockIdx.x, x, ldx,
-                                partial + (int64_t)blockIdx.x * panel_rows, panel_rows, ypan);
+    const int range = wg_order[blockIdx.x];
+    mv_range<BLOCK, ValT, VecT, true>(packed, val, blocks, wg_blk, range, x, ldx,
+                                      partial + (int64_t)range * panel_rows, panel_rows, ypan);
 }
 
-// k columns in one launch.  TAB = false: column c of a row-major X (x + c,
-// stride ldx).  TAB = true: column c read from xin.v[c] with stride
-// xin.ld[c] (the inputs of different served requests; the entry is picked by
-// a chain of selects on c, so the table stays in kernel-argument registers).
-// Workgroup (column c, group g) runs the ranges g*S .. g*S+S-1 of the
-// single-column product for column c, each into its own partial slot
-// (c * W + range), so every column is summed exactly as the single-column
-// call sums it.  The k workgroups of a group are dispatched to the same XCD
-// (workgroup ids are dealt to the 8 XCDs round-robin: id b goes to XCD b mod
-// 8), so they read the same blocks, and the same lines of a row-major X,
-// through one L2 at about the same time (ordinary loads, so the lines stay for
-// the others): A streams from HBM about once for the k columns.
-template <int BLOCK, typename ValT, typename VecT, bool TAB>
-__global__ __launch_bounds__(BLOCK) void mv_bucket_cols(
-    const uint32_t *__restrict__ packed, const ValT *__restrict__ val, const int2 *__restrict__ blocks,
-    const int32_t *__restrict__ wg_blk, const VecT *__restrict__ x, int64_t ldx, ColIn<VecT> xin,
-    double *__restrict__ partial, int panel_rows, int k, int W, int S)
-{
-    extern __shared__ double ypan[];
-    const int b = blockIdx.x;
-    const int c = (b % (8 * k)) / 8;
-    const int g = (b / (8 * k)) * 8 + b % 8;
-    const int w0 = g * S, w1 = min(W, w0 + S);
-    const VecT *xc = x + c;
-    int64_t ld = ldx;
-    if constexpr (TAB) {
-        xc = xin.v[0];
-        ld = xin.ld[0];
+// ------------------------------------------------------------------------
+// Scatter product for several columns of x at once (k >= 2).
+//
+// A workgroup runs one range for a group of KC <= 4 columns: its LDS holds KC
+// copies of the row panel, and a lane adds its nonzero into each of them.  What
+// bounds one column after another is the instruction stream and the address
+// unit, not memory: every column decoded the same words, re-read the same
+// values and touched the same lines of a row-major X.  With KC columns a lane
+// decodes a word once, reads the KC adjacent entries of its row of X with
+// 16-byte loads, and only the products and the LDS additions grow with KC.
+// Every row of a column is summed by the same wave in the same order as in the
+// single-column product, so the results are the same bit for bit.
+//
+// The x entries live in a ring of one block (four sub-blocks of four items a
+// lane): after sub-block s of block b has been multiplied, its place takes the
+// entries of sub-block s of block b+1, whose words are in registers, and the
+// words and values of block b+2 replace those of sub-block s just used.  So
+// the loads run four sub-blocks ahead without a copy between registers.  The
+// LDS panels allow one workgroup per CU (one wave per SIMD), so the registers
+// this takes (about 230 for four binary64 columns) cost no occupancy.
+// ------------------------------------------------------------------------
+constexpr int MV_SUB = 4;                       // items of a lane per sub-block
+constexpr int MV_NSUB = MV_ITEMS / MV_SUB;
+constexpr int MV_COLS = 4;                      // columns a workgroup takes at once, at most
+
+// Values of items 4*s .. 4*s+3 of one lane of a block.
+template <typename ValT> struct MvVal;
+template <> struct MvVal<double> {
+    double a[MV_SUB];
+    __device__ __forceinline__ void load(const double *base, int s, int lane)
+    {
 #pragma unroll
-        for (int t = 1; t < MULTI_MAX; ++t) {
-            xc = c == t ? xin.v[t] : xc;
-            ld = c == t ? xin.ld[t] : ld;
+        for (int h = 0; h < 2; ++h) {
+            const f64x2_t w = *reinterpret_cast<const f64x2_t *>(base + ((2 * s + h) * 64 + lane) * 2);
+            a[2 * h] = w.x;
+            a[2 * h + 1] = w.y;
         }
     }
-    for (int w = w0; w < w1; ++w)
-        mv_range<BLOCK, ValT, VecT, false>(packed, val, blocks, wg_blk, w, xc, ld,
-                                    partial + ((int64_t)c * W + w) * panel_rows, panel_rows, ypan);
+    __device__ __forceinline__ double get(int i) const { return a[i]; }
+};
+template <> struct MvVal<float> {
+    float a[MV_SUB];
+    __device__ __forceinline__ void load(const float *base, int s, int lane)
+    {
+        const f32x4_t w = *reinterpret_cast<const f32x4_t *>(base + (s * 64 + lane) * 4);
+        a[0] = w.x;
+        a[1] = w.y;
+        a[2] = w.z;
+        a[3] = w.w;
+    }
+    __device__ __forceinline__ double get(int i) const { return (double)a[i]; }
+};
+template <> struct MvVal<Bf16> {
+    uint32_t w[2];
+    __device__ __forceinline__ void load(const Bf16 *base, int s, int lane)
+    {
+        typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+        const u32x2_t q = *reinterpret_cast<const u32x2_t *>(base + ((s >> 1) * 64 + lane) * 8 + (s & 1) * 4);
+        w[0] = q.x;
+        w[1] = q.y;
+    }
+    __device__ __forceinline__ double get(int i) const
+    {
+        return bf16_bits_to_f64((w[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu);
+    }
+};
+
+// KC adjacent entries of a row of X.  A row starts on a multiple of the entry
+// size only, so the wide loads are typed with that alignment.
+template <typename VecT, int KC> struct MvRow;
+template <int KC> struct MvRow<double, KC> {
+    double v[KC];
+    __device__ __forceinline__ void load(const double *p)
+    {
+        typedef double f64x2_u __attribute__((ext_vector_type(2), aligned(8)));
+#pragma unroll
+        for (int h = 0; h < KC / 2; ++h) {
+            const f64x2_u w = *reinterpret_cast<const f64x2_u *>(p + 2 * h);
+            v[2 * h] = w.x;
+            v[2 * h + 1] = w.y;
+        }
+        if (KC & 1) v[KC - 1] = p[KC - 1];
+    }
+};
+template <int KC> struct MvRow<float, KC> {
+    float v[KC];
+    __device__ __forceinline__ void load(const float *p)
+    {
+        if constexpr (KC == 4) {
+            typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+            const f32x4_u w = *reinterpret_cast<const f32x4_u *>(p);
+            v[0] = w.x;
+            v[1] = w.y;
+            v[2] = w.z;
+            v[3] = w.w;
+        } else {
+            if constexpr (KC >= 2) {
+                typedef float f32x2_u __attribute__((ext_vector_type(2), aligned(4)));
+                const f32x2_u w = *reinterpret_cast<const f32x2_u *>(p);
+                v[0] = w.x;
+                v[1] = w.y;
+            }
+            if constexpr (KC & 1) v[KC - 1] = p[KC - 1];
+        }
+    }
+};
+
+// A group of adjacent columns of one row-major block: kc columns from x on,
+// rows ld entries apart; slot is the partial-sum slot of its first column.
+template <typename VecT> struct MvGroups {
+    const VecT *x[MULTI_MAX];
+    int64_t ld[MULTI_MAX];
+    int32_t kc[MULTI_MAX], slot[MULTI_MAX];
+};
+
+template <typename ValT> struct MvStage {
+    uint32_t w[MV_ITEMS];
+    MvVal<ValT> a[MV_NSUB];
+};
+
+// One range for KC columns.  WIDE: the row stride of X is too large for 32-bit
+// byte offsets inside a block's 65,536 columns.
+template <int BLOCK, typename ValT, typename VecT, int KC, bool WIDE>
+__device__ __forceinline__ void mv_range_cols(const uint32_t *__restrict__ packed, const ValT *__restrict__ val,
+                                              const int2 *__restrict__ blocks, const int32_t *__restrict__ wb,
+                                              const VecT *__restrict__ x, int64_t ldx, double *__restrict__ out,
+                                              int64_t col_stride, int panel_rows, double *ypan)
+{
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    for (int i = tid; i < KC * panel_rows; i += BLOCK) ypan[i] = 0.0;
+    __syncthreads();
+    const int b0 = __builtin_amdgcn_readfirstlane(wb[wave]), b1 = __builtin_amdgcn_readfirstlane(wb[wave + 1]);
+    const uint32_t ld_bytes = (uint32_t)(ldx * (int64_t)sizeof(VecT));
+    typedef MvRow<VecT, KC> Row;
+    MvStage<ValT> S0, S1;
+    Row xr[MV_NSUB][MV_SUB];
+    int base0 = 0, base1 = 0, cnt0 = 0, cnt1 = 0;
+    auto load = [&](MvStage<ValT> &S, int s, int b) {
+        const int64_t at = (int64_t)b * MV_BLK;
+        const u32x4_t q = *reinterpret_cast<const u32x4_t *>(packed + at + (s * 64 + lane) * 4);
+        S.w[4 * s] = q.x;
+        S.w[4 * s + 1] = q.y;
+        S.w[4 * s + 2] = q.z;
+        S.w[4 * s + 3] = q.w;
+        S.a[s].load(val + at, s, lane);
+    };
+    auto describe = [&](int b, int &base, int &cnt) {
+        const int2 d = blocks[b];
+        base = __builtin_amdgcn_readfirstlane(d.x);
+        cnt = __builtin_amdgcn_readfirstlane(d.y);
+    };
+    // padding slots hold word 0, so their gather reads the block's first column: no branch
+    auto gather = [&](const MvStage<ValT> &S, int s, int base) {
+        const VecT *xb = x + (int64_t)base * ldx;
+#pragma unroll
+        for (int j = 0; j < MV_SUB; ++j) {
+            const uint32_t c = S.w[4 * s + j] & 0xFFFFu;
+            if constexpr (WIDE) xr[s][j].load(xb + (int64_t)c * ldx);
+            else xr[s][j].load(reinterpret_cast<const VecT *>(reinterpret_cast<const char *>(xb) + c * ld_bytes));
+        }
+    };
+    double p[MV_SUB][KC];
+    uint32_t row[MV_SUB];
+    auto multiply = [&](const MvStage<ValT> &S, int s) {
+#pragma unroll
+        for (int j = 0; j < MV_SUB; ++j) {
+            row[j] = S.w[4 * s + j] >> 16;
+#pragma unroll
+            for (int c = 0; c < KC; ++c) p[j][c] = S.a[s].get(j) * (double)xr[s][j].v[c];
+        }
+    };
+    auto commit = [&](int s, int cnt) {
+        const int lim = cnt - lane;              // item i is a nonzero when i*64 < lim
+#pragma unroll
+        for (int j = 0; j < MV_SUB; ++j) {
+            if (cnt == MV_BLK || (4 * s + j) * WAVE < lim) {
+#pragma unroll
+                for (int c = 0; c < KC; ++c)
+                    __hip_atomic_fetch_add(&ypan[c * panel_rows + row[j]], p[j][c], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+    };
+    if (b0 < b1 && b1 - b0 <= 2) {
+        // one or two blocks (small matrices): no repeats of the last block, and no
+        // loads past a block's last nonzero
+        for (int b = b0; b < b1; ++b) {
+            describe(b, base0, cnt0);
+#pragma unroll
+            for (int s = 0; s < MV_NSUB; ++s)
+                if (s * MV_SUB * WAVE < cnt0) load(S0, s, b);
+#pragma unroll
+            for (int s = 0; s < MV_NSUB; ++s)
+                if (s * MV_SUB * WAVE < cnt0) gather(S0, s, base0);
+#pragma unroll
+            for (int s = 0; s < MV_NSUB; ++s)
+                if (s * MV_SUB * WAVE < cnt0) {
+                    multiply(S0, s);
+                    commit(s, cnt0);
+                }
+        }
+    } else if (b0 < b1) {
+        const int last = b1 - 1;
+        describe(b0, base0, cnt0);
+        describe(b0 + 1, base1, cnt1);
+#pragma unroll
+        for (int s = 0; s < MV_NSUB; ++s) load(S0, s, b0);
+#pragma unroll
+        for (int s = 0; s < MV_NSUB; ++s) load(S1, s, b0 + 1);
+#pragma unroll
+        for (int s = 0; s < MV_NSUB; ++s) gather(S0, s, base0);
+        // block b in C, block b+1 in N; past the end of the range the last block
+        // is loaded again, unused
+        auto block = [&](MvStage<ValT> &C, const MvStage<ValT> &N, int b, int &cnt_c, int &base_c, int base_n) {
+            const int b2 = min(b + 2, last);
+            int base2, cnt2;
+            describe(b2, base2, cnt2);
+#pragma unroll
+            for (int s = 0; s < MV_NSUB; ++s) {
+                multiply(C, s);
+                gather(N, s, base_n);
+                load(C, s, b2);
+                commit(s, cnt_c);
+            }
+            base_c = base2;
+            cnt_c = cnt2;
+        };
+        for (int b = b0;; b += 2) {
+            block(S0, S1, b, cnt0, base0, base1);
+            if (b + 1 >= b1) break;
+            block(S1, S0, b + 1, cnt1, base1, base0);
+            if (b + 2 >= b1) break;
+        }
+    }
+    __syncthreads();
+    for (int c = 0; c < KC; ++c)
+        for (int i = tid; i < panel_rows; i += BLOCK) out[c * col_stride + i] = ypan[c * panel_rows + i];
+}
+
+// Groups of columns in one launch: workgroup (group, range).  The groups of one
+// range, and the ranges of neighbouring columns, are dispatched to one XCD
+// (workgroup ids are dealt to the 8 XCDs round-robin, so id b runs on XCD b mod 8),
+// so they share the blocks and the lines of X through its L2 (ordinary loads: the lines
+// stay for the others).  The tables are picked by a chain of selects on the group,
+// so they stay in kernel arguments.  Column c of the launch keeps its partial
+// sums in slot c (W ranges of panel_rows each).
+template <int BLOCK, typename ValT, typename VecT>
+__global__ __launch_bounds__(BLOCK) void mv_bucket_cols(
+    const uint32_t *__restrict__ packed, const ValT *__restrict__ val, const int2 *__restrict__ blocks,
+    const int32_t *__restrict__ wg_blk, const int32_t *__restrict__ wg_order, MvGroups<VecT> groups, int ngroups,
+    double *__restrict__ partial, int panel_rows, int W)
+{
+    constexpr int NW = BLOCK / WAVE;
+    extern __shared__ double ypan[];
+    const int xcd = blockIdx.x % 8, i = blockIdx.x / 8;
+    const int g = i % ngroups, at = (i / ngroups) * 8 + xcd;
+    if (at >= W) return;
+    const int range = wg_order[at];
+    const VecT *x = groups.x[0];
+    int64_t ld = groups.ld[0];
+    int kc = groups.kc[0], slot = groups.slot[0];
+#pragma unroll
+    for (int t = 1; t < MULTI_MAX; ++t) {
+        x = g == t ? groups.x[t] : x;
+        ld = g == t ? groups.ld[t] : ld;
+        kc = g == t ? groups.kc[t] : kc;
+        slot = g == t ? groups.slot[t] : slot;
+    }
+    const int64_t col_stride = (int64_t)W * panel_rows;
+    double *out = partial + slot * col_stride + (int64_t)range * panel_rows;
+    const int32_t *wb = wg_blk + (int64_t)range * (NW + 1);
+    auto run = [&](auto cols, auto wide) {
+        mv_range_cols<BLOCK, ValT, VecT, decltype(cols)::value, decltype(wide)::value>(
+            packed, val, blocks, wb, x, ld, out, col_stride, panel_rows, ypan);
+    };
+    // a block spans fewer than 65,536 columns: 32-bit byte offsets below this stride
+    if (ld * (int64_t)sizeof(VecT) < 65536) {
+        if (kc == 1) run(IntC<1>(), IntC<0>());
+        else if (kc == 2) run(IntC<2>(), IntC<0>());
+        else if (kc == 3) run(IntC<3>(), IntC<0>());
+        else run(IntC<4>(), IntC<0>());
+    } else {
+        if (kc == 1) run(IntC<1>(), IntC<1>());
+        else if (kc == 2) run(IntC<2>(), IntC<1>());
+        else if (kc == 3) run(IntC<3>(), IntC<1>());
+        else run(IntC<4>(), IntC<1>());
+    }
 }
 
 // y[caller row] = sum over the panel's workgroups of their partials.  Internal
-// row r belongs to panel r mod npanels, at panel-local row r / npanels; threads
-// walk the panels one after another so each reads consecutive partials.  Eight
-// lanes share a row: lane t adds workgroups t, t+8, t+16, ... in ascending
-// order, then the eight sums are combined by a fixed butterfly, so the order
-// of every addition is fixed.
+// row r belongs to panel r mod npanels, at panel-local row r / npanels; a
+// workgroup takes 32 consecutive rows of one panel, eight threads a row: thread t
+// adds workgroups t, t+8, t+16, ... in ascending order with sixteen loads in
+// flight (a chain of dependent trips to memory bounds this kernel, not its
+// bytes), then the eight sums are combined pairwise, so the order of every
+// addition is fixed.  Column blockIdx.y: its partials start col_stride doubles
+// further, its output is out.u[column].
 template <typename VecT>
-__global__ void mv_reduce(const double *__restrict__ partial, int panel_rows, const PanelDesc *__restrict__ panels,
-                          int npanels, int64_t rows, const int32_t *__restrict__ inv, VecT *__restrict__ y, int64_t ldy,
-                          int64_t col_stride)
+__global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ partial, int panel_rows, int panel_blocks,
+                                                 const PanelDesc *__restrict__ panels, int npanels,
+                                                 const int32_t *__restrict__ inv, ColOut<VecT> out, int64_t col_stride)
 {
-    // column blockIdx.y: its partials start col_stride doubles further, its output one entry further
-    partial += blockIdx.y * col_stride;
-    y += blockIdx.y;
-    const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t slot = g >> 3;              // panel * panel_rows + panel-local row
-    const int t = (int)(g & 7);
-    const int p = (int)(slot / panel_rows);
-    const int local = (int)(slot - (int64_t)p * panel_rows);
-    const int64_t r = (int64_t)local * npanels + p;
-    const bool live = p < npanels && r < rows;
+    __shared__ double sums[8][32];
+    VecT *y = out.u[0];
+    int64_t ldy = out.ld[0];
+#pragma unroll
+    for (int c = 1; c < MULTI_MAX; ++c) {
+        y = blockIdx.y == c ? out.u[c] : y;
+        ldy = blockIdx.y == c ? out.ld[c] : ldy;
+    }
+    const int p = blockIdx.x / panel_blocks;
+    const int local = (blockIdx.x - p * panel_blocks) * 32 + (threadIdx.x & 31);
+    const int t = threadIdx.x >> 5;
+    const PanelDesc pd = panels[p];
+    const bool live = local < pd.rows;
     double s = 0.0;
     if (live) {
-        const PanelDesc pd = panels[p];
-        const double *src = partial + (int64_t)pd.wg0 * panel_rows + local;
-        int w = t;
-        for (; w + 24 < pd.nwg; w += 32) {
-            // four loads in flight, added in the same order as one at a time
-            const double a0 = src[(int64_t)w * panel_rows], a1 = src[(int64_t)(w + 8) * panel_rows];
-            const double a2 = src[(int64_t)(w + 16) * panel_rows], a3 = src[(int64_t)(w + 24) * panel_rows];
-            s += a0;
-            s += a1;
-            s += a2;
-            s += a3;
+        const double *src = partial + blockIdx.y * col_stride + (int64_t)pd.wg0 * panel_rows + local;
+        for (int w = t; w < pd.nwg; w += 8 * 16) {
+            double a[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) a[i] = w + 8 * i < pd.nwg ? src[(int64_t)(w + 8 * i) * panel_rows] : 0.0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (w + 8 * i < pd.nwg) s += a[i];
         }
-        for (; w < pd.nwg; w += 8) s += src[(int64_t)w * panel_rows];
     }
-    s += __shfl_xor(s, 1, 8);
-    s += __shfl_xor(s, 2, 8);
-    s += __shfl_xor(s, 4, 8);
-    if (live && t == 0) y[(int64_t)(inv ? inv[r] : r) * ldy] = (VecT)s;
+    sums[t][threadIdx.x & 31] = s;
+    __syncthreads();
+    if (t == 0 && live) {
+        const int l = threadIdx.x;
+        const double y0 = (sums[0][l] + sums[1][l]) + (sums[2][l] + sums[3][l]);
+        const double y1 = (sums[4][l] + sums[5][l]) + (sums[6][l] + sums[7][l]);
+        const int64_t r = (int64_t)local * npanels + p;
+        y[(int64_t)(inv ? inv[r] : r) * ldy] = (VecT)(y0 + y1);
+    }
 }
 
 // Multi-vector helpers over column tables (k <= MULTI_MAX columns).
@@ -674,43 +930,83 @@ void fill_tables(int k, const void *const *in, const int64_t *ldi, void *const *
     }
 }
 
-// k right-hand sides run as k passes of the scatter kernel over strided
-// columns of X and Y.
+// Sums the partials of `k` columns into their outputs.
+template <typename VecT>
+int launch_mv_reduce(const spw_matrix_s &A, const double *partial, int k, const ColOut<VecT> &out, hipStream_t stream)
+{
+    ProfScope ps(stream, "mv_reduce");
+    const unsigned panel_blocks = blocks_for(A.panel_rows, 32);
+    hipLaunchKernelGGL(mv_reduce<VecT>, dim3((unsigned)(A.n_panels * panel_blocks), (unsigned)k), dim3(256), 0, stream,
+                       partial, (int)A.panel_rows, (int)panel_blocks, A.d_panels, (int)A.n_panels,
+                       A.relabeled ? A.d_inv : nullptr, out, A.mv_wgs * A.panel_rows);
+    return (int)hipGetLastError();
+}
+
+// Columns of one launch that share an LDS panel: as many as fit, at most MV_COLS.
+int mv_cols_together(const spw_matrix_s &A)
+{
+    return (int)std::max<int64_t>(1, std::min<int64_t>(MV_COLS, mv_lds_rows_limit(SPW_F64, 1) / A.panel_rows));
+}
+
+// One launch of the scatter kernel for k <= MULTI_MAX columns with their own
+// inputs and outputs (the partial sums hold k columns), then their reductions in
+// one launch.  Columns that are adjacent entries of the same rows are taken
+// in groups of up to mv_cols_together, of sizes that differ by one at most.
+template <typename ValT, typename VecT>
+int mv_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const ColOut<VecT> &out, hipStream_t stream)
+{
+    int e;
+    const int W = (int)A.mv_wgs;
+    if (W > 0) {
+        static const bool attr = allow_full_lds(mv_bucket_cols<MV_BLOCK, ValT, VecT>);
+        (void)attr;
+        const int most = mv_cols_together(A);
+        MvGroups<VecT> gr{};
+        int ng = 0, widest = 1;
+        for (int c = 0; c < k;) {
+            int run = 1;                          // adjacent columns from c on
+            while (c + run < k && in.v[c + run] == in.v[c] + run && in.ld[c + run] == in.ld[c]) ++run;
+            const int parts = (run + most - 1) / most;
+            for (int q = 0; q < parts; ++q, ++ng) {
+                const int a = run * q / parts, n = run * (q + 1) / parts - a;
+                gr.x[ng] = in.v[c + a];
+                gr.ld[ng] = in.ld[c + a];
+                gr.kc[ng] = n;
+                gr.slot[ng] = c + a;
+                widest = std::max(widest, n);
+            }
+            c += run;
+        }
+        ProfScope ps(stream, "mv_bucket");
+        hipLaunchKernelGGL((mv_bucket_cols<MV_BLOCK, ValT, VecT>), dim3((unsigned)(8 * ng * ((W + 7) / 8))),
+                           dim3(MV_BLOCK), (size_t)A.panel_rows * 8 * (size_t)widest, stream,
+                           (const uint32_t *)A.d_mpacked, (const ValT *)A.d_mval, (const int2 *)A.d_mblocks,
+                           A.d_wg_blk, A.d_wg_order, gr, ng, A.scratch.partial_cols, (int)A.panel_rows, W);
+        if ((e = (int)hipGetLastError())) return e;
+    }
+    return launch_mv_reduce<VecT>(A, A.scratch.partial_cols, k, out, stream);
+}
+
+// k right-hand sides, up to pcols columns a launch when the multi-column partial
+// sums are there, else one column after another.
 template <typename ValT, typename VecT>
 int mv_typed(const spw_matrix_s &A, int32_t k, const VecT *x, int64_t ldx, VecT *y, int64_t ldy, hipStream_t stream)
 {
     if (A.rows == 0) return 0;
     int e;
-    const unsigned red_blocks = blocks_for(A.n_panels * A.panel_rows * 8, 256);
     if (k > 1 && A.mv_wgs > 0 && A.scratch.partial_cols && A.scratch.pcols > 0) {
-        // columns in batches of up to pcols, one launch per batch
-        static const bool attr_c = allow_full_lds(mv_bucket_cols<MV_BLOCK, ValT, VecT, false>);
-        (void)attr_c;
-        const int W = (int)A.mv_wgs, cus = device_cu_count(A.device);
-        for (int32_t c0 = 0; c0 < k; c0 += A.scratch.pcols) {
-            const int kb = (int)std::min<int64_t>(A.scratch.pcols, k - c0);
-            // S ranges per workgroup, the fewest for which all kb * ceil(W / S)
-            // workgroups run at once (one per CU): a few workgroups over the CU
-            // count would run as a second round and double the time
-            int S = (int)std::max<int64_t>(1, ((int64_t)W * kb + cus - 1) / cus);
-            while (S < W && (int64_t)kb * ((W + S - 1) / S) > cus) ++S;
-            const int G = (W + S - 1) / S;
-            const unsigned grid = (unsigned)(kb * 8 * ((G + 7) / 8));
-            {
-                ProfScope ps(stream, "mv_bucket");
-                hipLaunchKernelGGL((mv_bucket_cols<MV_BLOCK, ValT, VecT, false>), dim3(grid), dim3(MV_BLOCK),
-                                   (size_t)A.panel_rows * 8, stream, (const uint32_t *)A.d_mpacked,
-                                   (const ValT *)A.d_mval, (const int2 *)A.d_mblocks, A.d_wg_blk, x + c0, ldx,
-                                   ColIn<VecT>{}, A.scratch.partial_cols, (int)A.panel_rows, kb, W, S);
-                if ((e = (int)hipGetLastError())) return e;
+        const int most = std::min<int>(A.scratch.pcols, MULTI_MAX);
+        for (int32_t c0 = 0; c0 < k; c0 += most) {
+            const int kb = std::min<int>(most, k - c0);
+            ColIn<VecT> in{};
+            ColOut<VecT> out{};
+            for (int c = 0; c < kb; ++c) {
+                in.v[c] = x + c0 + c;
+                in.ld[c] = ldx;
+                out.u[c] = y + c0 + c;
+                out.ld[c] = ldy;
             }
-            {
-                ProfScope ps(stream, "mv_reduce");
-                hipLaunchKernelGGL(mv_reduce<VecT>, dim3(red_blocks, (unsigned)kb), dim3(256), 0, stream,
-                                   A.scratch.partial_cols, (int)A.panel_rows, A.d_panels, (int)A.n_panels, A.rows,
-                                   A.relabeled ? A.d_inv : nullptr, y + c0, ldy, (int64_t)W * A.panel_rows);
-                if ((e = (int)hipGetLastError())) return e;
-            }
+            if ((e = mv_cols_typed<ValT, VecT>(A, kb, in, out, stream))) return e;
         }
         return 0;
     }
@@ -722,17 +1018,14 @@ int mv_typed(const spw_matrix_s &A, int32_t k, const VecT *x, int64_t ldx, VecT 
             const size_t lds = (size_t)A.panel_rows * 8;
             hipLaunchKernelGGL((mv_bucket<MV_BLOCK, ValT, VecT>), dim3((unsigned)A.mv_wgs), dim3(MV_BLOCK), lds,
                                stream, (const uint32_t *)A.d_mpacked, (const ValT *)A.d_mval,
-                               (const int2 *)A.d_mblocks, A.d_wg_blk, x + c, ldx, A.scratch.partial,
+                               (const int2 *)A.d_mblocks, A.d_wg_blk, A.d_wg_order, x + c, ldx, A.scratch.partial,
                                (int)A.panel_rows);
             if ((e = (int)hipGetLastError())) return e;
         }
-        {
-            ProfScope ps(stream, "mv_reduce");
-            hipLaunchKernelGGL(mv_reduce<VecT>, dim3(red_blocks), dim3(256), 0, stream, A.scratch.partial,
-                               (int)A.panel_rows, A.d_panels, (int)A.n_panels, A.rows, A.relabeled ? A.d_inv : nullptr,
-                               y + c, ldy, (int64_t)0);
-            if ((e = (int)hipGetLastError())) return e;
-        }
+        ColOut<VecT> out{};
+        out.u[0] = y + c;
+        out.ld[0] = ldy;
+        if ((e = launch_mv_reduce<VecT>(A, A.scratch.partial, 1, out, stream))) return e;
     }
     return 0;
 }
@@ -818,47 +1111,6 @@ int launch_mv(const spw_matrix_s &A, spw_dtype vdt, int32_t k, const void *x, in
     });
 }
 
-namespace {
-// One launch of the scatter kernel for k <= MULTI_MAX columns with their own
-// input bases and strides, then the fixed-order reduction of each column into
-// its own output: every column is summed exactly as a single-column call sums
-// it, and the matrix is read once for the k columns.
-template <typename ValT, typename VecT>
-int mv_cols_tab(const spw_matrix_s &A, int k, const ColIn<VecT> &xin, VecT *const *out, const int64_t *ldo,
-                hipStream_t stream)
-{
-    if (A.rows == 0) return 0;
-    int e;
-    const int W = (int)A.mv_wgs;
-    if (W > 0) {
-        static const bool attr_t = allow_full_lds(mv_bucket_cols<MV_BLOCK, ValT, VecT, true>);
-        (void)attr_t;
-        const int cus = device_cu_count(A.device);
-        // as in the row-major form: the fewest ranges per workgroup S for which
-        // all k * ceil(W / S) workgroups run at once
-        int S = (int)std::max<int64_t>(1, ((int64_t)W * k + cus - 1) / cus);
-        while (S < W && (int64_t)k * ((W + S - 1) / S) > cus) ++S;
-        const int G = (W + S - 1) / S;
-        const unsigned grid = (unsigned)(k * 8 * ((G + 7) / 8));
-        ProfScope ps(stream, "mv_bucket");
-        hipLaunchKernelGGL((mv_bucket_cols<MV_BLOCK, ValT, VecT, true>), dim3(grid), dim3(MV_BLOCK),
-                           (size_t)A.panel_rows * 8, stream, (const uint32_t *)A.d_mpacked, (const ValT *)A.d_mval,
-                           (const int2 *)A.d_mblocks, A.d_wg_blk, (const VecT *)nullptr, (int64_t)0, xin,
-                           A.scratch.partial_cols, (int)A.panel_rows, k, W, S);
-        if ((e = (int)hipGetLastError())) return e;
-    }
-    const unsigned red_blocks = blocks_for(A.n_panels * A.panel_rows * 8, 256);
-    for (int c = 0; c < k; ++c) {
-        ProfScope ps(stream, "mv_reduce");
-        hipLaunchKernelGGL(mv_reduce<VecT>, dim3(red_blocks), dim3(256), 0, stream,
-                           A.scratch.partial_cols + (int64_t)c * W * A.panel_rows, (int)A.panel_rows, A.d_panels,
-                           (int)A.n_panels, A.rows, A.relabeled ? A.d_inv : nullptr, out[c], ldo[c], (int64_t)0);
-        if ((e = (int)hipGetLastError())) return e;
-    }
-    return 0;
-}
-}  // namespace
-
 int launch_mv_cols(const spw_matrix_s &A, spw_dtype vdt, int32_t k, const void *const *in, const int64_t *ldi,
                    void *const *out, const int64_t *ldo, void *stream)
 {
@@ -874,14 +1126,11 @@ int launch_mv_cols(const spw_matrix_s &A, spw_dtype vdt, int32_t k, const void *
     return with_types(A.value_storage, vdt, [&](auto vt, auto xt) {
         using ValT = decltype(vt);
         using VecT = decltype(xt);
-        ColIn<VecT> ti{};
-        VecT *to[MULTI_MAX];
-        for (int c = 0; c < k; ++c) {
-            ti.v[c] = (const VecT *)in[c];
-            ti.ld[c] = ldi[c];
-            to[c] = (VecT *)out[c];
-        }
-        return mv_cols_tab<ValT, VecT>(A, k, ti, to, ldo, (hipStream_t)stream);
+        ColIn<VecT> ti;
+        ColOut<VecT> to;
+        fill_tables<VecT>(k, in, ldi, out, ldo, ti, to);
+        if (A.rows == 0) return 0;
+        return mv_cols_typed<ValT, VecT>(A, k, ti, to, (hipStream_t)stream);
     });
 }
 
