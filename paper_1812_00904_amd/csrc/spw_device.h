@@ -510,6 +510,24 @@ __device__ __forceinline__ void vtm_reduce_chunk(const double *prod, uint32_t ma
     vtm_chunk_tail<VecT>(run, k, hk, head_sum, multi, my_n > 0, ci, segcol, c, lane, u, ldu, carry, kk, col);
 }
 
+// The sum of column cc's carries over a zone's chunks a .. b (k columns): the right one
+// of a, then the left ones, in ascending chunk order, with eight loads in flight (the chain
+// of dependent trips to memory is what bounds the zone kernels: a zone has up to a hundred
+// chunks).
+__device__ __forceinline__ double zone_sum(const double *__restrict__ carry, int a, int b, int64_t k, int cc)
+{
+    double s = carry[(2 * (int64_t)a + 1) * k + cc];
+    for (int c = a + 1; c <= b; c += 8) {
+        double t[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[i] = carry[2 * (int64_t)min(c + i, b) * k + cc];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (c + i <= b) s += t[i];
+    }
+    return s;
+}
+
 // dst[i] = src(i) for i < n, by the BLOCK threads of a workgroup, with U loads
 // in flight per thread (a load-then-store loop would wait for every load).
 template <int BLOCK, int U, typename T, typename Src>

@@ -199,10 +199,7 @@ __global__ void zone_fixup(const int32_t *__restrict__ zcol, const int32_t *__re
 {
     const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (k >= nz) return;
-    const int a = zfirst[k], b = zlast[k];
-    double s = carry[2 * a + 1];
-    for (int c = a + 1; c <= b; ++c) s += carry[2 * c];
-    u[zcol[k]] = (VecT)s;
+    u[zcol[k]] = (VecT)zone_sum(carry, zfirst[k], zlast[k], 1, 0);
 }
 
 // Renumber a short vector: out[r] = in[inv[r]].
@@ -727,10 +724,7 @@ __global__ void zone_fixup_tab(const int32_t *__restrict__ zcol, const int32_t *
     if (g >= nz * k) return;
     const int64_t z = g / k;
     const int cc = (int)(g - z * k);
-    const int a = zfirst[z], b = zlast[z];
-    double s = carry[(2 * (int64_t)a + 1) * k + cc];
-    for (int c = a + 1; c <= b; ++c) s += carry[(2 * (int64_t)c) * k + cc];
-    out.u[cc][(int64_t)zcol[z] * out.ld[cc]] = (VecT)s;
+    out.u[cc][(int64_t)zcol[z] * out.ld[cc]] = (VecT)zone_sum(carry, zfirst[z], zlast[z], k, cc);
 }
 
 // out[r*k + c] = column c of the table at caller row inv[r] (or r).

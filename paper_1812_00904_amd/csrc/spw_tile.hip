@@ -428,9 +428,7 @@ __global__ void zone_fixup_batch(const int32_t *__restrict__ zcol, const int32_t
     const int64_t z = g / k;
     const int cc = (int)(g - z * k);
     const int a = zfirst[z], b = zlast[z];
-    double s = carry[(2 * (int64_t)a + 1) * k + cc];
-    for (int c = a + 1; c <= b; ++c) s += carry[(2 * (int64_t)c) * k + cc];
-    U[(int64_t)zcol[z] * ldu + cc] = (VoutT)s;
+    U[(int64_t)zcol[z] * ldu + cc] = (VoutT)zone_sum(carry, a, b, k, cc);
 }
 
 template <typename VoutT>
@@ -503,8 +501,9 @@ int launch_tile_items(const spw_matrix_s &A, const ColDot &C, int k, const VecT 
 #define SPW_TILE(LL, WW) \
     if (L == LL && CW == WW) return go(cdot_tile<IdxT, ValT, VecT, LL, ITEMS, WW, OutT>);
     SPW_TILE(2, 1) SPW_TILE(4, 1) SPW_TILE(8, 1) SPW_TILE(16, 1) SPW_TILE(32, 1) SPW_TILE(64, 1)
-    SPW_TILE(1, 2) SPW_TILE(2, 2) SPW_TILE(4, 2) SPW_TILE(8, 2) SPW_TILE(16, 2) SPW_TILE(32, 2)
+    SPW_TILE(1, 2) SPW_TILE(2, 2) SPW_TILE(4, 2)
     if constexpr (sizeof(VecT) == 4) {
+        SPW_TILE(8, 2) SPW_TILE(16, 2) SPW_TILE(32, 2)
         SPW_TILE(1, 4) SPW_TILE(2, 4) SPW_TILE(4, 4) SPW_TILE(8, 4) SPW_TILE(16, 4)
     }
 #undef SPW_TILE
@@ -535,7 +534,11 @@ int coldot_batch_typed(const spw_matrix_s &A, const ColDot &C, const int32_t *in
         if ((e = (int)hipGetLastError())) return e;
     }
     if (C.nnz == 0) return 0;
-    {
+    constexpr spw_dtype vdt = sizeof(VecT) == 8 ? SPW_F64 : SPW_F32;
+    if (coldot_run_takes(A, C, vdt, k, ldv)) {
+        ProfScope ps(stream, "cdot_run");
+        if ((e = launch_coldot_run(A, C, inv, vdt, k, V, ldv, U, ldu, stream, sizeof(OutT) == 8))) return e;
+    } else {
         ProfScope ps(stream, "cdot_tile");
         const VecT *Vin = V;
         int64_t ldin = ldv;
