@@ -1183,8 +1183,8 @@ spw_status grow_cgls(spw_matrix_s &A, int64_t hist_len)
         if ((st = dev_alloc(A, &W.t, std::max<int64_t>(A.m, 1), "CGLS t"))) return st;
         if ((st = dev_alloc(A, &W.s, std::max<int64_t>(A.n, 1), "CGLS s"))) return st;
         if ((st = dev_alloc(A, &W.p, std::max<int64_t>(A.n, 1), "CGLS p"))) return st;
-        if ((st = dev_alloc(A, &W.partial, cgls_dot_parts(), "CGLS partial sums"))) return st;
-        if ((st = dev_alloc(A, &W.scal, 4, "CGLS scalars"))) return st;
+        if ((st = dev_alloc(A, &W.partial, cgls_partials(), "CGLS partial sums"))) return st;
+        if ((st = dev_alloc(A, &W.scal, 2, "CGLS scalars"))) return st;
     }
     if (W.hist_cap >= hist_len) return SPW_OK;
     if (W.hist) {
@@ -1928,42 +1928,59 @@ static spw_status spw_cgls_impl(spw_matrix A, spw_dtype vdt, const void *b, void
     w.scal = W.scal;
     w.hist_gamma = W.hist;
     w.hist_rho = W.hist + iters + 1;
-    auto vec = [&](CglsVecOp op) -> spw_status {
-        const int e = launch_cgls_vec(op, w, stream);
+    // A^T r by column dots over renumbered rows: the step that writes r writes it in
+    // their order too
+    const bool renumber = A->format == SPW_CSC && A->relabeled && A->nnz > 0;
+    if (renumber) {
+        w.rank = A->d_rank;
+        w.perm = A->scratch.vperm;
+    }
+    auto done = [&](int e) -> spw_status {
         if (e) return fail(SPW_ERR_DEVICE, std::string("spw_cgls: kernel launch failed: ") +
                                                hipGetErrorString((hipError_t)e));
         return SPW_OK;
     };
-    // one iteration k: t = A s_k, q_k = t + beta_k q_{k-1} (= A p_k), alpha_k, r_{k+1};
-    // p_k = s_k + beta_k p_{k-1}, x_{k+1} = x_k + alpha_k p_k; s_{k+1} = A^T r_{k+1}, gamma_{k+1},
-    // beta_{k+1}.  The first iteration takes q_0 = t and p_0 = s_0.  Every CGLS_REFRESH-th
-    // iteration forms p_k first and takes q_k = A p_k with a product of its own, so the
-    // rounding that the linear recurrence for q gathers is dropped at that point.
-    auto iteration = [&](bool first, bool refresh) -> spw_status {
+    auto vec = [&](CglsVecOp op, int64_t k) { return done(launch_cgls_vec(op, w, k, stream)); };
+    // out = A in (with A), out = A^T in: the single-vector products (the stream is claimed above)
+    auto product = [&](bool with_a, const double *in, double *out, bool renumbered) {
+        const bool scatter = (A->format == SPW_CSC) == with_a;
+        return done(scatter ? launch_mv(*A, SPW_F64, 1, in, 1, out, 1, stream)
+                            : launch_vtm(*A, SPW_F64, in, out, stream, renumbered));
+    };
+    // iteration k: t = A s_k, q_k = t + beta_k q_{k-1} (= A p_k), alpha_k, r_{k+1};
+    // p_k = s_k + beta_k p_{k-1}, x_{k+1} = x_k + alpha_k p_k; s_{k+1} = A^T r_{k+1}.  The first
+    // iteration takes q_0 = t and p_0 = s_0.  Every CGLS_REFRESH-th iteration forms p_k first
+    // and takes q_k = A p_k with a product of its own, so the rounding that the linear
+    // recurrence for q gathers is dropped at that point.
+    auto iteration = [&](int64_t k) -> spw_status {
+        const bool first = k == 0, refresh = k > 0 && (k + 1) % CGLS_REFRESH == 0;
         spw_status s2;
         if (refresh) {
-            if ((s2 = vec(CglsVecOp::P))) return s2;                                                   // p = s + beta p
-            if ((s2 = run_product(A, true, SPW_F64, 1, w.p, 1, w.t, 1, stream, "spw_cgls"))) return s2;  // t = A p
-            if ((s2 = vec(CglsVecOp::ALPHA_R0))) return s2;                                            // q = t
-            if ((s2 = vec(CglsVecOp::X))) return s2;
+            if ((s2 = vec(CglsVecOp::GAMMA, k))) return s2;
+            if ((s2 = vec(CglsVecOp::P, k))) return s2;                            // p = s + beta p
+            if ((s2 = product(true, w.p, w.t, false))) return s2;                  // t = A p
+            if ((s2 = vec(CglsVecOp::Q_DIRECT, k))) return s2;
+            if ((s2 = vec(CglsVecOp::R, k))) return s2;
+            if ((s2 = vec(CglsVecOp::X, k))) return s2;
         } else {
-            if ((s2 = run_product(A, true, SPW_F64, 1, w.s, 1, w.t, 1, stream, "spw_cgls"))) return s2;   // t = A s
-            if ((s2 = vec(first ? CglsVecOp::ALPHA_R0 : CglsVecOp::ALPHA_R))) return s2;
-            if ((s2 = vec(first ? CglsVecOp::PX0 : CglsVecOp::PX))) return s2;
+            if ((s2 = product(true, w.s, w.t, false))) return s2;                  // t = A s
+            if ((s2 = vec(first ? CglsVecOp::Q_FIRST : CglsVecOp::Q, k))) return s2;
+            if ((s2 = vec(CglsVecOp::R, k))) return s2;
+            if ((s2 = vec(first ? CglsVecOp::PX_FIRST : CglsVecOp::PX, k))) return s2;
         }
-        if ((s2 = run_product(A, false, SPW_F64, 1, w.r, 1, w.s, 1, stream, "spw_cgls"))) return s2;  // s = A^T r
-        return vec(CglsVecOp::GAMMA);
+        if ((s2 = product(false, renumber ? w.perm : w.r, w.s, renumber))) return s2;   // s = A^T r
+        return vec(CglsVecOp::S_NORM, k + 1);
     };
-    // r_0 = b - A x_0, s_0 = A^T r_0, gamma_0 = ||s_0||^2
-    if ((st = run_product(A, true, SPW_F64, 1, x, 1, w.q, 1, stream, "spw_cgls"))) return st;
-    if ((st = vec(CglsVecOp::R_INIT))) return st;
-    if ((st = run_product(A, false, SPW_F64, 1, w.r, 1, w.s, 1, stream, "spw_cgls"))) return st;
-    if ((st = vec(CglsVecOp::GAMMA0))) return st;
-    // Every iteration after the first launches the same kernels with the same
-    // arguments (the history index lives on the device), so a caller may
-    // capture a whole call without a history in a graph and replay it.
-    for (int64_t k = 1; k <= iters; ++k)
-        if ((st = iteration(k == 1, k > 1 && k % CGLS_REFRESH == 0))) return st;
+    // r_0 = b - A x_0, s_0 = A^T r_0
+    if ((st = product(true, w.x, w.q, false))) return st;
+    if ((st = vec(CglsVecOp::R_INIT, 0))) return st;
+    if ((st = product(false, w.r, w.s, false))) return st;
+    if ((st = vec(CglsVecOp::S_NORM, 0))) return st;
+    // The launches and their arguments follow from the call's arguments alone, so a caller
+    // may capture a whole call without a history in a graph and replay it.
+    for (int64_t k = 0; k < iters; ++k)
+        if ((st = iteration(k))) return st;
+    if ((st = vec(CglsVecOp::GAMMA, iters))) return st;
     if ((st = release_stream(*A, stream, "spw_cgls"))) return st;
     if (hist) {
         if (hipMemcpyAsync(hist, W.hist, (size_t)hl * sizeof(double), hipMemcpyDeviceToHost, (hipStream_t)stream) !=

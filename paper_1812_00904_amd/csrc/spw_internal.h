@@ -82,8 +82,8 @@ struct ColDot {
 struct CglsScratch {
     double *r = nullptr, *q = nullptr, *t = nullptr;   // m entries each
     double *s = nullptr, *p = nullptr;        // n entries each
-    double *partial = nullptr;                // partial sums of one inner product
-    double *scal = nullptr;                   // gamma, alpha, beta
+    double *partial = nullptr;                // partial sums of an iteration's inner products
+    double *scal = nullptr;                   // alpha, beta
     double *hist = nullptr;                   // hist_cap entries: gamma history, then rho history
     int64_t hist_cap = 0;
 };
@@ -163,7 +163,8 @@ namespace spw {
 // All return hipError_t as int (0 = success).  Implemented in spw_kernels.hip.
 
 // Single-vector column dots (u = B^T v) over A.cd.
-int launch_vtm(const spw_matrix_s &A, spw_dtype vdt, const void *v, void *u, void *stream);
+// renumbered: v is in the matrix's own row order already (in scratch.vperm, when the rows are renumbered).
+int launch_vtm(const spw_matrix_s &A, spw_dtype vdt, const void *v, void *u, void *stream, bool renumbered = false);
 // Column dots for k <= 8 columns in one pass: column c reads in[c] (stride
 // ldi[c]) and writes out[c] (stride ldo[c]); in/out/ldi/ldo are host arrays.
 // Every column is bit-identical to launch_vtm on it.
@@ -234,32 +235,34 @@ int64_t vtm_hot_rows_limit(spw_dtype vdt);
 int device_cu_count(int device);
 
 // CGLS vector steps (spw_solve.hip).  x and p have n entries, b, r and q
-// have m; hist_gamma / hist_rho receive the inner products of iteration k.
+// have m; hist_gamma / hist_rho receive the inner products of every iteration.
 struct CglsWork {
     int64_t m = 0, n = 0;
     const double *b = nullptr;
     double *x = nullptr, *r = nullptr, *q = nullptr, *t = nullptr, *s = nullptr, *p = nullptr;
     double *partial = nullptr, *scal = nullptr, *hist_gamma = nullptr, *hist_rho = nullptr;
+    const int32_t *rank = nullptr;      // with perm: r is also written there, renumbered
+    double *perm = nullptr;
 };
-// The steps around the two products of a CGLS iteration.  An iteration takes
+// The steps around the two products of iteration k = 0, 1, ..., which takes
 // t = A s (s = A^T r of the previous step) and forms q = A p by linearity,
 // q = t + beta q, so that the long vector update (p, then x) runs just before
 // the A^T r product rather than just before the A p product.
 enum class CglsVecOp : int {
     R_INIT,      // r = b - q (q = A x_0); rho_0 = ||r||^2
-    GAMMA0,      // gamma_0 = ||s||^2 (s = A^T r_0)
-    ALPHA_R0,    // first iteration: q = t; alpha = gamma / ||q||^2; r = r - alpha q; rho_k = ||r||^2
-    ALPHA_R,     // q = t + beta q; alpha = gamma / ||q||^2; r = r - alpha q; rho_k = ||r||^2
-    PX0,         // first iteration: p = s; x = x + alpha p
-    PX,          // p = s + beta p; x = x + alpha p
+    S_NORM,      // the partial sums of gamma_k = ||s||^2, which Q_FIRST, Q or GAMMA finish
+    GAMMA,       // gamma_k, beta_k = gamma_k / gamma_{k-1}
+    Q_FIRST,     // first iteration: gamma_0; q = t; partial sums of ||q||^2
+    Q,           // gamma_k, beta_k; q = t + beta q; the same
+    Q_DIRECT,    // an iteration that forms q = A p directly (after GAMMA): q = t; the same
+    R,           // alpha = gamma_k / ||q||^2; r = r - alpha q; partial sums of rho_{k+1} = ||r||^2
+    PX_FIRST,    // first iteration: rho_1; p = s; x = x + alpha p
+    PX,          // rho_{k+1}; p = s + beta p; x = x + alpha p
     P,           // p = s + beta p          (an iteration that forms q = A p directly)
-    X,           // x = x + alpha p
-    GAMMA        // gamma_k = ||s||^2 (s = A^T r); beta = gamma_k / gamma_{k-1}
+    X            // rho_{k+1}; x = x + alpha p
 };
-// The history index advances on the device (see spw_solve.hip), so the
-// launches of one iteration are the same every time.
-int launch_cgls_vec(CglsVecOp op, const CglsWork &w, void *stream);
-int64_t cgls_dot_parts();
+int launch_cgls_vec(CglsVecOp op, const CglsWork &w, int64_t k, void *stream);
+int64_t cgls_partials();
 
 // Profiling hooks (spw_profile.cpp).
 bool profile_on();

@@ -832,7 +832,7 @@ int launch_vtm_wave(const spw_matrix_s &A, const VecT *vin, int k, const ColOut<
 }
 
 template <typename ValT, typename VecT>
-int vtm_typed(const spw_matrix_s &A, const VecT *v, VecT *u, hipStream_t stream)
+int vtm_typed(const spw_matrix_s &A, const VecT *v, VecT *u, bool renumbered, hipStream_t stream)
 {
     const ColDot &C = A.cd;
     int e;
@@ -845,7 +845,7 @@ int vtm_typed(const spw_matrix_s &A, const VecT *v, VecT *u, hipStream_t stream)
     }
     if (C.nnz == 0) return 0;
     const VecT *vin = v;
-    if (A.relabeled) {
+    if (A.relabeled && !renumbered) {
         ProfScope ps(stream, "gather_vec");
         VecT *vp = reinterpret_cast<VecT *>(A.scratch.vperm);
         hipLaunchKernelGGL(gather_vec<VecT>, dim3(blocks_for(A.rows, 256)), dim3(256), 0, stream, A.d_inv, A.rows, v,
@@ -1051,12 +1051,12 @@ int device_cu_count(int device)
     return cus > 0 ? cus : 256;
 }
 
-int launch_vtm(const spw_matrix_s &A, spw_dtype vdt, const void *v, void *u, void *stream)
+int launch_vtm(const spw_matrix_s &A, spw_dtype vdt, const void *v, void *u, void *stream, bool renumbered)
 {
     return with_types(A.value_storage, vdt, [&](auto vt, auto xt) {
         using ValT = decltype(vt);
         using VecT = decltype(xt);
-        return vtm_typed<ValT, VecT>(A, (const VecT *)v, (VecT *)u, (hipStream_t)stream);
+        return vtm_typed<ValT, VecT>(A, (const VecT *)v, (VecT *)u, renumbered, (hipStream_t)stream);
     });
 }
 

@@ -10,16 +10,22 @@
 // back, instead of right before the A p product, whose streaming they slowed.
 //
 // Every inner product is formed in a fixed order, so a solve is bit-identical
-// from run to run: DOT_PARTS workgroups each sum a fixed contiguous range
+// from run to run: dot_parts(len) workgroups each sum a fixed contiguous range
 // (thread t adds elements t, t + BLOCK, ... of the range in order, then a
-// fixed butterfly inside each wave and the waves in ascending order), and one
-// workgroup adds the DOT_PARTS partial sums the same way.  The step sizes stay
-// on the device: the scalar kernel that finishes an inner product also forms
-// alpha or beta, so the loop never waits for the host.
+// fixed butterfly inside each wave and the waves in ascending order), and whoever needs
+// the product adds those partial sums the same way.  The step sizes stay on the
+// device, so the loop never waits for the host.
 //
-// Scalars slot layout (binary64): [0] gamma = ||A^T r||^2 of the current
-// iterate, [1] alpha, [2] beta, [3] the iteration the history is at (an
-// integer, so one captured iteration can be replayed unchanged).
+// On small and ordinary matrices the loop is bound by its chain of short kernels, so
+// the partial sums are finished by the kernel that uses them, not by a launch of one
+// workgroup in between: every workgroup of a short-vector pass adds the partial sums
+// itself (they are few for a short vector), and its first one writes the history entry
+// and the step size down for the passes over the long vectors.  Four vector launches an
+// iteration instead of seven, and the residual is written in the order the next
+// product reads it: ten iterations on 10,007 x 500,000 with 5e6 nonzeros 790 -> 684 us.
+//
+// Scalars (binary64): [0] alpha, [1] beta of the iteration.  gamma_k = ||A^T r_k||^2 and
+// ||r_k||^2 live in the histories.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -31,29 +37,45 @@ namespace {
 
 constexpr int SV_BLOCK = 256;
 constexpr int SV_WAVE = 64;
-constexpr int DOT_PARTS = 1024;          // partial sums per inner product (one per workgroup)
-constexpr int S_GAMMA = 0, S_ALPHA = 1, S_BETA = 2, S_ITER = 3;
+constexpr int DOT_PARTS = 1024;          // partial sums per inner product, at most (one per workgroup)
+constexpr int S_ALPHA = 0, S_BETA = 1;
+
+// Partial sums of an inner product over len elements: one per 2,048, so that a short
+// vector has few of them to add up.
+__host__ __device__ inline int dot_parts(int64_t len)
+{
+    const int64_t p = (len + 2047) / 2048;
+    return (int)(p < 1 ? 1 : p > DOT_PARTS ? DOT_PARTS : p);
+}
 
 // Sum of one value per thread over a workgroup of SV_BLOCK threads, in a fixed
-// order: butterfly inside each wave, then the waves in ascending order.  The
-// result is valid in thread 0.
+// order: butterfly inside each wave, then the waves in ascending order.  Every
+// thread gets it.
 __device__ __forceinline__ double block_sum(double v, double *lds)
 {
     for (int off = SV_WAVE / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, SV_WAVE);
     const int wave = threadIdx.x / SV_WAVE, lane = threadIdx.x % SV_WAVE;
+    __syncthreads();                     // an earlier sum has been read
     if (lane == 0) lds[wave] = v;
     __syncthreads();
     double s = 0.0;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < SV_BLOCK / SV_WAVE; ++w) s += lds[w];
+    for (int w = 0; w < SV_BLOCK / SV_WAVE; ++w) s += lds[w];
     return s;
 }
 
-// Range of workgroup g out of DOT_PARTS over len elements.
+// The inner product whose partial sums these are.
+__device__ __forceinline__ double finish_dot(const double *__restrict__ partial, int parts, double *lds)
+{
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < parts; i += SV_BLOCK) acc += partial[i];
+    return block_sum(acc, lds);
+}
+
+// Range of workgroup g out of parts over len elements.
 __device__ __forceinline__ void part_range(int64_t len, int64_t &a, int64_t &e)
 {
-    a = len * (int64_t)blockIdx.x / DOT_PARTS;
-    e = len * ((int64_t)blockIdx.x + 1) / DOT_PARTS;
+    a = len * (int64_t)blockIdx.x / (int64_t)gridDim.x;
+    e = len * ((int64_t)blockIdx.x + 1) / (int64_t)gridDim.x;
 }
 
 // partial[g] = sum over workgroup g's range of a_i * a_i.  Eight loads are
@@ -79,19 +101,55 @@ __global__ __launch_bounds__(SV_BLOCK) void sq_part(const double *__restrict__ a
     if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
-// FIRST: q = t.  Otherwise q = t + beta q.  Either way partial[g] = sum of
-// q_i * q_i of the new q over workgroup g's range.
-template <bool FIRST>
-__global__ __launch_bounds__(SV_BLOCK) void q_step(double *__restrict__ q, const double *__restrict__ t, int64_t len,
-                                                   const double *__restrict__ scal, double *__restrict__ partial)
+// gamma_k from the partial sums of s; beta_k = gamma_k / gamma_{k-1} (0 for k = 0 and when
+// gamma_{k-1} is 0).  The first workgroup writes both down.
+__device__ __forceinline__ double finish_gamma(const double *__restrict__ spart, int sparts, int64_t k,
+                                               double *__restrict__ hist_gamma, double *__restrict__ scal, double *lds)
+{
+    const double gamma = finish_dot(spart, sparts, lds);
+    const double before = k > 0 ? hist_gamma[k - 1] : 0.0;
+    const double beta = before > 0.0 ? gamma / before : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        hist_gamma[k] = gamma;
+        scal[S_BETA] = beta;
+    }
+    return beta;
+}
+
+// One workgroup: gamma_k and beta_k, where no short-vector pass follows that finishes them.
+__global__ __launch_bounds__(SV_BLOCK) void gamma_step(const double *__restrict__ spart, int sparts, int64_t k,
+                                                       double *__restrict__ hist_gamma, double *__restrict__ scal)
 {
     __shared__ double lds[SV_BLOCK / SV_WAVE];
-    const double beta = FIRST ? 0.0 : scal[S_BETA];
+    finish_gamma(spart, sparts, k, hist_gamma, scal, lds);
+}
+
+// One workgroup: out[0] = the inner product.
+__global__ __launch_bounds__(SV_BLOCK) void dot_step(const double *__restrict__ partial, int parts,
+                                                     double *__restrict__ out)
+{
+    __shared__ double lds[SV_BLOCK / SV_WAVE];
+    const double sum = finish_dot(partial, parts, lds);
+    if (threadIdx.x == 0) out[0] = sum;
+}
+
+// DIRECT: q = t.  Otherwise q = t + beta_k q.  Either way partial[g] = sum of
+// q_i * q_i of the new q over workgroup g's range.  GAMMA: gamma_k (and beta_k) are
+// finished here, else they have been (gamma_step).
+template <bool DIRECT, bool GAMMA>
+__global__ __launch_bounds__(SV_BLOCK) void q_step(double *__restrict__ q, const double *__restrict__ t, int64_t len,
+                                                   const double *__restrict__ spart, int sparts, int64_t k,
+                                                   double *__restrict__ hist_gamma, double *__restrict__ scal,
+                                                   double *__restrict__ partial)
+{
+    __shared__ double lds[SV_BLOCK / SV_WAVE];
+    double beta = 0.0;
+    if (GAMMA) beta = finish_gamma(spart, sparts, k, hist_gamma, scal, lds);
     int64_t s, e;
     part_range(len, s, e);
     double acc = 0.0;
     for (int64_t i = s + threadIdx.x; i < e; i += SV_BLOCK) {
-        const double qi = FIRST ? t[i] : t[i] + beta * q[i];
+        const double qi = DIRECT ? t[i] : t[i] + beta * q[i];
         q[i] = qi;
         acc += qi * qi;
     }
@@ -99,20 +157,17 @@ __global__ __launch_bounds__(SV_BLOCK) void q_step(double *__restrict__ q, const
     if (threadIdx.x == 0) partial[blockIdx.x] = sum;
 }
 
-// INIT: r = b - q.  UPDATE: r = r - alpha q.  Either way partial[g] = sum of
-// r_i * r_i of the new r over workgroup g's range.
-template <bool INIT>
-__global__ __launch_bounds__(SV_BLOCK) void r_step(double *__restrict__ r, const double *__restrict__ b,
+// r = b - q, partial[g] = sum of r_i * r_i of the new r over workgroup g's range.
+__global__ __launch_bounds__(SV_BLOCK) void r_init(double *__restrict__ r, const double *__restrict__ b,
                                                    const double *__restrict__ q, int64_t len,
-                                                   const double *__restrict__ scal, double *__restrict__ partial)
+                                                   double *__restrict__ partial)
 {
     __shared__ double lds[SV_BLOCK / SV_WAVE];
-    const double alpha = INIT ? 0.0 : scal[S_ALPHA];
     int64_t s, e;
     part_range(len, s, e);
     double acc = 0.0;
     for (int64_t i = s + threadIdx.x; i < e; i += SV_BLOCK) {
-        const double ri = INIT ? b[i] - q[i] : r[i] - alpha * q[i];
+        const double ri = b[i] - q[i];
         r[i] = ri;
         acc += ri * ri;
     }
@@ -120,48 +175,40 @@ __global__ __launch_bounds__(SV_BLOCK) void r_step(double *__restrict__ r, const
     if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
-// What the scalar kernel does with the finished inner product.  Iteration k
-// (the history index) is scal[S_ITER]: 0 during the start-up, set to 1 by
-// OP_GAMMA0 and advanced by OP_GAMMA, the last scalar step of an iteration.
-enum ScalarOp : int {
-    OP_GAMMA0 = 0,   // gamma = sum, hist_gamma[0] = sum, k = 1
-    OP_ALPHA = 1,    // delta = sum, alpha = gamma / delta (0 when either is 0)
-    OP_GAMMA = 2,    // gamma_new = sum, beta = gamma_new / gamma (0 when gamma is 0), gamma = gamma_new,
-                     // hist_gamma[k] = sum, k = k + 1
-    OP_RHO = 3,      // hist_rho[k] = sum
-    OP_RHO0 = 4      // hist_rho[0] = sum, k = 0
-};
-
-// One workgroup: adds the DOT_PARTS partial sums in a fixed order and applies op.
-__global__ __launch_bounds__(SV_BLOCK) void scalar_step(const double *__restrict__ partial, int op,
-                                                        double *__restrict__ scal, double *__restrict__ hist_gamma,
-                                                        double *__restrict__ hist_rho)
+// alpha = gamma_k / ||q||^2 (0 when either is 0), r = r - alpha q, partial[g] = sum of
+// r_i * r_i of the new r over workgroup g's range.  rank (may be NULL): r is also written to
+// perm in the matrix's own row order, which the next product reads.
+__global__ __launch_bounds__(SV_BLOCK) void r_step(double *__restrict__ r, const double *__restrict__ q, int64_t len,
+                                                   const double *__restrict__ qpart, int qparts, int64_t k,
+                                                   const double *__restrict__ hist_gamma, double *__restrict__ scal,
+                                                   const int32_t *__restrict__ rank, double *__restrict__ perm,
+                                                   double *__restrict__ partial)
 {
     __shared__ double lds[SV_BLOCK / SV_WAVE];
+    const double delta = finish_dot(qpart, qparts, lds);
+    const double gamma = hist_gamma[k];
+    const double alpha = (gamma > 0.0 && delta > 0.0) ? gamma / delta : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) scal[S_ALPHA] = alpha;
+    int64_t s, e;
+    part_range(len, s, e);
     double acc = 0.0;
-    for (int i = threadIdx.x; i < DOT_PARTS; i += SV_BLOCK) acc += partial[i];
-    const double sum = block_sum(acc, lds);
-    if (threadIdx.x != 0) return;
-    const int64_t k = (int64_t)scal[S_ITER];
-    if (op == OP_RHO0) {
-        scal[S_ITER] = 0.0;
-        hist_rho[0] = sum;
-    } else if (op == OP_GAMMA0) {
-        scal[S_GAMMA] = sum;
-        hist_gamma[0] = sum;
-        scal[S_ITER] = 1.0;
-    } else if (op == OP_ALPHA) {
-        const double gamma = scal[S_GAMMA];
-        scal[S_ALPHA] = (gamma > 0.0 && sum > 0.0) ? gamma / sum : 0.0;
-    } else if (op == OP_GAMMA) {
-        const double gamma = scal[S_GAMMA];
-        scal[S_BETA] = gamma > 0.0 ? sum / gamma : 0.0;
-        scal[S_GAMMA] = sum;
-        hist_gamma[k] = sum;
-        scal[S_ITER] = (double)(k + 1);
-    } else {
-        hist_rho[k] = sum;
+    for (int64_t i = s + threadIdx.x; i < e; i += SV_BLOCK) {
+        const double ri = r[i] - alpha * q[i];
+        r[i] = ri;
+        if (rank) perm[rank[i]] = ri;
+        acc += ri * ri;
     }
+    const double t = block_sum(acc, lds);
+    if (threadIdx.x == 0) partial[blockIdx.x] = t;
+}
+
+// ||r||^2 of the iteration, by the first workgroup of a pass over the long vectors.
+__device__ __forceinline__ void finish_rho(const double *__restrict__ rpart, int rparts, double *__restrict__ rho)
+{
+    __shared__ double lds[SV_BLOCK / SV_WAVE];
+    if (blockIdx.x != 0) return;
+    const double sum = finish_dot(rpart, rparts, lds);
+    if (threadIdx.x == 0) *rho = sum;
 }
 
 // p = s + beta p (FIRST: p = s), then x = x + alpha p with the new p: one
@@ -169,9 +216,11 @@ __global__ __launch_bounds__(SV_BLOCK) void scalar_step(const double *__restrict
 template <bool FIRST>
 __global__ __launch_bounds__(SV_BLOCK) void px_step(double *__restrict__ x, double *__restrict__ p,
                                                     const double *__restrict__ s, int64_t len,
-                                                    const double *__restrict__ scal)
+                                                    const double *__restrict__ scal, const double *__restrict__ rpart,
+                                                    int rparts, double *__restrict__ rho)
 {
     const double alpha = scal[S_ALPHA], beta = FIRST ? 0.0 : scal[S_BETA];
+    finish_rho(rpart, rparts, rho);
     const int64_t stride = (int64_t)gridDim.x * SV_BLOCK;
     for (int64_t i = blockIdx.x * (int64_t)SV_BLOCK + threadIdx.x; i < len; i += stride) {
         const double pi = FIRST ? s[i] : s[i] + beta * p[i];
@@ -191,9 +240,11 @@ __global__ __launch_bounds__(SV_BLOCK) void p_step(double *__restrict__ p, const
 }
 
 __global__ __launch_bounds__(SV_BLOCK) void x_step(double *__restrict__ x, const double *__restrict__ p, int64_t len,
-                                                   const double *__restrict__ scal)
+                                                   const double *__restrict__ scal, const double *__restrict__ rpart,
+                                                   int rparts, double *__restrict__ rho)
 {
     const double alpha = scal[S_ALPHA];
+    finish_rho(rpart, rparts, rho);
     const int64_t stride = (int64_t)gridDim.x * SV_BLOCK;
     for (int64_t i = blockIdx.x * (int64_t)SV_BLOCK + threadIdx.x; i < len; i += stride) x[i] = x[i] + alpha * p[i];
 }
@@ -206,49 +257,56 @@ unsigned stream_grid(int64_t len)
 
 }  // namespace
 
-int64_t cgls_dot_parts() { return DOT_PARTS; }
+// Partial sums of the three inner products of an iteration (q, r, s).
+int64_t cgls_partials() { return 3 * DOT_PARTS; }
 
-int launch_cgls_vec(CglsVecOp op, const CglsWork &w, void *stream)
+int launch_cgls_vec(CglsVecOp op, const CglsWork &w, int64_t k, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    auto scalar = [&](ScalarOp sop) {
-        hipLaunchKernelGGL(scalar_step, dim3(1), dim3(SV_BLOCK), 0, st, w.partial, (int)sop, w.scal, w.hist_gamma,
-                           w.hist_rho);
-    };
+    double *qpart = w.partial, *rpart = w.partial + DOT_PARTS, *spart = w.partial + 2 * DOT_PARTS;
+    const int mp = dot_parts(w.m), np = dot_parts(w.n);
+    const dim3 block(SV_BLOCK);
     switch (op) {
     case CglsVecOp::R_INIT:     // r = b - q, rho_0
-        hipLaunchKernelGGL(r_step<true>, dim3(DOT_PARTS), dim3(SV_BLOCK), 0, st, w.r, w.b, w.q, w.m, w.scal, w.partial);
-        scalar(OP_RHO0);
+        hipLaunchKernelGGL(r_init, dim3(mp), block, 0, st, w.r, w.b, w.q, w.m, rpart);
+        hipLaunchKernelGGL(dot_step, dim3(1), block, 0, st, rpart, mp, w.hist_rho);
         break;
-    case CglsVecOp::GAMMA0:     // gamma_0 = ||s||^2
-        hipLaunchKernelGGL(sq_part, dim3(DOT_PARTS), dim3(SV_BLOCK), 0, st, w.s, w.n, w.partial);
-        scalar(OP_GAMMA0);
+    case CglsVecOp::S_NORM:     // the partial sums of ||s||^2
+        hipLaunchKernelGGL(sq_part, dim3(np), block, 0, st, w.s, w.n, spart);
         break;
-    case CglsVecOp::ALPHA_R0:   // q = t, alpha = gamma / ||q||^2, r = r - alpha q, rho_k
-    case CglsVecOp::ALPHA_R:    // q = t + beta q, the same
-        if (op == CglsVecOp::ALPHA_R0)
-            hipLaunchKernelGGL(q_step<true>, dim3(DOT_PARTS), dim3(SV_BLOCK), 0, st, w.q, w.t, w.m, w.scal, w.partial);
-        else
-            hipLaunchKernelGGL(q_step<false>, dim3(DOT_PARTS), dim3(SV_BLOCK), 0, st, w.q, w.t, w.m, w.scal, w.partial);
-        scalar(OP_ALPHA);
-        hipLaunchKernelGGL(r_step<false>, dim3(DOT_PARTS), dim3(SV_BLOCK), 0, st, w.r, w.b, w.q, w.m, w.scal, w.partial);
-        scalar(OP_RHO);
+    case CglsVecOp::GAMMA:      // gamma_k, beta_k
+        hipLaunchKernelGGL(gamma_step, dim3(1), block, 0, st, spart, np, k, w.hist_gamma, w.scal);
         break;
-    case CglsVecOp::PX0:        // p = s, x = x + alpha p
-        hipLaunchKernelGGL(px_step<true>, dim3(stream_grid(w.n)), dim3(SV_BLOCK), 0, st, w.x, w.p, w.s, w.n, w.scal);
+    case CglsVecOp::Q_FIRST:    // gamma_k, q = t
+        hipLaunchKernelGGL((q_step<true, true>), dim3(mp), block, 0, st, w.q, w.t, w.m, spart, np, k, w.hist_gamma,
+                           w.scal, qpart);
         break;
-    case CglsVecOp::PX:         // p = s + beta p, x = x + alpha p
-        hipLaunchKernelGGL(px_step<false>, dim3(stream_grid(w.n)), dim3(SV_BLOCK), 0, st, w.x, w.p, w.s, w.n, w.scal);
+    case CglsVecOp::Q:          // gamma_k, beta_k, q = t + beta q
+        hipLaunchKernelGGL((q_step<false, true>), dim3(mp), block, 0, st, w.q, w.t, w.m, spart, np, k, w.hist_gamma,
+                           w.scal, qpart);
+        break;
+    case CglsVecOp::Q_DIRECT:   // q = t
+        hipLaunchKernelGGL((q_step<true, false>), dim3(mp), block, 0, st, w.q, w.t, w.m, spart, np, k, w.hist_gamma,
+                           w.scal, qpart);
+        break;
+    case CglsVecOp::R:          // alpha, r = r - alpha q
+        hipLaunchKernelGGL(r_step, dim3(mp), block, 0, st, w.r, w.q, w.m, qpart, mp, k, w.hist_gamma, w.scal, w.rank,
+                           w.perm, rpart);
+        break;
+    case CglsVecOp::PX_FIRST:   // rho_{k+1}, p = s, x = x + alpha p
+        hipLaunchKernelGGL(px_step<true>, dim3(stream_grid(w.n)), block, 0, st, w.x, w.p, w.s, w.n, w.scal, rpart, mp,
+                           w.hist_rho + k + 1);
+        break;
+    case CglsVecOp::PX:         // rho_{k+1}, p = s + beta p, x = x + alpha p
+        hipLaunchKernelGGL(px_step<false>, dim3(stream_grid(w.n)), block, 0, st, w.x, w.p, w.s, w.n, w.scal, rpart, mp,
+                           w.hist_rho + k + 1);
         break;
     case CglsVecOp::P:          // p = s + beta p
-        hipLaunchKernelGGL(p_step, dim3(stream_grid(w.n)), dim3(SV_BLOCK), 0, st, w.p, w.s, w.n, w.scal);
+        hipLaunchKernelGGL(p_step, dim3(stream_grid(w.n)), block, 0, st, w.p, w.s, w.n, w.scal);
         break;
-    case CglsVecOp::X:          // x = x + alpha p
-        hipLaunchKernelGGL(x_step, dim3(stream_grid(w.n)), dim3(SV_BLOCK), 0, st, w.x, w.p, w.n, w.scal);
-        break;
-    case CglsVecOp::GAMMA:      // gamma_k = ||s||^2, beta
-        hipLaunchKernelGGL(sq_part, dim3(DOT_PARTS), dim3(SV_BLOCK), 0, st, w.s, w.n, w.partial);
-        scalar(OP_GAMMA);
+    case CglsVecOp::X:          // rho_{k+1}, x = x + alpha p
+        hipLaunchKernelGGL(x_step, dim3(stream_grid(w.n)), block, 0, st, w.x, w.p, w.n, w.scal, rpart, mp,
+                           w.hist_rho + k + 1);
         break;
     }
     return (int)hipGetLastError();
