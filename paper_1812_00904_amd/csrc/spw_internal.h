@@ -204,12 +204,13 @@ int launch_coldot_batch(const spw_matrix_s &A, const ColDot &C, const int32_t *i
                         const void *V, int64_t ldv, void *U, int64_t ldu, void *stream, bool out_f64 = false);
 // The run kernel of those column dots (spw_run.hip), without the columns that have no
 // nonzeros and without the zone sums; coldot_run_takes says whether it is the better one for
-// a call.  It is taken past 8 columns: for binary64 vectors over the matrix's own
-// storage (20,000 x 5e6, 5e7 nonzeros, us, tile and run: k = 9 828 and 580, 16 773 and 557, 64
-// 2,178 and 1,746; at k = 8 the tile's sixteen short streams win, 500 and 520), and over the
-// transpose for both types where the caller's rows are whole 16-byte groups.  Binary32
-// over the matrix's own storage stays with the tile (k = 16 452 and 498, 32 650 and 932): a
-// gather is half as wide there, and the starts of columns weigh more.
+// a call.  It is taken past 8 columns, but for the smallest matrices and the shortest columns:
+// for binary64 vectors over the matrix's own storage (20,000 x 5e6, 5e7 nonzeros, us, tile
+// and run: k = 9 828 and 580, 16 773 and 557, 64 2,178 and 1,746; at k = 8 the tile's sixteen
+// short streams win, 500 and 520), and over the transpose for both types where the caller's
+// rows are whole 16-byte groups.  Binary32 over the matrix's own storage stays with the tile
+// (k = 16 452 and 498, 32 650 and 932): a gather is half as wide there, and the starts of
+// columns weigh more.
 bool coldot_run_takes(const spw_matrix_s &A, const ColDot &C, spw_dtype vdt, int32_t k, int64_t ldv);
 int launch_coldot_run(const spw_matrix_s &A, const ColDot &C, const int32_t *inv, spw_dtype vdt, int32_t k, const void *V,
                       int64_t ldv, void *U, int64_t ldu, void *stream, bool out_f64);

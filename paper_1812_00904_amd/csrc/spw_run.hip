@@ -457,11 +457,28 @@ int run_transpose(const spw_matrix_s &A, const ColDot &C, int k, const VecT *V, 
 
 bool coldot_run_takes(const spw_matrix_s &A, const ColDot &C, spw_dtype vdt, int32_t k, int64_t ldv)
 {
-    if (&C == &A.cd) return vdt == SPW_F64 && k > 8;
+    if (k <= 8) return false;
+    if (&C == &A.cd) {
+        if (vdt != SPW_F64) return false;
+        // A wave walks its chunk's column starts one after the other, where the tile's lanes take
+        // a few positions each: short columns need a wide block to pay for their starts, and a
+        // matrix of few chunks a wave has nothing to hide them behind.  Tile and run (us, 5,000
+        // rows, binary64), k = 16: 1e6 nonzeros 10 a column 29 and 33, 30 a column 26 and 27; 4e6 10
+        // a column 61 and 67, 30 a column 54 and 52; 1.6e7 3, 6 and 10 a column 357 and 383, 274 and
+        // 260, 233 and 210.  k = 32: 1e6 3 and 10 a column 46 and 55, 39 and 38; 8e6 1.5 a column
+        // 455 and 445.  k = 64: 5e5 3 and 6 a column 58 and 62, 51 and 50; 2e6 1.5 a column 243 and 194.
+        const int64_t filled = C.cols - C.n_empty;
+        const int64_t least = k <= 16 ? (C.nnz < (int64_t)1 << 23 ? 30 : 8)
+                              : k <= 32 ? (C.nnz < (int64_t)1 << 22 ? 8 : 0)
+                                        : (C.nnz < (int64_t)1 << 21 ? 6 : 0);
+        return C.nnz >= least * filled;
+    }
     // the transpose gathers the caller's rows: whole 16-byte groups of columns; 2-byte rows
-    // are kept as 32-bit byte offsets
+    // are kept as 32-bit byte offsets.  Its columns are long, only the size counts (k = 16,
+    // binary32, tile and run: 5e5 nonzeros 19 and 23 to 26, 1e6 20 to 26 and 23 to 27, 2e6 58 and 42).
     const int64_t es = vdt == SPW_F64 ? 8 : 4;
-    return k > 8 && (k * es) % 16 == 0 && (C.idx_kind == IdxKind::I32 || ldv * es < 65536);
+    if (k <= 16 && C.nnz < (int64_t)5 << 18) return false;
+    return (k * es) % 16 == 0 && (C.idx_kind == IdxKind::I32 || ldv * es < 65536);
 }
 
 int launch_coldot_run(const spw_matrix_s &A, const ColDot &C, const int32_t *inv, spw_dtype vdt, int32_t k, const void *V,

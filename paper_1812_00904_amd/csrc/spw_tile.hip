@@ -501,9 +501,8 @@ int launch_tile_items(const spw_matrix_s &A, const ColDot &C, int k, const VecT 
 #define SPW_TILE(LL, WW) \
     if (L == LL && CW == WW) return go(cdot_tile<IdxT, ValT, VecT, LL, ITEMS, WW, OutT>);
     SPW_TILE(2, 1) SPW_TILE(4, 1) SPW_TILE(8, 1) SPW_TILE(16, 1) SPW_TILE(32, 1) SPW_TILE(64, 1)
-    SPW_TILE(1, 2) SPW_TILE(2, 2) SPW_TILE(4, 2)
+    SPW_TILE(1, 2) SPW_TILE(2, 2) SPW_TILE(4, 2) SPW_TILE(8, 2) SPW_TILE(16, 2) SPW_TILE(32, 2)
     if constexpr (sizeof(VecT) == 4) {
-        SPW_TILE(8, 2) SPW_TILE(16, 2) SPW_TILE(32, 2)
         SPW_TILE(1, 4) SPW_TILE(2, 4) SPW_TILE(4, 4) SPW_TILE(8, 4) SPW_TILE(16, 4)
     }
 #undef SPW_TILE

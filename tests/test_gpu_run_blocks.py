@@ -91,3 +91,43 @@ def test_entries_that_are_not_finite(spw):
         holds = np.isin(np.arange(A.n), col[A.idx == {3: rows[0], 5: rows[1]}.get(c, -1)])
         assert np.array_equal(~np.isfinite(U[:, c]), holds), c
     M.close()
+
+
+@pytest.mark.parametrize("k", [9, 10, 15, 16, 17, 31, 32, 33, 64])
+@pytest.mark.parametrize("rest", [0, 7, 16, 255, 1023])
+def test_long_columns(spw, k, rest):
+    # 40 nonzeros a column: every width takes the run kernel over the matrix's own storage
+    rng = np.random.Generator(np.random.PCG64(k))
+    lengths = rng.integers(30, 51, 400)
+    lengths[rng.random(400) < 0.1] = 0
+    lengths[-1] += (rest - int(lengths.sum())) % 1024
+    A = synth.from_lengths(6_000, lengths, rest + 1)
+    assert A.ptr[-1] % 1024 == rest
+    for chunk in (512, 1024):
+        M = spw.SpwMatrix(spw.SPW_CSC, A.m, A.n, A.ptr, A.idx, A.val, transpose=1, chunk_nnz=chunk)
+        print("run long k=%d rest=%d chunk=%d" % (k, rest, chunk), flush=True)
+        compare(spw, M, A, k, torch.float64, 1e-13, (k, rest, chunk))
+        M.close()
+
+
+@pytest.mark.parametrize("n", [100_000, 300_000])
+def test_transpose_narrow_blocks(spw, n):
+    # enough nonzeros for the narrow blocks of the kept transpose, with and without several row blocks
+    A = synth.random_csc(700, n, 1_400_000 // n, seed=n, row_alpha=0.5)
+    M = spw.SpwMatrix(spw.SPW_CSC, A.m, A.n, A.ptr, A.idx, A.val, transpose=1)
+    for k in (12, 16):
+        for dtype, tol in ((torch.float64, 1e-13), (torch.float32, 1e-5)):
+            print("run narrow n=%d k=%d %s" % (n, k, dtype), flush=True)
+            compare(spw, M, A, k, dtype, tol, (n, k, dtype))
+    M.close()
+
+
+@pytest.mark.parametrize("mean", [3, 5, 6, 7, 8, 9, 29, 31])
+def test_either_side_of_the_rule(spw, mean):
+    # both kernels give the same result within the bound wherever the line between them lies
+    A = synth.from_lengths(1_000, np.full(900, mean), mean)
+    M = spw.SpwMatrix(spw.SPW_CSC, A.m, A.n, A.ptr, A.idx, A.val, transpose=1)
+    for k in (16, 32, 64):
+        print("run rule mean=%d k=%d" % (mean, k), flush=True)
+        compare(spw, M, A, k, torch.float64, 1e-13, (mean, k))
+    M.close()
