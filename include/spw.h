@@ -78,8 +78,9 @@ typedef struct spw_matrix_s *spw_matrix;
  *                   (BF16 directly from binary64, no double rounding); a value
  *                   that overflows the storage type is SPW_ERR_BAD_MATRIX.
  *                   Products promote stored values exactly to binary64.
- *   chunk_nnz     : nonzeros per column-dot chunk: 0 = automatic (1024, or the
- *                   tuner's choice with autotune), 512 or 1024; any other value is
+ *   chunk_nnz     : nonzeros per column-dot chunk: 0 = automatic (1024; 512 for small
+ *                   matrices and for short columns; the tuner's choice with
+ *                   autotune), 512 or 1024; any other value is
  *                   SPW_ERR_UNSUPPORTED.  Smaller chunks give small matrices more
  *                   workers (Section II's P grows as the chunk shrinks).
  *   relabel       : -1 automatic, 0 off, 1 on.  On: rows are renumbered inside

@@ -252,7 +252,7 @@ void free_one(spw_matrix_s &A, void *p)
 // Frees the device arrays of a column-dot storage and resets it.
 void free_coldot(spw_matrix_s &A, ColDot &C)
 {
-    for (void *p : {C.d_idx, C.d_val, (void *)C.d_empty, (void *)C.d_zone_col, (void *)C.d_zone_first,
+    for (void *p : {C.d_idx, C.d_val, (void *)C.d_empty, (void *)C.d_empty_of[1], (void *)C.d_zone_col, (void *)C.d_zone_first,
                     (void *)C.d_zone_last, (void *)C.d_wchunks, (void *)C.d_heads, (void *)C.d_cinfo,
                     (void *)C.d_segcol})
         free_one(A, p);
@@ -538,6 +538,32 @@ spw_status build_coldot(spw_matrix_s &A, ColDot &C, int64_t rows, int64_t cols, 
             ci[2] = (int32_t)nseg;
             ci[3] = flags;
         }
+        segcol.push_back((int32_t)cols);          // after the last chunk's segments
+        // The empty columns that a staged chunk does not write (vtm_reduce_staged): those before
+        // the first column, in long gaps, and after segments of chunks that are not staged
+        // or have no empty column inside.
+        {
+            const int64_t cap = vtm_stage_cap(WCH);
+            int64_t filled = 0;
+            for (int64_t j = 0; j < cols; ++j) filled += ptr[j] < ptr[j + 1];
+            C.gap_max = cols - filled <= GAP_SHARE * filled ? GAP_MAX : 0;
+            std::vector<int32_t> far;
+            auto add = [&](int64_t a, int64_t b) {
+                for (int64_t j = a; j < b; ++j) far.push_back((int32_t)j);
+            };
+            if (nch > 0) add(0, segcol[0]);
+            for (int64_t c = 0; c < nch; ++c) {
+                const int32_t *ci = &cinfo[(size_t)(4 * c)];
+                const bool staged = (c + 1) * WCH <= nnz && ci[2] <= cap && !(ci[3] & 4);
+                for (int64_t t = 0; t < ci[2]; ++t) {
+                    const int64_t j = segcol[(size_t)(ci[1] + t)], nx = segcol[(size_t)(ci[1] + t + 1)];
+                    if (!staged || nx - j - 1 > C.gap_max) add(j + 1, nx);
+                }
+            }
+            C.n_empty_of[1] = (int64_t)far.size();
+            if ((st = dev_alloc(A, &C.d_empty_of[1], std::max<int64_t>(C.n_empty_of[1], 1), "empty columns"))) return st;
+            if ((st = h2d(C.d_empty_of[1], far.data(), far.size() * 4, "empty columns"))) return st;
+        }
         if (segcol.size() >= ((size_t)1 << 31)) return fail(SPW_ERR_UNSUPPORTED, "segment table exceeds 2^31 entries");
         if ((st = dev_alloc(A, &C.d_heads, (int64_t)heads.size(), "column-start bits"))) return st;
         if ((st = h2d(C.d_heads, heads.data(), heads.size() * 2, "column-start bits"))) return st;
@@ -554,6 +580,8 @@ spw_status build_coldot(spw_matrix_s &A, ColDot &C, int64_t rows, int64_t cols, 
         C.n_empty = (int64_t)empty.size();
         if ((st = dev_alloc(A, &C.d_empty, std::max<int64_t>(C.n_empty, 1), "empty columns"))) return st;
         if ((st = h2d(C.d_empty, empty.data(), empty.size() * 4, "empty columns"))) return st;
+        C.d_empty_of[0] = C.d_empty;
+        C.n_empty_of[0] = C.n_empty;
     }
     if ((st = dev_alloc(A, &C.d_zone_col, std::max<int64_t>(C.n_zones, 1), "zone table"))) return st;
     if ((st = dev_alloc(A, &C.d_zone_first, std::max<int64_t>(C.n_zones, 1), "zone table"))) return st;
@@ -634,6 +662,29 @@ spw_status plan_workers(spw_matrix_s &A, ColDot &C, const int64_t *ptr, spw_part
     if ((st = dev_alloc(A, &C.d_wchunks, P + 1, "worker chunk runs"))) return st;
     if ((st = h2d(C.d_wchunks, first.data(), first.size() * 4, "worker chunk runs"))) return st;
     return SPW_OK;
+}
+
+// The column-dot chunk where the caller leaves it open.  1,024 nonzeros, but 512 where
+// - columns are short: a chunk of 512 stages every segment it can hold and one of 1,024 at
+//   most 256 (binary64, 8e6 nonzeros, us at 1,024 / 512: 0.7 a column with most empty 162 / 66,
+//   1 71 / 35, 2 48 / 34, 3 39 / 31);
+// - the whole matrix is less than one chunk of 1,024 for each of the waves that the chip holds,
+//   whatever its columns (1e6 nonzeros 16 a column: one vector 16 / 15, three 27 / 22, sixteen 35 / 27;
+//   2e6: 17 / 18, 29 / 28, 39 / 38 and with binary32 vectors 16 / 16, 27 / 27, 32 / 31);
+// - binary64 values leave a wave fewer than five chunks, so that the last round is uneven,
+//   and columns are not long (9e6, 4 a column: 37 / 32, three 89 / 74; 8 a column 33 / 31, 71 / 70,
+//   16 a column three 67 / 69, and at 5e7, 10 a column, 124 / 135).  With 4- or 2-byte values or
+//   vectors several vectors at once pay for the shorter chunks there (9e6, 8 a column, three
+//   vectors 60 / 68).
+int64_t auto_chunk(int64_t cols, const int64_t *ptr, spw_dtype storage)
+{
+    const int64_t nnz = ptr[cols];
+    int64_t filled = 0;
+    for (int64_t j = 0; j < cols; ++j) filled += ptr[j] < ptr[j + 1];
+    const int64_t waves = (int64_t)1024 * 2048;             // one chunk of 1,024 for each of 2,048 waves
+    const bool tiny = 4 * nnz < 3 * waves;
+    const bool uneven = storage == SPW_F64 && nnz < 5 * waves && nnz < 8 * filled;
+    return tiny || uneven || nnz < 3 * filled ? 512 : vtm_chunk_default();
 }
 
 // The number of row panels of the scatter product.  P panels read x P times
@@ -1317,7 +1368,7 @@ static spw_status spw_create_impl(spw_matrix *out, spw_format fmt, int64_t m, in
     if (opts.partition != SPW_PART_NONZERO && opts.partition != SPW_PART_COLUMN &&
         opts.partition != SPW_PART_MERGE)
         return fail(SPW_ERR_INVALID_ARG, "spw_create: bad partition");
-    const int64_t chunk = opts.chunk_nnz > 0 ? opts.chunk_nnz : vtm_chunk_default();
+    int64_t chunk = opts.chunk_nnz > 0 ? opts.chunk_nnz : vtm_chunk_default();
     if (opts.chunk_nnz < 0 || !vtm_chunk_supported(chunk))
         return fail(SPW_ERR_UNSUPPORTED, "spw_create: chunk_nnz must be 0, 512 or 1024");
     if (opts.wg_size != 0 && opts.wg_size != 256 && opts.wg_size != 512 && opts.wg_size != 1024)
@@ -1422,6 +1473,7 @@ static spw_status spw_create_impl(spw_matrix *out, spw_format fmt, int64_t m, in
             for (int64_t p = a; p < b; ++p) rowi[(size_t)p] = rl ? rank[(size_t)idx[p]] : idx[p];
         });
     }
+    if (opts.chunk_nnz == 0) chunk = auto_chunk(cols, ptr, A->value_storage);
     A->vtm_block[0] = A->vtm_block[1] = opts.wg_size;
     A->autotune = opts.autotune;
     A->fingerprint = matrix_fingerprint(fmt, opts.value_storage, m, n, nnz, ptr, idx);

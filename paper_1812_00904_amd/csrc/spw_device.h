@@ -344,31 +344,48 @@ __device__ __forceinline__ void buf_store_nt(double x, __amdgpu_buffer_rsrc_t r,
 }
 
 // Segments of one chunk a wave stages in LDS before writing them out; chunks
-// with more segments take the general path.
-constexpr int STAGE_CAP = 256;
-constexpr int STAGE_STRIDE = STAGE_CAP + 64;     // plus one spare slot per lane
+// with more segments take the general path.  Chunks of 512 stage all they can hold
+// (that size is taken for short columns); chunks of 1,024 stage 256 for binary64
+// vectors, and none for binary32 ones, whose LDS is worth more as hot rows of v.
+template <int ITEMS, typename VecT> constexpr int stage_cap()
+{
+    return ITEMS == 8 ? 512 : sizeof(VecT) == 8 ? 256 : 0;
+}
+// ... plus one spare slot per lane
+template <int ITEMS, typename VecT> constexpr int stage_stride()
+{
+    return stage_cap<ITEMS, VecT>() ? stage_cap<ITEMS, VecT>() + 64 : 0;
+}
 
-// Reduces one full chunk (all 64*ITEMS positions are nonzeros) whose columns
-// have no empty column between them, so segment q is column jlo + q, with at
-// most STAGE_CAP segments.  Same additions in the same order as
+// Reduces one full chunk (all 64*ITEMS positions are nonzeros) with at most stage_cap
+// segments.  Same additions in the same order as
 // vtm_reduce_chunk, with the per-position branches replaced by selects.  Every
 // segment's sum goes to this wave's LDS stage at its segment index (writes
 // that carry nothing go to the lane's spare slot), then the wave copies the
-// chunk's segments out: a contiguous run of columns in one or two coalesced
-// buffer stores, and the two chunk-cut segments to their carry slots.  LDS
+// chunk's segments out, the two chunk-cut segments to their carry slots.  LDS
 // instructions of one wave execute in order, so the copy sees every write.
+//   no empty column inside: segment q is column jlo + q, so the copy is a
+//     contiguous run of columns in coalesced buffer stores
+//   empty columns inside: segment q is column segcol[seg0 + q], and the lane that
+//     writes it also writes the zeros of the empty columns up to the next segment's
+//     (gaps of up to gap_max; the others are in the caller's list).  The general path
+//     before took its store per position under a branch, and the empty columns a kernel
+//     of scattered zeros: 8e6 nonzeros in 1.1e7 columns 162 -> 66 us.
 // The caller guarantees nseg * ldu * sizeof(VecT) < 2^31.
 template <int ITEMS, typename VecT>
-__device__ __forceinline__ void vtm_reduce_dense(const double *prod, uint32_t mask, int4 ci, int64_t c, int lane,
-                                                 VecT *__restrict__ u, int64_t ldu, double *__restrict__ carry,
-                                                 int kk, int col, __attribute__((address_space(3))) double *stage)
+__device__ __forceinline__ void vtm_reduce_staged(const double *prod, uint32_t mask, int4 ci,
+                                                  const int32_t *__restrict__ segcol, int64_t c, int lane,
+                                                  VecT *__restrict__ u, int64_t ldu, double *__restrict__ carry,
+                                                  int kk, int col, __attribute__((address_space(3))) double *stage,
+                                                  int gap_max)
 {
+    constexpr int CAP = stage_cap<ITEMS, VecT>();
     const uint32_t after_s = lane == 0 ? (mask & ~1u) : mask;
     const int cnt = __popc(after_s);
     const int incl = wave_prefix_sum(cnt);
     const int k0 = incl - cnt + (lane > 0 ? (int)(mask & 1u) : 0);   // segment of the lane's first position
     const uint32_t hb = mask & ((1u << ITEMS) - 1u) & ~1u;             // column starts after the first position
-    const int spare = STAGE_CAP + lane;
+    const int spare = CAP + lane;
     double run = 0.0, head_sum = 0.0;
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
@@ -391,25 +408,38 @@ __device__ __forceinline__ void vtm_reduce_dense(const double *prod, uint32_t ma
     const double tot = (lane > 0 && prev_k == k0) ? prev_s + head_sum : head_sum;
     stage[hb != 0u ? k0 : spare] = tot;
     stage[(lane == WAVE - 1 || next_hk != k) ? k : spare] = o.s;
-    // copy out: segment t is column jlo + t, except a first segment that began
+    // copy out, except a first segment that began
     // in an earlier chunk and a last one that continues into the next
     const int nseg = ci.z, flags = ci.w;
     const bool first_carry = !(flags & CHUNK_START_HEAD), last_carry = (flags & CHUNK_END_CONT) != 0;
-    const __amdgpu_buffer_rsrc_t ub =
-        buf_view(u + (int64_t)ci.x * ldu, (uint32_t)((int64_t)nseg * ldu * (int64_t)sizeof(VecT)));
-    const uint32_t step_bytes = (uint32_t)(ldu * (int64_t)sizeof(VecT));
-    if (sizeof(VecT) == 8 && ldu == 1) {
-        // contiguous binary64 outputs: 64 lanes write 512 consecutive bytes
-        for (int t = lane; t < nseg; t += WAVE) {
-            const double val = stage[t];
-            const bool to_carry = (t == 0 && first_carry) || (t == nseg - 1 && last_carry);
-            buf_store_nt(val, ub, to_carry ? BUF_DROP : (uint32_t)t * 8u);
+    if (flags & CHUNK_DENSE) {
+        const __amdgpu_buffer_rsrc_t ub =
+            buf_view(u + (int64_t)ci.x * ldu, (uint32_t)((int64_t)nseg * ldu * (int64_t)sizeof(VecT)));
+        const uint32_t step_bytes = (uint32_t)(ldu * (int64_t)sizeof(VecT));
+        if (sizeof(VecT) == 8 && ldu == 1) {
+            // contiguous binary64 outputs: 64 lanes write 512 consecutive bytes
+            for (int t = lane; t < nseg; t += WAVE) {
+                const double val = stage[t];
+                const bool to_carry = (t == 0 && first_carry) || (t == nseg - 1 && last_carry);
+                buf_store_nt(val, ub, to_carry ? BUF_DROP : (uint32_t)t * 8u);
+            }
+        } else {
+            for (int t = lane; t < nseg; t += WAVE) {
+                const double val = stage[t];
+                const bool to_carry = (t == 0 && first_carry) || (t == nseg - 1 && last_carry);
+                buf_store((VecT)val, ub, to_carry ? BUF_DROP : (uint32_t)t * step_bytes);
+            }
         }
     } else {
+        // the table's next entry is the next chunk's first column after the last segment
+        const int32_t *sc = segcol + ci.y;
         for (int t = lane; t < nseg; t += WAVE) {
-            const double val = stage[t];
+            const int j = sc[t], gap = sc[t + 1] - j - 1;
             const bool to_carry = (t == 0 && first_carry) || (t == nseg - 1 && last_carry);
-            buf_store((VecT)val, ub, to_carry ? BUF_DROP : (uint32_t)t * step_bytes);
+            VecT *p = u + (int64_t)j * ldu;
+            if (!to_carry) *p = (VecT)stage[t];
+            if (gap <= gap_max)
+                for (int g = 1; g <= gap; ++g) p[g * ldu] = (VecT)0;
         }
     }
     if (lane == 0) {
@@ -418,8 +448,8 @@ __device__ __forceinline__ void vtm_reduce_dense(const double *prod, uint32_t ma
     }
 }
 
-// As vtm_reduce_dense, without the LDS stage (binary32 outputs, whose LDS is
-// worth more as hot rows of v): the same additions in the same order, with a
+// One full chunk without an empty column inside, without the LDS stage (binary32 outputs of
+// chunks of 1,024): the same additions in the same order, with a
 // column wholly inside a lane written by a buffer store of its own.  Same
 // additions in the same order as vtm_reduce_chunk, with the per-position
 // branches replaced by selects: a column wholly inside a lane is written by a

@@ -65,8 +65,12 @@ struct ColDot {
     void *d_idx = nullptr;
     void *d_val = nullptr;
     ZonePlan zp;
-    int32_t *d_empty = nullptr;
+    int32_t *d_empty = nullptr;         // the columns without nonzeros
     int64_t n_empty = 0;
+    // by what the column dots write themselves: [0] nothing (all of them), [1] the gaps of staged chunks
+    int32_t *d_empty_of[2] = {nullptr, nullptr};
+    int64_t n_empty_of[2] = {0, 0};
+    int gap_max = 0;                    // gaps up to this are written by the staged chunks
     int32_t *d_zone_col = nullptr, *d_zone_first = nullptr, *d_zone_last = nullptr;
     int64_t n_zones = 0;
     int32_t *d_wchunks = nullptr;       // column partitioning: first chunk of each worker (n_workers+1)
@@ -232,7 +236,14 @@ int64_t vtm_chunk_default();
 bool vtm_chunk_supported(int64_t chunk);
 // Waves the single-vector column-dot kernel runs for nchunks chunks on device.
 int64_t vtm_workers(int device, int64_t nchunks);
-int64_t vtm_hot_rows_limit(spw_dtype vdt);
+// Segments of a chunk that its wave stages (binary64 vectors; binary32 ones only with chunks of 512).
+int64_t vtm_stage_cap(int64_t chunk);
+// The longest gap of empty columns that a staged chunk fills with zeros itself, and the
+// most empty columns per other one for which chunks do so: past that the lanes' loops over
+// the gaps cost more than a kernel over a list (8e6 nonzeros, seven empty columns in ten:
+// 175 us with the list, 121 without; 474,543 in 3.6e6 columns: 26 and 37).
+constexpr int GAP_MAX = 32;
+constexpr int64_t GAP_SHARE = 3;
 int device_cu_count(int device);
 
 // CGLS vector steps (spw_solve.hip).  x and p have n entries, b, r and q

@@ -53,16 +53,15 @@ __global__ __launch_bounds__(BLOCK) void vtm_wave(
     const IdxT *__restrict__ idx, const ValT *__restrict__ val, const uint16_t *__restrict__ heads,
     const int4 *__restrict__ cinfo, const int32_t *__restrict__ segcol, int64_t nnz, int64_t nchunks,
     const int32_t *__restrict__ wchunks, const VecT *__restrict__ v, int k, int vhot, ColOut<VecT> out,
-    double *__restrict__ carry)
+    double *__restrict__ carry, int gap_max)
 {
     if (!MULTI) k = 1;
     const int64_t ldv = k;
     constexpr int NW = BLOCK / WAVE;
     constexpr int WCH = WAVE * ITEMS;
     extern __shared__ double lds[];
-    // LDS: each wave's segment stage (STAGE_STRIDE doubles; binary64 vectors
-    // only), then the hot rows of v
-    constexpr int STAGED = sizeof(VecT) == 8 ? STAGE_STRIDE : 0;
+    // LDS: each wave's segment stage, then the hot rows of v
+    constexpr int STAGED = stage_stride<ITEMS, VecT>();
     VecT *vh = reinterpret_cast<VecT *>(lds + NW * STAGED);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     __attribute__((address_space(3))) double *stage =
@@ -147,16 +146,19 @@ __global__ __launch_bounds__(BLOCK) void vtm_wave(
                 prod[i] = C.a.get(i) * (double)(C.r.get(i) < vhot ? lv[i] : gv[i]);
             VecT *uc = MULTI ? out.u[col] : out.u[0];
             const int64_t ldu = MULTI ? out.ld[col] : 1;
-            // full chunk, no empty column inside, segments fit the stage, output
-            // view within 2^31 bytes
-            const bool dense_full = e - s == WCH && (ci.w & CHUNK_DENSE) &&
+            // full chunk, output view within 2^31 bytes, and its segments fit the stage (none
+            // empty inside, without one)
+            if constexpr (STAGED > 0) {
+                const bool staged = e - s == WCH && ci.z <= stage_cap<ITEMS, VecT>() &&
                                     ldu <= (int64_t)(1 << 28) / (WCH * (int64_t)sizeof(VecT));
-            if constexpr (sizeof(VecT) == 8) {
-                if (dense_full && ci.z <= STAGE_CAP)
-                    vtm_reduce_dense<ITEMS, VecT>(prod, C.mask, ci, cc, lane, uc, ldu, carry, k, col, stage);
+                if (staged)
+                    vtm_reduce_staged<ITEMS, VecT>(prod, C.mask, ci, segcol, cc, lane, uc, ldu, carry, k, col, stage,
+                                                   gap_max);
                 else
                     vtm_reduce_chunk<ITEMS, VecT>(prod, C.mask, s, e, ci, segcol, cc, lane, uc, ldu, carry, k, col);
             } else {
+                const bool dense_full = e - s == WCH && (ci.w & CHUNK_DENSE) &&
+                                        ldu <= (int64_t)(1 << 28) / (WCH * (int64_t)sizeof(VecT));
                 if (dense_full)
                     vtm_reduce_dense_direct<ITEMS, VecT>(prod, C.mask, ci, segcol, cc, lane, uc, ldu, carry, k, col);
                 else
@@ -744,17 +746,18 @@ __global__ void gather_tab(const int32_t *__restrict__ inv, int64_t rows, int k,
 // smaller workgroups run two to a CU (8 waves, as one 512-thread workgroup),
 // each with half the LDS.
 int vtm_wgs_per_cu(int block) { return block >= VTM_BLOCK ? VTM_WG_PER_CU : VTM_BLOCK / block; }
-// LDS of one column-dot workgroup outside the hot rows: the waves' segment
-// stages, for binary64 vectors.
-int64_t vtm_stage_bytes(size_t elem_bytes, int block = VTM_BLOCK)
+// LDS of one column-dot workgroup outside the hot rows: the waves' segment stages.
+template <int ITEMS, typename VecT>
+int64_t vtm_stage_bytes(int block)
 {
-    return elem_bytes == 8 ? (int64_t)(block / WAVE) * STAGE_STRIDE * (int64_t)sizeof(double) : 0;
+    return (int64_t)(block / WAVE) * stage_stride<ITEMS, VecT>() * (int64_t)sizeof(double);
 }
-// Hot rows of v that fit beside the stages, for k columns of elem_bytes each.
-int64_t hot_rows_limit(size_t elem_bytes, int64_t k, int block = VTM_BLOCK)
+// Hot rows of v that fit beside the stages, for k columns.
+template <int ITEMS, typename VecT>
+int64_t hot_rows_limit(int64_t k, int block)
 {
-    return (LDS_BYTES / vtm_wgs_per_cu(block) - 256 - vtm_stage_bytes(elem_bytes, block)) /
-           ((int64_t)elem_bytes * k);
+    return (LDS_BYTES / vtm_wgs_per_cu(block) - 256 - vtm_stage_bytes<ITEMS, VecT>(block)) /
+           ((int64_t)sizeof(VecT) * k);
 }
 
 // Whether the single-vector column dots fit 16 waves per CU (128 registers
@@ -790,8 +793,8 @@ int launch_vtm_wave_items(const spw_matrix_s &A, const VecT *vin, int k, const C
     // column partitioning: one wave per worker of the plan (single-vector calls)
     const int32_t *wch = (!MULTI && C.d_wchunks) ? C.d_wchunks : nullptr;
     const int block = MULTI ? VTM_BLOCK : vtm_block_for<ITEMS, ValT, VecT>(A, wch != nullptr);
-    const int vhot = (int)std::min<int64_t>(A.rows, hot_rows_limit(sizeof(VecT), k, block));
-    const size_t lds = (size_t)vtm_stage_bytes(sizeof(VecT), block) + (size_t)vhot * k * sizeof(VecT);
+    const int vhot = (int)std::min<int64_t>(A.rows, hot_rows_limit<ITEMS, VecT>(k, block));
+    const size_t lds = (size_t)vtm_stage_bytes<ITEMS, VecT>(block) + (size_t)vhot * k * sizeof(VecT);
     auto run = [&](auto kernel) -> int {
         const int nw = block / WAVE;
         const int64_t wgs_needed = (C.zp.n_chunks + nw - 1) / nw;
@@ -800,7 +803,7 @@ int launch_vtm_wave_items(const spw_matrix_s &A, const VecT *vin, int k, const C
                 : (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * vtm_wgs_per_cu(block), wgs_needed));
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, stream, (const IdxT *)C.d_idx, (const ValT *)C.d_val,
                            C.d_heads, (const int4 *)C.d_cinfo, C.d_segcol, C.nnz, C.zp.n_chunks, wch, vin, k, vhot,
-                           out, A.scratch.carry);
+                           out, A.scratch.carry, C.gap_max);
         return (int)hipGetLastError();
     };
     if constexpr (!MULTI && vtm_fits_1024<ITEMS, ValT, VecT>()) {
@@ -831,16 +834,35 @@ int launch_vtm_wave(const spw_matrix_s &A, const VecT *vin, int k, const ColOut<
     return (int)hipErrorNotSupported;
 }
 
+// Which list of empty columns the column-dot kernel leaves to zero_cols: 0 all of them, 1 those
+// not written with the segments of staged chunks.  Where chunks are not staged (1,024
+// nonzeros with binary32 vectors) it is all.
+template <typename VecT>
+int empty_set(const ColDot &C)
+{
+    return C.zp.chunk == 512 || sizeof(VecT) == 8 ? 1 : 0;
+}
+// The largest output stride of the staged copy (the kernel's own condition).
+template <typename VecT>
+int64_t staged_ld_limit(const ColDot &C)
+{
+    return (int64_t)(1 << 28) / (C.zp.chunk * (int64_t)sizeof(VecT));
+}
+
 template <typename ValT, typename VecT>
 int vtm_typed(const spw_matrix_s &A, const VecT *v, VecT *u, bool renumbered, hipStream_t stream)
 {
     const ColDot &C = A.cd;
     int e;
     if (C.cols == 0) return 0;
-    if (C.n_empty > 0) {
+    // the kernel writes the empty columns between a staged chunk's segments itself, unless
+    // there is nothing else to do
+    const int set = C.nnz == 0 ? 0 : empty_set<VecT>(C);
+    const int64_t n_empty = C.n_empty_of[set];
+    if (n_empty > 0) {
         ProfScope ps(stream, "zero_cols");
-        hipLaunchKernelGGL(zero_cols<VecT>, dim3(blocks_for(C.n_empty, 256)), dim3(256), 0, stream, C.d_empty,
-                           C.n_empty, u);
+        hipLaunchKernelGGL(zero_cols<VecT>, dim3(blocks_for(n_empty, 256)), dim3(256), 0, stream, C.d_empty_of[set],
+                           n_empty, u);
         if ((e = (int)hipGetLastError())) return e;
     }
     if (C.nnz == 0) return 0;
@@ -880,10 +902,14 @@ int vtm_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const Co
     const ColDot &C = A.cd;
     int e;
     if (C.cols == 0) return 0;
-    if (C.n_empty > 0) {
+    bool wide = false;                            // an output stride the staged copy does not take
+    for (int c = 0; c < k; ++c) wide = wide || out.ld[c] > staged_ld_limit<VecT>(C);
+    const int set = C.nnz == 0 || wide ? 0 : empty_set<VecT>(C);
+    const int64_t n_empty = C.n_empty_of[set];
+    if (n_empty > 0) {
         ProfScope ps(stream, "zero_cols");
-        hipLaunchKernelGGL(zero_cols_tab<VecT>, dim3(blocks_for(C.n_empty * k, 256)), dim3(256), 0, stream,
-                           C.d_empty, C.n_empty, k, out);
+        hipLaunchKernelGGL(zero_cols_tab<VecT>, dim3(blocks_for(n_empty * k, 256)), dim3(256), 0, stream,
+                           C.d_empty_of[set], n_empty, k, out);
         if ((e = (int)hipGetLastError())) return e;
     }
     if (C.nnz == 0) return 0;
@@ -1042,7 +1068,7 @@ int64_t vtm_workers(int device, int64_t nchunks)
                                                                (nchunks + nw - 1) / nw));
     return wgs * nw;
 }
-int64_t vtm_hot_rows_limit(spw_dtype vdt) { return hot_rows_limit(vdt == SPW_F64 ? 8 : 4, 1); }
+int64_t vtm_stage_cap(int64_t chunk) { return chunk == 512 ? stage_cap<8, double>() : stage_cap<16, double>(); }
 
 int device_cu_count(int device)
 {
