@@ -431,22 +431,52 @@ spw_status claim_stream(spw_matrix_s &A, void *stream, const char *fname)
     return SPW_OK;
 }
 
-// Marks the end of a call's work on stream.
-spw_status release_stream(spw_matrix_s &A, void *stream, const char *fname)
+// The event after a call's work.
+spw_status done_event(spw_matrix_s &A, const char *fname)
+{
+    if (A.last_done) return SPW_OK;
+    hipEvent_t e;
+    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(SPW_ERR_DEVICE, std::string(fname) + ": hipEventCreate failed");
+    }
+    A.last_done = e;
+    return SPW_OK;
+}
+
+thread_local void *t_stop = nullptr;            // a hipEvent_t
+
+// Hands the event to the call's last kernel launch, which completes it (take_stop); dropped
+// again on every way out of the call.  A matrix's first call records its event by itself.
+struct StopEvent {
+    bool offered = false;
+    spw_status offer(spw_matrix_s &A, void *stream, const char *fname)
+    {
+        if (capturing(stream)) return SPW_OK;
+        std::lock_guard<std::mutex> lk(A.use_mu);
+        if (!A.used) return SPW_OK;
+        const spw_status st = done_event(A, fname);
+        if (st) return st;
+        t_stop = A.last_done;
+        offered = true;
+        return SPW_OK;
+    }
+    bool taken() const { return offered && !t_stop; }
+    ~StopEvent() { t_stop = nullptr; }
+};
+
+// Marks the end of a call's work on stream (recorded: its last kernel completes the event).
+spw_status release_stream(spw_matrix_s &A, void *stream, const char *fname, bool recorded = false)
 {
     if (capturing(stream)) return SPW_OK;
     std::lock_guard<std::mutex> lk(A.use_mu);
-    if (!A.last_done) {
-        hipEvent_t e;
-        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+    if (!recorded) {
+        const spw_status st = done_event(A, fname);
+        if (st) return st;
+        if (hipEventRecord((hipEvent_t)A.last_done, (hipStream_t)stream) != hipSuccess) {
             (void)hipGetLastError();
-            return fail(SPW_ERR_DEVICE, std::string(fname) + ": hipEventCreate failed");
+            return fail(SPW_ERR_DEVICE, std::string(fname) + ": hipEventRecord failed");
         }
-        A.last_done = e;
-    }
-    if (hipEventRecord((hipEvent_t)A.last_done, (hipStream_t)stream) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(SPW_ERR_DEVICE, std::string(fname) + ": hipEventRecord failed");
     }
     A.last_stream = stream;
     A.used = true;
@@ -999,6 +1029,13 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
 }
 
 }  // namespace
+
+void *take_stop()
+{
+    void *e = t_stop;
+    t_stop = nullptr;
+    return e;
+}
 
 spw_status grow_scratch(spw_matrix_s &A, int32_t k)
 {
@@ -1805,7 +1842,10 @@ static spw_status run_product(spw_matrix A, bool want_mv, spw_dtype vdt, int32_t
     if (st) return st;
     if ((st = grow_scratch(*A, coldot_tile_width(k)))) return st;
     int e = 0;
+    StopEvent stop;
     if (k == 1) {
+        // k > 1: below, where the plan ends in one of these kernels too
+        if ((st = stop.offer(*A, stream, fname))) return st;
         if (ldi == 1 && ldo == 1) {
             e = scatter ? launch_mv(*A, vdt, 1, in, 1, out, 1, stream) : launch_vtm(*A, vdt, in, out, stream);
         } else if (scatter) {
@@ -1843,12 +1883,13 @@ static spw_status run_product(spw_matrix A, bool want_mv, spw_dtype vdt, int32_t
         }
         if (!plan) plan = rule_plan(*A, scatter, k, ldo);
         if (scatter && plan == SPW_PLAN_PASSES && (st = grow_partial_cols(*A, std::min<int32_t>(k, 8)))) return st;
+        if (plan == SPW_PLAN_PASSES && (st = stop.offer(*A, stream, fname))) return st;
         e = run_plan(*A, plan, scatter, vdt, k, in, ldi, out, ldo, stream);
     }
     if (e == (int)hipErrorNotSupported)
         return fail(SPW_ERR_UNSUPPORTED, std::string(fname) + ": this dtype / k / storage combination is not available");
     if (e) return fail(SPW_ERR_DEVICE, std::string(fname) + ": kernel launch failed: " + hipGetErrorString((hipError_t)e));
-    return release_stream(*A, stream, fname);
+    return release_stream(*A, stream, fname, stop.taken());
 }
 
 static spw_status batch_plan_impl(spw_matrix A, spw_op op, spw_dtype vdt, int32_t k, spw_plan *plan, int32_t *tuned)

@@ -4,6 +4,7 @@
 // gets its own copy.
 #pragma once
 
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -595,6 +596,17 @@ constexpr int MV_BLOCK = SPW_MV_BLOCK;
 constexpr int LDS_BYTES = 160 * 1024;
 
 inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
+
+// Launches a kernel; with a stop event, which the kernel's own completion signals.  A
+// record after the kernel is a packet of its own that waits for it and flushes the caches
+// (two kernels of 4 us back to back: 10.1 us, 13.0 with a record, 10.1 with a stop event).
+template <typename K, typename... Args>
+int launch_kernel(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t stream, void *stop, Args... args)
+{
+    if (stop) hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, nullptr, (hipEvent_t)stop, 0, args...);
+    else hipLaunchKernelGGL(kernel, grid, block, lds, stream, args...);
+    return (int)hipGetLastError();
+}
 
 struct ProfScope {
     void *stream;

@@ -171,9 +171,9 @@ namespace spw {
 int launch_vtm(const spw_matrix_s &A, spw_dtype vdt, const void *v, void *u, void *stream, bool renumbered = false);
 // Column dots for k <= 8 columns in one pass: column c reads in[c] (stride
 // ldi[c]) and writes out[c] (stride ldo[c]); in/out/ldi/ldo are host arrays.
-// Every column is bit-identical to launch_vtm on it.
+// Every column is bit-identical to launch_vtm on it.  last: no launch of the same call follows.
 int launch_vtm_cols(const spw_matrix_s &A, spw_dtype vdt, int32_t k, const void *const *in, const int64_t *ldi,
-                    void *const *out, const int64_t *ldo, void *stream);
+                    void *const *out, const int64_t *ldo, void *stream, bool last = true);
 // Column dots for k columns of row-major V (ldv) into U (ldu), at most 8
 // columns per pass; every column is bit-identical to launch_vtm on it.
 int launch_vtm_multi(const spw_matrix_s &A, spw_dtype vdt, int32_t k, const void *v, int64_t ldv, void *u,
@@ -206,6 +206,9 @@ inline int32_t coldot_tile_width(int32_t k)
 // out_f64: U holds binary64 whatever vdt is (the blocked transpose's partial sums).
 int launch_coldot_batch(const spw_matrix_s &A, const ColDot &C, const int32_t *inv, spw_dtype vdt, int32_t k,
                         const void *V, int64_t ldv, void *U, int64_t ldu, void *stream, bool out_f64 = false);
+// The event that the last kernel of this thread's running call is to complete, for the launch
+// that is the last one (NULL: none; an event left here is recorded by itself).
+void *take_stop();
 // The run kernel of those column dots (spw_run.hip), without the columns that have no
 // nonzeros and without the zone sums; coldot_run_takes says whether it is the better one for
 // a call.  It is taken past 8 columns, but for the smallest matrices and the shortest columns:

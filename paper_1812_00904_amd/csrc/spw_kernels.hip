@@ -786,7 +786,7 @@ int vtm_block_for(const spw_matrix_s &A, bool colpart)
 
 template <int ITEMS, typename IdxT, typename ValT, typename VecT, bool MULTI>
 int launch_vtm_wave_items(const spw_matrix_s &A, const VecT *vin, int k, const ColOut<VecT> &out,
-                          hipStream_t stream)
+                          hipStream_t stream, void *stop)
 {
     const ColDot &C = A.cd;
     const int cus = device_cu_count(A.device);
@@ -801,10 +801,9 @@ int launch_vtm_wave_items(const spw_matrix_s &A, const VecT *vin, int k, const C
         const unsigned grid =
             wch ? (unsigned)(C.n_workers / nw)
                 : (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * vtm_wgs_per_cu(block), wgs_needed));
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, stream, (const IdxT *)C.d_idx, (const ValT *)C.d_val,
-                           C.d_heads, (const int4 *)C.d_cinfo, C.d_segcol, C.nnz, C.zp.n_chunks, wch, vin, k, vhot,
-                           out, A.scratch.carry, C.gap_max);
-        return (int)hipGetLastError();
+        return launch_kernel(kernel, dim3(grid), dim3(block), lds, stream, stop, (const IdxT *)C.d_idx,
+                             (const ValT *)C.d_val, C.d_heads, (const int4 *)C.d_cinfo, C.d_segcol, C.nnz,
+                             C.zp.n_chunks, wch, vin, k, vhot, out, A.scratch.carry, C.gap_max);
     };
     if constexpr (!MULTI && vtm_fits_1024<ITEMS, ValT, VecT>()) {
         if (block == 1024) {
@@ -827,10 +826,11 @@ int launch_vtm_wave_items(const spw_matrix_s &A, const VecT *vin, int k, const C
 
 // Chunks of 1,024 (16 positions per lane) or 512 (8 per lane) nonzeros.
 template <typename IdxT, typename ValT, typename VecT, bool MULTI>
-int launch_vtm_wave(const spw_matrix_s &A, const VecT *vin, int k, const ColOut<VecT> &out, hipStream_t stream)
+int launch_vtm_wave(const spw_matrix_s &A, const VecT *vin, int k, const ColOut<VecT> &out, hipStream_t stream,
+                    void *stop)
 {
-    if (A.cd.zp.chunk == 1024) return launch_vtm_wave_items<16, IdxT, ValT, VecT, MULTI>(A, vin, k, out, stream);
-    if (A.cd.zp.chunk == 512) return launch_vtm_wave_items<8, IdxT, ValT, VecT, MULTI>(A, vin, k, out, stream);
+    if (A.cd.zp.chunk == 1024) return launch_vtm_wave_items<16, IdxT, ValT, VecT, MULTI>(A, vin, k, out, stream, stop);
+    if (A.cd.zp.chunk == 512) return launch_vtm_wave_items<8, IdxT, ValT, VecT, MULTI>(A, vin, k, out, stream, stop);
     return (int)hipErrorNotSupported;
 }
 
@@ -880,15 +880,16 @@ int vtm_typed(const spw_matrix_s &A, const VecT *v, VecT *u, bool renumbered, hi
         ColOut<VecT> out{};
         out.u[0] = u;
         out.ld[0] = 1;
-        e = C.idx_kind == IdxKind::U16 ? launch_vtm_wave<uint16_t, ValT, VecT, false>(A, vin, 1, out, stream)
-                                       : launch_vtm_wave<int32_t, ValT, VecT, false>(A, vin, 1, out, stream);
+        void *stop = C.n_zones > 0 ? nullptr : take_stop();
+        e = C.idx_kind == IdxKind::U16 ? launch_vtm_wave<uint16_t, ValT, VecT, false>(A, vin, 1, out, stream, stop)
+                                       : launch_vtm_wave<int32_t, ValT, VecT, false>(A, vin, 1, out, stream, stop);
         if (e) return e;
     }
     if (C.n_zones > 0) {
         ProfScope ps(stream, "zone_fixup");
-        hipLaunchKernelGGL(zone_fixup<VecT>, dim3(blocks_for(C.n_zones, 256)), dim3(256), 0, stream, C.d_zone_col,
-                           C.d_zone_first, C.d_zone_last, C.n_zones, A.scratch.carry, u);
-        if ((e = (int)hipGetLastError())) return e;
+        e = launch_kernel(zone_fixup<VecT>, dim3(blocks_for(C.n_zones, 256)), dim3(256), 0, stream, take_stop(),
+                          C.d_zone_col, C.d_zone_first, C.d_zone_last, C.n_zones, A.scratch.carry, u);
+        if (e) return e;
     }
     return 0;
 }
@@ -896,7 +897,7 @@ int vtm_typed(const spw_matrix_s &A, const VecT *v, VecT *u, bool renumbered, hi
 // Up to MULTI_MAX columns in one pass, each with its own input and output
 // base and stride; every column is bit-identical to the single-vector product.
 template <typename ValT, typename VecT>
-int vtm_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const ColOut<VecT> &out,
+int vtm_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const ColOut<VecT> &out, bool last,
                    hipStream_t stream)
 {
     const ColDot &C = A.cd;
@@ -923,15 +924,17 @@ int vtm_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const Co
     }
     {
         ProfScope ps(stream, "vtm_wave_multi");
-        e = C.idx_kind == IdxKind::U16 ? launch_vtm_wave<uint16_t, ValT, VecT, true>(A, vp, k, out, stream)
-                                       : launch_vtm_wave<int32_t, ValT, VecT, true>(A, vp, k, out, stream);
+        void *stop = C.n_zones > 0 || !last ? nullptr : take_stop();
+        e = C.idx_kind == IdxKind::U16 ? launch_vtm_wave<uint16_t, ValT, VecT, true>(A, vp, k, out, stream, stop)
+                                       : launch_vtm_wave<int32_t, ValT, VecT, true>(A, vp, k, out, stream, stop);
         if (e) return e;
     }
     if (C.n_zones > 0) {
         ProfScope ps(stream, "zone_fixup");
-        hipLaunchKernelGGL(zone_fixup_tab<VecT>, dim3(blocks_for(C.n_zones * k, 256)), dim3(256), 0, stream,
-                           C.d_zone_col, C.d_zone_first, C.d_zone_last, C.n_zones, k, A.scratch.carry, out);
-        if ((e = (int)hipGetLastError())) return e;
+        e = launch_kernel(zone_fixup_tab<VecT>, dim3(blocks_for(C.n_zones * k, 256)), dim3(256), 0, stream,
+                          last ? take_stop() : nullptr, C.d_zone_col, C.d_zone_first, C.d_zone_last, C.n_zones, k,
+                          A.scratch.carry, out);
+        if (e) return e;
     }
     return 0;
 }
@@ -952,14 +955,14 @@ void fill_tables(int k, const void *const *in, const int64_t *ldi, void *const *
 
 // Sums the partials of `k` columns into their outputs.
 template <typename VecT>
-int launch_mv_reduce(const spw_matrix_s &A, const double *partial, int k, const ColOut<VecT> &out, hipStream_t stream)
+int launch_mv_reduce(const spw_matrix_s &A, const double *partial, int k, const ColOut<VecT> &out, bool last,
+                     hipStream_t stream)
 {
     ProfScope ps(stream, "mv_reduce");
     const unsigned panel_blocks = blocks_for(A.panel_rows, 32);
-    hipLaunchKernelGGL(mv_reduce<VecT>, dim3((unsigned)(A.n_panels * panel_blocks), (unsigned)k), dim3(256), 0, stream,
-                       partial, (int)A.panel_rows, (int)panel_blocks, A.d_panels, (int)A.n_panels,
-                       A.relabeled ? A.d_inv : nullptr, out, A.mv_wgs * A.panel_rows);
-    return (int)hipGetLastError();
+    return launch_kernel(mv_reduce<VecT>, dim3((unsigned)(A.n_panels * panel_blocks), (unsigned)k), dim3(256), 0,
+                         stream, last ? take_stop() : nullptr, partial, (int)A.panel_rows, (int)panel_blocks,
+                         A.d_panels, (int)A.n_panels, A.relabeled ? A.d_inv : nullptr, out, A.mv_wgs * A.panel_rows);
 }
 
 // Columns of one launch that share an LDS panel: as many as fit, at most MV_COLS.
@@ -973,7 +976,8 @@ int mv_cols_together(const spw_matrix_s &A)
 // one launch.  Columns that are adjacent entries of the same rows are taken
 // in groups of up to mv_cols_together, of sizes that differ by one at most.
 template <typename ValT, typename VecT>
-int mv_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const ColOut<VecT> &out, hipStream_t stream)
+int mv_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const ColOut<VecT> &out, bool last,
+                  hipStream_t stream)
 {
     int e;
     const int W = (int)A.mv_wgs;
@@ -1004,7 +1008,7 @@ int mv_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const Col
                            A.d_wg_blk, A.d_wg_order, gr, ng, A.scratch.partial_cols, (int)A.panel_rows, W);
         if ((e = (int)hipGetLastError())) return e;
     }
-    return launch_mv_reduce<VecT>(A, A.scratch.partial_cols, k, out, stream);
+    return launch_mv_reduce<VecT>(A, A.scratch.partial_cols, k, out, last, stream);
 }
 
 // k right-hand sides, up to pcols columns a launch when the multi-column partial
@@ -1026,7 +1030,7 @@ int mv_typed(const spw_matrix_s &A, int32_t k, const VecT *x, int64_t ldx, VecT 
                 out.u[c] = y + c0 + c;
                 out.ld[c] = ldy;
             }
-            if ((e = mv_cols_typed<ValT, VecT>(A, kb, in, out, stream))) return e;
+            if ((e = mv_cols_typed<ValT, VecT>(A, kb, in, out, c0 + kb == k, stream))) return e;
         }
         return 0;
     }
@@ -1045,7 +1049,7 @@ int mv_typed(const spw_matrix_s &A, int32_t k, const VecT *x, int64_t ldx, VecT 
         ColOut<VecT> out{};
         out.u[0] = y + c;
         out.ld[0] = ldy;
-        if ((e = launch_mv_reduce<VecT>(A, A.scratch.partial, 1, out, stream))) return e;
+        if ((e = launch_mv_reduce<VecT>(A, A.scratch.partial, 1, out, c + 1 == k, stream))) return e;
     }
     return 0;
 }
@@ -1087,7 +1091,7 @@ int launch_vtm(const spw_matrix_s &A, spw_dtype vdt, const void *v, void *u, voi
 }
 
 int launch_vtm_cols(const spw_matrix_s &A, spw_dtype vdt, int32_t k, const void *const *in, const int64_t *ldi,
-                    void *const *out, const int64_t *ldo, void *stream)
+                    void *const *out, const int64_t *ldo, void *stream, bool last)
 {
     if (k < 1 || k > MULTI_MAX) return (int)hipErrorInvalidValue;
     return with_types(A.value_storage, vdt, [&](auto vt, auto xt) {
@@ -1096,7 +1100,7 @@ int launch_vtm_cols(const spw_matrix_s &A, spw_dtype vdt, int32_t k, const void 
         ColIn<VecT> ti;
         ColOut<VecT> to;
         fill_tables<VecT>(k, in, ldi, out, ldo, ti, to);
-        return vtm_cols_typed<ValT, VecT>(A, k, ti, to, (hipStream_t)stream);
+        return vtm_cols_typed<ValT, VecT>(A, k, ti, to, last, (hipStream_t)stream);
     });
 }
 
@@ -1115,7 +1119,7 @@ int launch_vtm_multi(const spw_matrix_s &A, spw_dtype vdt, int32_t k, const void
             li[c] = ldv;
             lo[c] = ldu;
         }
-        const int e = launch_vtm_cols(A, vdt, kk, in, li, out, lo, stream);
+        const int e = launch_vtm_cols(A, vdt, kk, in, li, out, lo, stream, c0 + kk == k);
         if (e) return e;
     }
     return 0;
@@ -1150,7 +1154,7 @@ int launch_mv_cols(const spw_matrix_s &A, spw_dtype vdt, int32_t k, const void *
         ColOut<VecT> to;
         fill_tables<VecT>(k, in, ldi, out, ldo, ti, to);
         if (A.rows == 0) return 0;
-        return mv_cols_typed<ValT, VecT>(A, k, ti, to, (hipStream_t)stream);
+        return mv_cols_typed<ValT, VecT>(A, k, ti, to, true, (hipStream_t)stream);
     });
 }
 
