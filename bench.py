@@ -48,9 +48,9 @@ sys.path.insert(0, ROOT)
 METRIC = "Ax / vᵀA effective HBM GB/s (% of peak); batched vs plain; p50/p99 latency"
 HBM_PEAK_GBS = 8000.0
 NROT = 4          # input vectors the timed pairs rotate through
-# the sources of the single-vector kernels the headline roofline is taken on, and of the tiles
+# the sources of the single-vector kernels the headline roofline is taken on, and of the multi-RHS column dots
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1812_00904_amd", "csrc", f) for f in ("spw_device.h", "spw_kernels.hip")]
-TILE_SRCS = [os.path.join(ROOT, "paper_1812_00904_amd", "csrc", "spw_tile.hip")]
+TILE_SRCS = [os.path.join(ROOT, "paper_1812_00904_amd", "csrc", f) for f in ("spw_tile.hip", "spw_run.hip")]
 COUNTER_FILES = {"wide": os.path.join(ROOT, "profiles", "pmc_counters_wide_2e8.txt"),
                  "batched": os.path.join(ROOT, "profiles", "pmc_counters_batched_5e7.txt")}
 TRAFFIC_FILE = COUNTER_FILES["wide"]
@@ -1082,7 +1082,7 @@ def summarize_counters(workload: str, dirs):
         v = c.get(name)
         return None if v is None else v[0]
 
-    order = sorted(per, key=lambda k: (not k.startswith(("vtm_wave", "mv_bucket", "cdot_tile")), k))
+    order = sorted(per, key=lambda k: (not k.startswith(("vtm_wave", "mv_bucket", "cdot_run", "cdot_tile")), k))
     for kern in order:
         c = per[kern]
         if kern.startswith(("at::", "__amd")):
