@@ -415,10 +415,11 @@ bool capturing(void *stream)
     return yes;
 }
 
-spw_status claim_stream(spw_matrix_s &A, void *stream, const char *fname)
+// Whether a call on stream may use the matrix now (use_mu held).
+spw_status may_use(spw_matrix_s &A, void *stream, const char *fname)
 {
-    if (capturing(stream)) return SPW_OK;
-    std::lock_guard<std::mutex> lk(A.use_mu);
+    if (A.held > 0 && stream != A.held_stream)
+        return fail(SPW_ERR_BUSY, std::string(fname) + ": a solve is being issued on another stream");
     if (A.used && stream != A.last_stream && A.last_done) {
         const hipError_t q = hipEventQuery((hipEvent_t)A.last_done);
         if (q == hipErrorNotReady)
@@ -429,6 +430,13 @@ spw_status claim_stream(spw_matrix_s &A, void *stream, const char *fname)
         }
     }
     return SPW_OK;
+}
+
+spw_status claim_stream(spw_matrix_s &A, void *stream, const char *fname)
+{
+    if (capturing(stream)) return SPW_OK;
+    std::lock_guard<std::mutex> lk(A.use_mu);
+    return may_use(A, stream, fname);
 }
 
 // The event after a call's work.
@@ -482,6 +490,55 @@ spw_status release_stream(spw_matrix_s &A, void *stream, const char *fname, bool
     A.used = true;
     return SPW_OK;
 }
+
+// Holds a matrix for one stream while a call of many launches is being issued: the event that
+// keeps other streams out is recorded after the last of them, also where the call ends early.
+class StreamHold {
+public:
+    StreamHold(spw_matrix_s &A, void *stream) : A_(A), stream_(stream) {}
+    StreamHold(const StreamHold &) = delete;
+    StreamHold &operator=(const StreamHold &) = delete;
+    spw_status claim(const char *fname)
+    {
+        if (capturing(stream_)) return SPW_OK;
+        std::lock_guard<std::mutex> lk(A_.use_mu);
+        spw_status st = may_use(A_, stream_, fname);
+        if (!st) st = done_event(A_, fname);
+        if (st) return st;
+        ++A_.held;
+        A_.held_stream = stream_;
+        holding_ = true;
+        return SPW_OK;
+    }
+    // Records the event, then lets other streams in once it has passed.
+    spw_status release(const char *fname)
+    {
+        if (!holding_ || drop()) return SPW_OK;
+        return fail(SPW_ERR_DEVICE, std::string(fname) + ": hipEventRecord failed");
+    }
+    ~StreamHold()
+    {
+        if (holding_) drop();
+    }
+
+private:
+    bool drop()
+    {
+        holding_ = false;
+        std::lock_guard<std::mutex> lk(A_.use_mu);
+        --A_.held;
+        if (hipEventRecord((hipEvent_t)A_.last_done, (hipStream_t)stream_) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        A_.last_stream = stream_;
+        A_.used = true;
+        return true;
+    }
+    spw_matrix_s &A_;
+    void *stream_;
+    bool holding_ = false;
+};
 
 // Column-dot storage of a rows x cols CSC matrix (ptr over columns, rows[]
 // already in the numbering the kernel will use).
@@ -2000,8 +2057,10 @@ static spw_status spw_cgls_impl(spw_matrix A, spw_dtype vdt, const void *b, void
     if ((A->m > 0 && !b) || (A->n > 0 && !x)) return fail(SPW_ERR_INVALID_ARG, "spw_cgls: NULL vector");
     DeviceGuard dg(A->device);
     if (dg.st) return dg.st;
-    // refuse a busy matrix before any workspace is reallocated
-    spw_status st = claim_stream(*A, stream, "spw_cgls");
+    // refuse a busy matrix before any workspace is reallocated, and keep other streams out until
+    // every launch of the solve is issued
+    StreamHold hold(*A, stream);
+    spw_status st = hold.claim("spw_cgls");
     if (st) return st;
     if ((st = grow_scratch(*A, 1))) return st;
     const int64_t hl = 2 * ((int64_t)iters + 1);
@@ -2034,7 +2093,7 @@ static spw_status spw_cgls_impl(spw_matrix A, spw_dtype vdt, const void *b, void
         return SPW_OK;
     };
     auto vec = [&](CglsVecOp op, int64_t k) { return done(launch_cgls_vec(op, w, k, stream)); };
-    // out = A in (with A), out = A^T in: the single-vector products (the stream is claimed above)
+    // out = A in (with A), out = A^T in: the single-vector products (the stream is held above)
     auto product = [&](bool with_a, const double *in, double *out, bool renumbered) {
         const bool scatter = (A->format == SPW_CSC) == with_a;
         return done(scatter ? launch_mv(*A, SPW_F64, 1, in, 1, out, 1, stream)
@@ -2074,7 +2133,7 @@ static spw_status spw_cgls_impl(spw_matrix A, spw_dtype vdt, const void *b, void
     for (int64_t k = 0; k < iters; ++k)
         if ((st = iteration(k))) return st;
     if ((st = vec(CglsVecOp::GAMMA, iters))) return st;
-    if ((st = release_stream(*A, stream, "spw_cgls"))) return st;
+    if ((st = hold.release("spw_cgls"))) return st;
     if (hist) {
         if (hipMemcpyAsync(hist, W.hist, (size_t)hl * sizeof(double), hipMemcpyDeviceToHost, (hipStream_t)stream) !=
                 hipSuccess ||

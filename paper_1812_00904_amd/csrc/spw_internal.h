@@ -159,6 +159,9 @@ struct spw_matrix_s {
     void *last_stream = nullptr;
     void *last_done = nullptr;          // hipEvent_t, created on first use
     bool used = false;
+    // Solves being issued, all on held_stream: their event comes after their last launch only.
+    int held = 0;
+    void *held_stream = nullptr;
 };
 
 namespace spw {

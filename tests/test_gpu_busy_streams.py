@@ -1,6 +1,8 @@
 """A matrix serves one stream at a time: while its last call is pending on one stream a call on
 another is refused, whatever kernel the pending call ends in, on its first call and on
 later ones; once that work is done the other stream is served."""
+import threading
+
 import pytest
 import torch
 
@@ -58,3 +60,49 @@ def test_pending_call_refuses_another_stream(spw, op, k, long_columns):
     torch.cuda.synchronize()
     assert torch.equal(y, z)
     M.close()
+
+
+@pytest.mark.parametrize("fmt", ["csc", "csr"])
+def test_solve_being_issued_refuses_another_stream(spw, fmt):
+    # x moves once the first iteration has run; thousands of launches are then still to be issued, and the
+    # call's event comes after the last.  A new matrix: no earlier call's event stands in for it.
+    A = synth.random_csc(50, 2_000, 6, seed=3)
+    code, m, n = (spw.SPW_CSC, A.m, A.n) if fmt == "csc" else (spw.SPW_CSR, A.n, A.m)
+    b, v, u = (torch.rand(s, dtype=torch.float64, device="cuda") for s in (m, m, n))
+    alone = torch.zeros(n, dtype=torch.float64, device="cuda")
+    iters = 5_000
+    for used_before in (False, True):
+        M = spw.SpwMatrix(code, m, n, A.ptr, A.idx, A.val)
+        sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
+        x = torch.zeros(n, dtype=torch.float64, device="cuda")
+        if used_before:
+            M.vtm(v, u, stream=sb)
+        torch.cuda.synchronize()
+        print("solve being issued %s used=%d" % (fmt, used_before), flush=True)
+        errs = []
+
+        def solve():
+            try:
+                M.cgls(b, x, iters, hist=False, stream=sa)
+            except spw.SpwError as e:
+                errs.append(e)
+
+        t = threading.Thread(target=solve)
+        t.start()
+        with torch.cuda.stream(sb):
+            while t.is_alive() and not x.any().item():
+                pass
+        refusals = 0
+        for call in (lambda: M.vtm(v, u, stream=sb), lambda: M.mv(u, v, stream=sb),
+                     lambda: M.cgls(b, torch.zeros_like(x), 1, hist=False, stream=sb)):
+            with pytest.raises(spw.SpwError) as e:
+                call()
+            assert e.value.status_name == "SPW_ERR_BUSY"
+            refusals += t.is_alive()
+        t.join()
+        assert refusals and not errs                      # refused while the solve was being issued
+        torch.cuda.synchronize()
+        M.cgls(b, alone.zero_(), iters, hist=False, stream=sb)
+        torch.cuda.synchronize()
+        assert torch.equal(x.view(torch.int64), alone.view(torch.int64))   # and the solve was not disturbed
+        M.close()
