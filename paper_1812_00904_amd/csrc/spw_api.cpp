@@ -826,54 +826,55 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     const int64_t P = (rows + R - 1) / R;
     A.panel_rows = R;
     A.n_panels = P;
-    // 1. Nonzeros of every panel before each block of CB columns (the panels' own
-    //    column-ordered positions are found from these by scanning one block).
-    const int64_t CB = 1024, ncb = (cols + CB - 1) / CB;
-    std::vector<int32_t> panel_of;              // of a row (one panel: unused)
-    std::vector<int64_t> before_cb((size_t)((ncb + 1) * P), 0);   // [block * P + panel]
-    if (P == 1) {
-        for (int64_t c = 0; c <= ncb; ++c) before_cb[(size_t)c] = ptr[std::min(c * CB, cols)];
-    } else {
-        panel_of.resize((size_t)rows);
+    // 1. With several panels, the nonzeros panel by panel, each panel's in column order:
+    //    a counting sort over parts of the source, whatever the number of panels.
+    struct Nz {
+        int32_t p, j;                           // source position and column
+    };
+    std::unique_ptr<Nz[]> order;
+    std::vector<int64_t> panel_at((size_t)P + 1, 0);        // a panel's first entry in order
+    panel_at[(size_t)P] = nnz;
+    if (P > 1) {
+        order.reset(new Nz[(size_t)std::max<int64_t>(nnz, 1)]);
+        std::vector<int32_t> panel_of((size_t)rows);
         for (int64_t r = 0; r < rows; ++r) panel_of[(size_t)r] = (int32_t)(r % P);
-        parallel_for(ncb * CB, [&](int64_t a, int64_t b) {
-            for (int64_t c = (a + CB - 1) / CB; c < (b + CB - 1) / CB; ++c) {
-                int64_t *cnt = &before_cb[(size_t)((c + 1) * P)];
-                for (int64_t p = ptr[c * CB]; p < ptr[std::min((c + 1) * CB, cols)]; ++p)
-                    ++cnt[panel_of[(size_t)rowi[p]]];
+        // few enough parts that their tables stay small beside the nonzeros
+        const int64_t T = std::max<int64_t>(1, std::min<int64_t>(32, nnz / (4 * P)));
+        std::vector<int64_t> at((size_t)(T * P), 0);        // [part * P + panel]
+        parallel_ranges(T, [&](int64_t t) {
+            int64_t *cnt = &at[(size_t)(t * P)];
+            for (int64_t p = nnz * t / T; p < nnz * (t + 1) / T; ++p) ++cnt[panel_of[(size_t)rowi[p]]];
+        });
+        int64_t run = 0;
+        for (int64_t q = 0; q < P; ++q) {
+            panel_at[(size_t)q] = run;
+            for (int64_t t = 0; t < T; ++t) {
+                const int64_t n = at[(size_t)(t * P + q)];
+                at[(size_t)(t * P + q)] = run;
+                run += n;
+            }
+        }
+        parallel_ranges(T, [&](int64_t t) {
+            int64_t *to = &at[(size_t)(t * P)];
+            const int64_t p0 = nnz * t / T, p1 = nnz * (t + 1) / T;
+            int64_t j = std::upper_bound(ptr, ptr + cols + 1, p0) - ptr - 1;
+            for (int64_t p = p0; p < p1; ++p) {
+                while (ptr[j + 1] <= p) ++j;
+                order[(size_t)to[panel_of[(size_t)rowi[p]]]++] = Nz{(int32_t)p, (int32_t)j};
             }
         });
-        for (int64_t c = 0; c < ncb; ++c)
-            for (int64_t q = 0; q < P; ++q)
-                before_cb[(size_t)((c + 1) * P + q)] += before_cb[(size_t)(c * P + q)];
     }
-    auto in_panel = [&](int64_t p, int64_t q) { return P == 1 || panel_of[(size_t)rowi[p]] == q; };
-    auto panel_nnz = [&](int64_t q) { return before_cb[(size_t)(ncb * P + q)]; };
+    auto panel_nnz = [&](int64_t q) { return panel_at[(size_t)(q + 1)] - panel_at[(size_t)q]; };
     // nonzeros of panel q in columns before j
     auto before = [&](int64_t q, int64_t j) -> int64_t {
         if (P == 1) return ptr[j];
-        const int64_t c = j / CB;
-        int64_t n = before_cb[(size_t)(c * P + q)];
-        if (c * CB < j)
-            for (int64_t p = ptr[c * CB]; p < ptr[j]; ++p) n += in_panel(p, q);
-        return n;
+        const Nz *a = order.get() + panel_at[(size_t)q], *b = order.get() + panel_at[(size_t)(q + 1)];
+        return std::lower_bound(a, b, j, [](const Nz &z, int64_t col) { return z.j < col; }) - a;
     };
-    // (column, position) of nonzero number t of panel q
-    struct At {
-        int64_t j, p;
-    };
-    auto locate = [&](int64_t q, int64_t t) -> At {
-        if (P == 1) return At{std::upper_bound(ptr, ptr + cols + 1, t) - ptr - 1, t};
-        int64_t lo = 0, hi = ncb;               // the last block with at most t nonzeros of q before it
-        while (hi - lo > 1) {
-            const int64_t mid = (lo + hi) / 2;
-            if (before_cb[(size_t)(mid * P + q)] <= t) lo = mid;
-            else hi = mid;
-        }
-        int64_t p = ptr[lo * CB];
-        for (int64_t n = before_cb[(size_t)(lo * P + q)];; ++p)
-            if (in_panel(p, q) && n++ == t) break;
-        return At{std::upper_bound(ptr, ptr + cols + 1, p) - ptr - 1, p};
+    // column of nonzero number t of panel q
+    auto column_of = [&](int64_t q, int64_t t) -> int64_t {
+        if (P == 1) return std::upper_bound(ptr, ptr + cols + 1, t) - ptr - 1;
+        return order[(size_t)(panel_at[(size_t)q] + t)].j;
     };
 
     // 2. Deal each panel's rows to the NB waves, heaviest first onto the lightest wave.
@@ -902,7 +903,7 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     struct WgRange {
         int32_t panel;
         int64_t a, b;      // panel-ordered positions
-        At start;          // column and position of the first
+        int64_t col;       // column of the first
     };
     std::vector<WgRange> wr;
     A.panels.clear();
@@ -962,14 +963,13 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
                     a = qn * w / nw;
                     b = qn * (w + 1) / nw;
                 }
-                if (b > a) wr.push_back(WgRange{(int32_t)q, a, b, At{0, 0}});
+                if (b > a) wr.push_back(WgRange{(int32_t)q, a, b, column_of(q, a)});
             }
         }
         pd.nwg = (int32_t)(wr.size() - (size_t)pd.wg0);
         A.panels.push_back(pd);
     }
     const int64_t W = (int64_t)wr.size();
-    parallel_ranges(W, [&](int64_t w) { wr[(size_t)w].start = locate(wr[(size_t)w].panel, wr[(size_t)w].a); });
     // Launch order: the ranges by their first column, so that the panels of one
     // column region are neighbours, and the x-th eighth of that sequence on XCD x
     // (workgroup ids are dealt to the 8 XCDs round-robin): the panels of a region then
@@ -979,7 +979,7 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
         std::vector<int32_t> seq((size_t)W);
         std::iota(seq.begin(), seq.end(), 0);
         std::stable_sort(seq.begin(), seq.end(), [&](int32_t a, int32_t b) {
-            return wr[(size_t)a].start.j < wr[(size_t)b].start.j;
+            return wr[(size_t)a].col < wr[(size_t)b].col;
         });
         size_t next = 0;
         for (int64_t x = 0; x < 8; ++x)
@@ -1002,10 +1002,16 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
             base[v] = 0;
             count[v] = BLK;                                 // no block yet
         }
-        int64_t j = g.start.j, p = g.start.p;
-        for (int64_t left = g.b - g.a; left > 0; ++p) {
-            if (!in_panel(p, g.panel)) continue;
-            while (ptr[j + 1] <= p) ++j;
+        const Nz *nz = P > 1 ? order.get() + panel_at[(size_t)g.panel] : nullptr;
+        int64_t j = g.col;
+        for (int64_t t = g.a; t < g.b; ++t) {
+            int64_t p = t;
+            if (nz) {
+                p = nz[t].p;
+                j = nz[t].j;
+            } else {
+                while (ptr[j + 1] <= p) ++j;
+            }
             const int v = wave_of[(size_t)rowi[p]];
             if (count[v] == BLK || j - base[v] >= SPAN) {
                 base[v] = j;
@@ -1014,7 +1020,6 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
             }
             ++count[v];
             put(v, j - base[v], p);
-            --left;
         }
     };
     std::vector<int32_t> wg_blk((size_t)(W * (NB + 1)), 0);
