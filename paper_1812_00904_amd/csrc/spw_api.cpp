@@ -786,6 +786,7 @@ int64_t auto_chunk(int64_t cols, const int64_t *ptr, spw_dtype storage)
 // the multi-column product take them at once, so the next such count is taken where it
 // is at most 1.7 times the best one (20,000 x 5e6: four panels, 6 us of a single
 // product for a four-column block at a third of its time).
+// cols: mv_read_cols, not the matrix's columns, where the ranges span uneven numbers of them.
 int64_t mv_auto_panels(int64_t rows, int64_t cols, int64_t limit)
 {
     const double best = std::sqrt(6.0 * 256.0 * (double)rows / (double)std::max<int64_t>(cols, 1));
@@ -800,6 +801,36 @@ int64_t mv_auto_panels(int64_t rows, int64_t cols, int64_t limit)
         }
     }
     return std::min(P, std::max<int64_t>(rows, 1));
+}
+
+// The columns whose entries of x the panels wait for.  A range of equal nonzeros reads as
+// many entries as it holds columns, and every panel of the widest range reads them again, at
+// about 35 bytes a nanosecond and CU: where columns are ordered by length, the last range's
+// entries decide, not the average (20,000 x 5e6, 5e7 nonzeros, us at 1 / 2 / 3 / 4 panels,
+// columns by descending length 167 / 200 / 228 / 243, unordered 121 / 115 / - / 118).  So the
+// widest range's columns times the number of ranges, from two and a half times the average on:
+// below that the ranges of unordered columns of very uneven lengths differ by themselves, and a
+// panel fewer costs more than it gives (19,996 x 1.36e6, 9e6 nonzeros, binary32 vectors, 32 us in
+// five panels, 35 in four).  Ranges that are not of equal nonzeros (the other partitions) span
+// even numbers of columns or are meant not to.
+int64_t mv_read_cols(int64_t cols, const int64_t *ptr, spw_partition part, int64_t ranges)
+{
+    const int64_t nnz = ptr[cols];
+    if (part != SPW_PART_NONZERO || nnz < ranges) return cols;
+    std::vector<int64_t> filled((size_t)ranges, 0);
+    auto column_at = [&](int64_t p) { return std::upper_bound(ptr, ptr + cols + 1, p) - ptr - 1; };
+    parallel_ranges(ranges, [&](int64_t w) {
+        const int64_t a = column_at(nnz * w / ranges), b = column_at(nnz * (w + 1) / ranges - 1);
+        int64_t n = 0;
+        for (int64_t j = a; j <= b; ++j) n += ptr[j] < ptr[j + 1];
+        filled[(size_t)w] = n;
+    });
+    int64_t widest = 0, sum = 0;
+    for (int64_t n : filled) {
+        widest = std::max(widest, n);
+        sum += n;
+    }
+    return 2 * widest * ranges > 5 * sum ? std::max(cols, widest * ranges) : cols;
 }
 
 // Row panels, wave row sets and blocks of the scatter product (see
@@ -819,7 +850,8 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     if (panel_rows_opt > 0) {
         R = std::min<int64_t>(panel_rows_opt, limit);
     } else {
-        const int64_t want = mv_auto_panels(rows, cols, limit);
+        const int64_t read = mv_read_cols(cols, ptr, A.partition, device_cu_count(A.device));
+        const int64_t want = mv_auto_panels(rows, read, limit);
         R = (rows + want - 1) / want;
     }
     R = std::max<int64_t>(std::min(R, rows), 1);

@@ -1,0 +1,44 @@
+"""The number of row panels of the scatter product where columns are ordered by length: every panel
+reads the entries of x again, and the ranges of equal nonzeros at the short columns read most of them,
+so such a matrix keeps few panels; unordered columns and partitions that even the columns out keep
+theirs.  Products against the CPU oracle within 1e-13 * sum|a||x|."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def spw():
+    from paper_1812_00904_amd import spw as mod
+    mod.load()
+    assert torch.cuda.is_available()
+    return mod
+
+
+# 5,000 x 200,000, about 20 a column with many of one: six panels for even ranges, one where a range
+# of 1/256 of the nonzeros spans twenty times the average number of columns
+@pytest.mark.parametrize("order,partition,panels", [
+    ("random", 0, 6), ("descending", 0, 1), ("ascending", 0, 1), ("descending", 1, 6), ("descending", 2, 6),
+    ("gaps", 0, 6)])
+def test_panels_by_column_order(spw, order, partition, panels):
+    rng = np.random.Generator(np.random.PCG64(3))
+    lengths = np.r_[np.full(60_000, 1), rng.integers(2, 55, 140_000)]
+    if order == "random":
+        lengths = rng.permutation(lengths)
+    elif order == "gaps":                             # half of the columns empty, together: not read
+        lengths = np.r_[rng.integers(10, 31, 50_000), np.zeros(100_000, dtype=np.int64), rng.integers(10, 31, 50_000)]
+    else:
+        lengths = np.sort(lengths)[::-1 if order == "descending" else 1]
+    A = synth.from_lengths(5_000, lengths, 11, row_alpha=0.5)
+    x = synth.vector(A.n, 3, 1)
+    ref, d = oracle.mv_csc(A.m, A.n, A.ptr, A.idx, A.val, x, with_d=True)
+    M = spw.SpwMatrix(spw.SPW_CSC, A.m, A.n, A.ptr, A.idx, A.val, partition=partition)
+    assert M.info()["n_panels"] == panels
+    y = M.mv(torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.all(np.abs(y - ref) <= 1e-13 * d)
+    M.close()
