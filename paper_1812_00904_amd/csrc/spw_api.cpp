@@ -1000,6 +1000,7 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
         }
         pd.nwg = (int32_t)(wr.size() - (size_t)pd.wg0);
         A.panels.push_back(pd);
+        A.panel_wgs = std::max<int64_t>(A.panel_wgs, pd.nwg);
     }
     const int64_t W = (int64_t)wr.size();
     // Launch order: the ranges by their first column, so that the panels of one

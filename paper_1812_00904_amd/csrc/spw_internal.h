@@ -145,7 +145,7 @@ struct spw_matrix_s {
     int64_t n_mblocks = 0;
     std::vector<spw::PanelDesc> panels;
     spw::PanelDesc *d_panels = nullptr;
-    int64_t mv_wgs = 0;
+    int64_t mv_wgs = 0, panel_wgs = 0;  // workgroup ranges: all, most of one panel
 
     spw::Scratch scratch;
     spw::CglsScratch cgls;

@@ -660,12 +660,16 @@ __global__ __launch_bounds__(BLOCK) void mv_bucket_cols(
 // y[caller row] = sum over the panel's workgroups of their partials.  Internal
 // row r belongs to panel r mod npanels, at panel-local row r / npanels; a
 // workgroup takes 32 consecutive rows of one panel, eight threads a row: thread t
-// adds workgroups t, t+8, t+16, ... in ascending order with sixteen loads in
+// adds workgroups t, t+8, t+16, ... in ascending order with up to sixteen loads in
 // flight (a chain of dependent trips to memory bounds this kernel, not its
 // bytes), then the eight sums are combined pairwise, so the order of every
-// addition is fixed.  Column blockIdx.y: its partials start col_stride doubles
+// addition is fixed.  FEW: panels of at most eight workgroups, where one thread takes a
+// whole row, in the same order, and the panels are one sequence of rows, so that small
+// ones fill a workgroup too (2e6 x 2e6 in 98 panels of two or three workgroups: 83 us with
+// eight threads a row, five of them idle, now 43; 500,000 rows in 49 panels 32 and 17).  Column blockIdx.y: its partials start col_stride doubles
 // further, its output is out.u[column].
-template <typename VecT>
+constexpr int MV_FEW = 8;
+template <typename VecT, bool FEW>
 __global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ partial, int panel_rows, int panel_blocks,
                                                  const PanelDesc *__restrict__ panels, int npanels,
                                                  const int32_t *__restrict__ inv, ColOut<VecT> out, int64_t col_stride)
@@ -678,22 +682,45 @@ __global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ part
         y = blockIdx.y == c ? out.u[c] : y;
         ldy = blockIdx.y == c ? out.ld[c] : ldy;
     }
-    const int p = blockIdx.x / panel_blocks;
-    const int local = (blockIdx.x - p * panel_blocks) * 32 + (threadIdx.x & 31);
-    const int t = threadIdx.x >> 5;
+    int p, local, t = 0;
+    if constexpr (FEW) {
+        const uint32_t g = blockIdx.x * 256u + threadIdx.x;
+        p = (int)min(g / (uint32_t)panel_rows, (uint32_t)npanels - 1u);
+        local = (int)(g - (uint32_t)p * (uint32_t)panel_rows);
+    } else {
+        p = blockIdx.x / panel_blocks;
+        local = (blockIdx.x - p * panel_blocks) * 32 + (threadIdx.x & 31);
+        t = threadIdx.x >> 5;
+    }
     const PanelDesc pd = panels[p];
     const bool live = local < pd.rows;
+    const double *src = partial + blockIdx.y * col_stride + (int64_t)pd.wg0 * panel_rows + local;
+    const int64_t r = (int64_t)local * npanels + p;
+    int64_t to = r;
+    if (inv && t == 0 && live) to = inv[r];       // beside the partial sums, not after them
+    if constexpr (FEW) {
+        if (!live) return;
+        double a[MV_FEW];
+#pragma unroll
+        for (int i = 0; i < MV_FEW; ++i) a[i] = i < pd.nwg ? src[(int64_t)i * panel_rows] : 0.0;
+        y[to * ldy] = (VecT)(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
+        return;
+    }
     double s = 0.0;
     if (live) {
-        const double *src = partial + blockIdx.y * col_stride + (int64_t)pd.wg0 * panel_rows + local;
-        for (int w = t; w < pd.nwg; w += 8 * 16) {
-            double a[16];
+        auto add = [&](auto loads) __attribute__((always_inline)) {
+            constexpr int U = decltype(loads)::value;
+            for (int w = t; w < pd.nwg; w += 8 * U) {
+                double a[U];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) a[i] = w + 8 * i < pd.nwg ? src[(int64_t)(w + 8 * i) * panel_rows] : 0.0;
+                for (int i = 0; i < U; ++i) a[i] = w + 8 * i < pd.nwg ? src[(int64_t)(w + 8 * i) * panel_rows] : 0.0;
 #pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (w + 8 * i < pd.nwg) s += a[i];
-        }
+                for (int i = 0; i < U; ++i)
+                    if (w + 8 * i < pd.nwg) s += a[i];
+            }
+        };
+        if (pd.nwg <= 8 * 4) add(IntC<4>());
+        else add(IntC<16>());
     }
     sums[t][threadIdx.x & 31] = s;
     __syncthreads();
@@ -701,8 +728,7 @@ __global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ part
         const int l = threadIdx.x;
         const double y0 = (sums[0][l] + sums[1][l]) + (sums[2][l] + sums[3][l]);
         const double y1 = (sums[4][l] + sums[5][l]) + (sums[6][l] + sums[7][l]);
-        const int64_t r = (int64_t)local * npanels + p;
-        y[(int64_t)(inv ? inv[r] : r) * ldy] = (VecT)(y0 + y1);
+        y[to * ldy] = (VecT)(y0 + y1);
     }
 }
 
@@ -959,10 +985,14 @@ int launch_mv_reduce(const spw_matrix_s &A, const double *partial, int k, const 
                      hipStream_t stream)
 {
     ProfScope ps(stream, "mv_reduce");
+    auto run = [&](auto kernel, unsigned blocks, unsigned panel_blocks) {
+        return launch_kernel(kernel, dim3(blocks, (unsigned)k), dim3(256), 0, stream, last ? take_stop() : nullptr, partial,
+                             (int)A.panel_rows, (int)panel_blocks, A.d_panels, (int)A.n_panels,
+                             A.relabeled ? A.d_inv : nullptr, out, A.mv_wgs * A.panel_rows);
+    };
+    if (A.panel_wgs <= MV_FEW) return run(mv_reduce<VecT, true>, blocks_for(A.n_panels * A.panel_rows, 256), 0u);
     const unsigned panel_blocks = blocks_for(A.panel_rows, 32);
-    return launch_kernel(mv_reduce<VecT>, dim3((unsigned)(A.n_panels * panel_blocks), (unsigned)k), dim3(256), 0,
-                         stream, last ? take_stop() : nullptr, partial, (int)A.panel_rows, (int)panel_blocks,
-                         A.d_panels, (int)A.n_panels, A.relabeled ? A.d_inv : nullptr, out, A.mv_wgs * A.panel_rows);
+    return run(mv_reduce<VecT, false>, (unsigned)A.n_panels * panel_blocks, panel_blocks);
 }
 
 // Columns of one launch that share an LDS panel: as many as fit, at most MV_COLS.
