@@ -833,6 +833,25 @@ int64_t mv_read_cols(int64_t cols, const int64_t *ptr, spw_partition part, int64
     return 2 * widest * ranges > 5 * sum ? std::max(cols, widest * ranges) : cols;
 }
 
+// The expected squared rounding error of a row's sum of N nonzeros (random signs; in units
+// of N times one rounding's), for P panels over W ranges with `copies` sums a row and
+// range: each sum runs over n = N P / (W copies) nonzeros and adds n / 2, the eight chains of
+// mv_reduce add W copies / (16 P) (N / 16 at most) and their tree 3.  More panels make longer
+// sums, so that without copies a dense matrix loses (2-norm against 80-bit sums in the fewest
+// panels, in the rule's and in those with copies: 4,000 x 3,000 two thirds full 3.0e-16, 5.7e-16,
+// 2.2e-16; 2,000 x 30,000 with 548 a column 3.3e-16, 6.3e-16, 3.0e-16).  The copies cost what their partial sums
+// take (those matrices 20.4 -> 22.7 us, 39.9 -> 42.3; 50,000 x 50,000 with 100 a column 22.2 -> 24.4).
+// least: the fewest panels that the LDS takes, one workgroup a CU or two where it takes them,
+// one sum a row.
+struct MvError {
+    double N = 0, least = 0;
+    double of(int64_t P, int64_t W, int64_t copies) const
+    {
+        const double sums = std::max((double)W / (double)P, 1.0) * (double)copies;
+        return N / sums / 2 + std::min(sums, N) / 16 + 3;
+    }
+};
+
 // Row panels, wave row sets and blocks of the scatter product (see
 // spw_internal.h and the scatter kernel).  rowi holds the internal
 // (renumbered) rows.
@@ -858,6 +877,15 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     const int64_t P = (rows + R - 1) / R;
     A.panel_rows = R;
     A.n_panels = P;
+    MvError error;
+    {
+        error.N = (double)nnz / (double)std::max<int64_t>(rows, 1);
+        const int64_t few = panel_rows_opt > 0 ? P : std::max<int64_t>(1, (rows + limit - 1) / limit);
+        const int64_t tall = (rows + few - 1) / few;
+        error.least = error.of(few, device_cu_count(A.device), 1);
+        if (2 * (tall * 8 + 256) <= 160 * 1024)
+            error.least = std::min(error.least, error.of(few, 2 * device_cu_count(A.device), 1));
+    }
     // 1. With several panels, the nonzeros panel by panel, each panel's in column order:
     //    a counting sort over parts of the source, whatever the number of panels.
     struct Nz {
@@ -909,24 +937,7 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
         return order[(size_t)(panel_at[(size_t)q] + t)].j;
     };
 
-    // 2. Deal each panel's rows to the NB waves, heaviest first onto the lightest wave.
-    std::vector<uint8_t> wave_of((size_t)rows, 0);
-    {
-        const std::vector<int64_t> rc = count_rows(rows, nnz, rowi);
-        for (int64_t q = 0; q < P; ++q) {
-            std::vector<int32_t> rs;
-            for (int64_t r = q; r < rows; r += P) rs.push_back((int32_t)r);
-            std::stable_sort(rs.begin(), rs.end(), [&](int32_t a, int32_t b) { return rc[(size_t)a] > rc[(size_t)b]; });
-            std::vector<int64_t> load((size_t)NB, 0);
-            for (int32_t r : rs) {
-                const int64_t wv = std::min_element(load.begin(), load.end()) - load.begin();
-                wave_of[(size_t)r] = (uint8_t)wv;
-                load[(size_t)wv] += rc[(size_t)r];
-            }
-        }
-    }
-
-    // 3. Workgroups: contiguous runs of one panel's column-ordered nonzeros, one
+    // 2. Workgroups: contiguous runs of one panel's column-ordered nonzeros, one
     //    per CU in total.  Two per CU where the panels are small enough were no
     //    faster anywhere: they double the partial sums (1,000 x 1e5 with 1e6
     //    nonzeros 18.6 us at two, 13.3 us at one; 20,000 x 5e6 with 5e7 nonzeros
@@ -957,6 +968,80 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
         std::stable_sort(rem.begin(), rem.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
         for (size_t i = 0; i < rem.size() && used < target; ++i, ++used) pnw[(size_t)rem[i].second]++;
     }
+    // 3. Slots of the LDS panel: `copies` of every row's, and more of the rows with very many
+    //    nonzeros.  A nonzero goes to one of its row's slots by its column.
+    //    Copies: the fewest that keep the sums as exact as in the fewest panels (MvError), at
+    //    most 512 partial sums a row (their reduction takes longer than it gains from there on).
+    int64_t copies = 1;
+    const int64_t beside = std::max<int64_t>(1, std::min<int64_t>(4, limit / R));    // columns beside one another in the LDS
+    while (copies < 16 && 2 * copies * R * beside <= limit && 2 * copies * target <= 512 * P &&
+           error.of(P, target, copies) > 0.9 * error.least &&
+           error.of(P, target, 2 * copies) < 0.9 * error.of(P, target, copies))
+        copies *= 2;
+    //    More slots: a row with more than 64 nonzeros a slot and four times the average row's
+    //    has about one for every 64, or for as many more as the room beside the others
+    //    allows, 64 or 4,096 partial sums over the panel's ranges at most.  Its one running sum would be
+    //    the product's largest error and one wave's work: 30,011 x 2e6 with 12e6 nonzeros and
+    //    Zipf(0.8) rows, error in the 2-norm against 80-bit sums 6.6e-16 in two panels,
+    //    9.9e-16 in six and 2.8e-16 in six with these slots; with Zipf(2) rows 66 us of A x in
+    //    one panel, 73 in four and 48 in four with them.
+    const std::vector<int64_t> rc = count_rows(rows, nnz, rowi);
+    std::vector<uint32_t> spread((size_t)rows, 0);          // (first of them << 8) | their number
+    std::vector<HotRow> hot;
+    int64_t extra = 0;                                      // of any panel
+    {
+        const int64_t room = std::min(limit / beside - copies * R, std::max<int64_t>(R / 32, std::min<int64_t>(R, 32)));
+        for (int64_t q = 0; q < P && room > 0; ++q) {
+            const int64_t nw = pnw[(size_t)q] * copies;     // partial sums of a row
+            std::vector<int32_t> rs;
+            for (int64_t r = q; r < rows; r += P)
+                if (nw > 0 && rc[(size_t)r] > 64 * nw && rc[(size_t)r] > 4 * (nnz / rows)) rs.push_back((int32_t)r);
+            if (rs.empty()) continue;
+            std::stable_sort(rs.begin(), rs.end(), [&](int32_t x, int32_t y) { return rc[(size_t)x] > rc[(size_t)y]; });
+            auto more = [&](int32_t r, int64_t per) {
+                const int64_t c = std::min(std::min<int64_t>(64, std::max<int64_t>(4096 / pnw[(size_t)q], 2)),
+                                           copies * ((rc[(size_t)r] + per * nw - 1) / (per * nw)));
+                return std::max<int64_t>(c - copies, 0);
+            };
+            int64_t per = 64, n;
+            for (;; per *= 2) {
+                n = 0;
+                for (int32_t r : rs) n += more(r, per);
+                if (n <= room) break;
+            }
+            int64_t first = copies * R;
+            for (int32_t r : rs) {
+                const int64_t c = more(r, per);
+                if (c < 1) break;
+                spread[(size_t)r] = (uint32_t)(first << 8) | (uint32_t)c;
+                hot.push_back(HotRow{(int32_t)q, (int32_t)(r / P), (int32_t)first, (int32_t)c});
+                first += c;
+            }
+            extra = std::max(extra, n);
+        }
+    }
+    const int64_t V = copies * R + extra;
+    A.panel_slots = V;
+    A.row_copies = copies;
+    A.n_hot_rows = (int64_t)hot.size();
+    // Deal each panel's slots to the NB waves, heaviest first onto the lightest wave.
+    std::vector<uint8_t> wave_of((size_t)(P * V), 0);       // [panel * V + slot]
+    for (int64_t q = 0; q < P; ++q) {
+        std::vector<std::pair<int64_t, int32_t>> ss;        // nonzeros, slot
+        for (int64_t r = q; r < rows; r += P) {
+            const int64_t first = spread[(size_t)r] >> 8, c = copies + (spread[(size_t)r] & 0xFFu);
+            for (int64_t i = 0; i < c; ++i)
+                ss.push_back({rc[(size_t)r] / c, (int32_t)(i < copies ? i * R + r / P : first + i - copies)});
+        }
+        std::stable_sort(ss.begin(), ss.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+        std::vector<int64_t> load((size_t)NB, 0);
+        for (const auto &t : ss) {
+            const int64_t wv = std::min_element(load.begin(), load.end()) - load.begin();
+            wave_of[(size_t)(q * V + t.second)] = (uint8_t)wv;
+            load[(size_t)wv] += t.first;
+        }
+    }
+
     for (int64_t q = 0; q < P; ++q) {
         const int64_t qn = panel_nnz(q);
         PanelDesc pd;
@@ -1019,15 +1104,23 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
             for (int64_t b = x; b < W; b += 8) wg_order[(size_t)b] = seq[next++];
     }
 
-    // 4. Blocks per (workgroup, wave): nonzeros of that wave's rows in column
+    // 4. Blocks per (workgroup, wave): nonzeros of that wave's slots in column
     //    order, at most BLK per block and spanning fewer than SPAN columns.  One
     //    walk over every range counts its blocks, a second one fills them.
     if (BLK > 1024 || BLK % 256) return fail(SPW_ERR_UNSUPPORTED, "scatter block size mismatch");
     if (NB > 8) return fail(SPW_ERR_UNSUPPORTED, "scatter wave count mismatch");
-    std::vector<uint32_t> local_of((size_t)rows);           // panel-local row, as the words hold it
-    for (int64_t r = 0; r < rows; ++r) local_of[(size_t)r] = (uint32_t)(r / P) << 16;
-    // Calls open(wave, column) when a block of that wave begins and put(wave, column
-    // offset, position) for every nonzero of range w.
+    std::vector<uint32_t> local_of((size_t)rows);           // panel-local row; bit 31: has more slots
+    for (int64_t r = 0; r < rows; ++r) local_of[(size_t)r] = (uint32_t)(r / P) | (spread[(size_t)r] ? 1u << 31 : 0u);
+    // the slot of row r's nonzero in column j (a multiplicative hash of the column)
+    auto slot_of = [&](int32_t r, int64_t j) -> uint32_t {
+        const uint32_t l = local_of[(size_t)r], h = ((uint32_t)j * 2654435769u) >> 16;
+        if (!(l >> 31)) return copies == 1 ? l : (h * (uint32_t)copies >> 16) * (uint32_t)R + l;
+        const uint32_t more = spread[(size_t)r] & 0xFFu, first = spread[(size_t)r] >> 8;
+        const uint32_t i = h * ((uint32_t)copies + more) >> 16;
+        return i < copies ? i * (uint32_t)R + (l & ~(1u << 31)) : first + i - (uint32_t)copies;
+    };
+    // Calls open(wave, column) when a block of that wave begins and put(wave, slot,
+    // column offset, position) for every nonzero of range w.
     auto walk = [&](int64_t w, auto &&open, auto &&put) {
         const WgRange &g = wr[(size_t)w];
         int64_t base[8], count[8];
@@ -1036,6 +1129,7 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
             count[v] = BLK;                                 // no block yet
         }
         const Nz *nz = P > 1 ? order.get() + panel_at[(size_t)g.panel] : nullptr;
+        const uint8_t *waves = &wave_of[(size_t)(g.panel * V)];
         int64_t j = g.col;
         for (int64_t t = g.a; t < g.b; ++t) {
             int64_t p = t;
@@ -1045,19 +1139,20 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
             } else {
                 while (ptr[j + 1] <= p) ++j;
             }
-            const int v = wave_of[(size_t)rowi[p]];
+            const uint32_t slot = slot_of(rowi[p], j);
+            const int v = waves[slot];
             if (count[v] == BLK || j - base[v] >= SPAN) {
                 base[v] = j;
                 count[v] = 0;
                 open(v, j);
             }
             ++count[v];
-            put(v, j - base[v], p);
+            put(v, slot, j - base[v], p);
         }
     };
     std::vector<int32_t> wg_blk((size_t)(W * (NB + 1)), 0);
     parallel_ranges(W, [&](int64_t w) {
-        walk(w, [&](int v, int64_t) { ++wg_blk[(size_t)(w * (NB + 1) + v + 1)]; }, [](int, int64_t, int64_t) {});
+        walk(w, [&](int v, int64_t) { ++wg_blk[(size_t)(w * (NB + 1) + v + 1)]; }, [](int, uint32_t, int64_t, int64_t) {});
     });
     int64_t nblk = 0;
     for (int64_t w = 0; w < W; ++w) {
@@ -1091,12 +1186,12 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
                 std::memset(packed.get() + id[v] * BLK, 0, (size_t)BLK * sizeof(uint32_t));
                 std::memset(mval.get() + id[v] * BLK * es, 0, (size_t)(BLK * es));
             },
-            [&](int v, int64_t off, int64_t p) {
+            [&](int v, uint32_t slot, int64_t off, int64_t p) {
                 // logical nonzero l = jj*64 + ln goes to the interleaved slots the kernel reads
                 const int32_t l = count[v]++;
                 const int32_t jj = l / 64, ln = l % 64;
                 const int64_t at = id[v] * BLK;
-                packed[(size_t)(at + ((jj / 4) * 64 + ln) * 4 + jj % 4)] = local_of[(size_t)rowi[p]] | (uint32_t)off;
+                packed[(size_t)(at + ((jj / 4) * 64 + ln) * 4 + jj % 4)] = slot << 16 | (uint32_t)off;
                 put_value(storage, mval.get(), at + ((jj / GV) * 64 + ln) * GV + jj % GV, val[p]);
                 bdesc[(size_t)(2 * id[v] + 1)] = count[v];
             });
@@ -1120,6 +1215,16 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     if ((st = h2d(A.d_wg_order, wg_order.data(), wg_order.size() * 4, "workgroup order"))) return st;
     if ((st = dev_alloc(A, &A.d_panels, P, "panels"))) return st;
     if ((st = h2d(A.d_panels, A.panels.data(), A.panels.size() * sizeof(PanelDesc), "panels"))) return st;
+    if (!hot.empty()) {
+        // one bit a row: summed by a workgroup of its own
+        const int64_t words = (R + 31) / 32;
+        std::vector<uint32_t> mask((size_t)(P * words), 0);
+        for (const HotRow &h : hot) mask[(size_t)(h.panel * words + h.local / 32)] |= 1u << (h.local % 32);
+        if ((st = dev_alloc(A, &A.d_hot, (int64_t)hot.size(), "rows of several slots"))) return st;
+        if ((st = h2d(A.d_hot, hot.data(), hot.size() * sizeof(HotRow), "rows of several slots"))) return st;
+        if ((st = dev_alloc(A, &A.d_hot_mask, (int64_t)mask.size(), "rows of several slots"))) return st;
+        if ((st = h2d(A.d_hot_mask, mask.data(), mask.size() * 4, "rows of several slots"))) return st;
+    }
     return SPW_OK;
 }
 
@@ -1137,7 +1242,7 @@ spw_status grow_scratch(spw_matrix_s &A, int32_t k)
     spw_status st;
     if (!A.scratch.partial) {
         // partial sums of the scatter product: one column at a time
-        if ((st = dev_alloc(A, &A.scratch.partial, std::max<int64_t>(A.mv_wgs, 1) * A.panel_rows, "partial sums")))
+        if ((st = dev_alloc(A, &A.scratch.partial, std::max<int64_t>(A.mv_wgs, 1) * A.panel_slots, "partial sums")))
             return st;
     }
     const int64_t nch = std::max<int64_t>(A.cd.zp.n_chunks, A.cdt.zp.n_chunks);
@@ -1347,7 +1452,7 @@ spw_status grow_partial_cols(spw_matrix_s &A, int32_t cols)
         A.scratch.pcols = 0;
     }
     spw_status st;
-    if ((st = dev_alloc(A, &A.scratch.partial_cols, (int64_t)cols * A.mv_wgs * A.panel_rows, "multi-column partial sums")))
+    if ((st = dev_alloc(A, &A.scratch.partial_cols, (int64_t)cols * A.mv_wgs * A.panel_slots, "multi-column partial sums")))
         return st;
     A.scratch.pcols = cols;
     return SPW_OK;

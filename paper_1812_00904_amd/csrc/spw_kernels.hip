@@ -225,14 +225,14 @@ __global__ void gather_vec(const int32_t *__restrict__ inv, int64_t len, const V
 // slot ((j/2)*64 + lane)*2 + j%2, so every load instruction reads one
 // contiguous span while each add instruction covers 64 consecutive nonzeros
 // (whose x entries share a few cache lines).  A word is
-// (panel-local row << 16 | column - block column base).  The streams are read
+// (panel slot << 16 | column - block column base).  The streams are read
 // with non-temporal loads so they do not push x out of the caches.
 //   blocks : (column base, count) per block
 //   wg_blk : per workgroup, NW+1 offsets into blocks: wave w owns [wg_blk[w], wg_blk[w+1])
 //   x      : input, entry j at x[j*ldx]
-//   partial: per-workgroup partial sums, panel_rows entries each
+//   partial: per-workgroup partial sums, one per slot
 // The loop keeps two blocks of words/values and one block of x gathers in
-// flight.  Dynamic LDS: panel_rows doubles.
+// flight.  Dynamic LDS: one double per slot.
 // ------------------------------------------------------------------------
 constexpr int MV_ITEMS = 16;
 constexpr int MV_BLK = WAVE * MV_ITEMS;
@@ -261,16 +261,16 @@ __device__ __forceinline__ void mv_load(MvBlk<ValT> &B, const uint32_t *__restri
 }
 
 // One workgroup range of the scatter product into the LDS panel ypan, written
-// to out (panel_rows doubles).
+// to out (one double per slot).
 template <int BLOCK, typename ValT, typename VecT, bool NT>
 __device__ __forceinline__ void mv_range(const uint32_t *__restrict__ packed, const ValT *__restrict__ val,
                                          const int2 *__restrict__ blocks, const int32_t *__restrict__ wg_blk,
                                          int range, const VecT *__restrict__ x, int64_t ldx,
-                                         double *__restrict__ out, int panel_rows, double *ypan)
+                                         double *__restrict__ out, int slots, double *ypan)
 {
     constexpr int NW = BLOCK / WAVE;
     const int tid = threadIdx.x, wave = tid / WAVE, lane = tid & (WAVE - 1);
-    for (int i = tid; i < panel_rows; i += BLOCK) ypan[i] = 0.0;
+    for (int i = tid; i < slots; i += BLOCK) ypan[i] = 0.0;
     __syncthreads();
 
     const int32_t *wb = wg_blk + (int64_t)range * (NW + 1);
@@ -352,19 +352,19 @@ __device__ __forceinline__ void mv_range(const uint32_t *__restrict__ packed, co
         }
     }
     __syncthreads();
-    for (int i = tid; i < panel_rows; i += BLOCK) out[i] = ypan[i];
+    for (int i = tid; i < slots; i += BLOCK) out[i] = ypan[i];
 }
 
 template <int BLOCK, typename ValT, typename VecT>
 __global__ __launch_bounds__(BLOCK) void mv_bucket(
     const uint32_t *__restrict__ packed, const ValT *__restrict__ val, const int2 *__restrict__ blocks,
     const int32_t *__restrict__ wg_blk, const int32_t *__restrict__ wg_order, const VecT *__restrict__ x, int64_t ldx,
-    double *__restrict__ partial, int panel_rows)
+    double *__restrict__ partial, int slots)
 {
     extern __shared__ double ypan[];
     const int range = wg_order[blockIdx.x];
     mv_range<BLOCK, ValT, VecT, true>(packed, val, blocks, wg_blk, range, x, ldx,
-                                      partial + (int64_t)range * panel_rows, panel_rows, ypan);
+                                      partial + (int64_t)range * slots, slots, ypan);
 }
 
 // ------------------------------------------------------------------------
@@ -493,11 +493,11 @@ template <int BLOCK, typename ValT, typename VecT, int KC, bool WIDE>
 __device__ __forceinline__ void mv_range_cols(const uint32_t *__restrict__ packed, const ValT *__restrict__ val,
                                               const int2 *__restrict__ blocks, const int32_t *__restrict__ wb,
                                               const VecT *__restrict__ x, int64_t ldx, double *__restrict__ out,
-                                              int64_t col_stride, int panel_rows, double *ypan)
+                                              int64_t col_stride, int slots, double *ypan)
 {
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
-    for (int i = tid; i < KC * panel_rows; i += BLOCK) ypan[i] = 0.0;
+    for (int i = tid; i < KC * slots; i += BLOCK) ypan[i] = 0.0;
     __syncthreads();
     const int b0 = __builtin_amdgcn_readfirstlane(wb[wave]), b1 = __builtin_amdgcn_readfirstlane(wb[wave + 1]);
     const uint32_t ld_bytes = (uint32_t)(ldx * (int64_t)sizeof(VecT));
@@ -546,7 +546,7 @@ __device__ __forceinline__ void mv_range_cols(const uint32_t *__restrict__ packe
             if (cnt == MV_BLK || (4 * s + j) * WAVE < lim) {
 #pragma unroll
                 for (int c = 0; c < KC; ++c)
-                    __hip_atomic_fetch_add(&ypan[c * panel_rows + row[j]], p[j][c], __ATOMIC_RELAXED,
+                    __hip_atomic_fetch_add(&ypan[c * slots + row[j]], p[j][c], __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
             }
         }
@@ -604,7 +604,7 @@ __device__ __forceinline__ void mv_range_cols(const uint32_t *__restrict__ packe
     }
     __syncthreads();
     for (int c = 0; c < KC; ++c)
-        for (int i = tid; i < panel_rows; i += BLOCK) out[c * col_stride + i] = ypan[c * panel_rows + i];
+        for (int i = tid; i < slots; i += BLOCK) out[c * col_stride + i] = ypan[c * slots + i];
 }
 
 // Groups of columns in one launch: workgroup (group, range).  The groups of one
@@ -613,12 +613,12 @@ __device__ __forceinline__ void mv_range_cols(const uint32_t *__restrict__ packe
 // so they share the blocks and the lines of X through its L2 (ordinary loads: the lines
 // stay for the others).  The tables are picked by a chain of selects on the group,
 // so they stay in kernel arguments.  Column c of the launch keeps its partial
-// sums in slot c (W ranges of panel_rows each).
+// sums in slot c (W ranges of one double per slot each).
 template <int BLOCK, typename ValT, typename VecT>
 __global__ __launch_bounds__(BLOCK) void mv_bucket_cols(
     const uint32_t *__restrict__ packed, const ValT *__restrict__ val, const int2 *__restrict__ blocks,
     const int32_t *__restrict__ wg_blk, const int32_t *__restrict__ wg_order, MvGroups<VecT> groups, int ngroups,
-    double *__restrict__ partial, int panel_rows, int W)
+    double *__restrict__ partial, int slots, int W)
 {
     constexpr int NW = BLOCK / WAVE;
     extern __shared__ double ypan[];
@@ -636,12 +636,12 @@ __global__ __launch_bounds__(BLOCK) void mv_bucket_cols(
         kc = g == t ? groups.kc[t] : kc;
         slot = g == t ? groups.slot[t] : slot;
     }
-    const int64_t col_stride = (int64_t)W * panel_rows;
-    double *out = partial + slot * col_stride + (int64_t)range * panel_rows;
+    const int64_t col_stride = (int64_t)W * slots;
+    double *out = partial + slot * col_stride + (int64_t)range * slots;
     const int32_t *wb = wg_blk + (int64_t)range * (NW + 1);
     auto run = [&](auto cols, auto wide) {
         mv_range_cols<BLOCK, ValT, VecT, decltype(cols)::value, decltype(wide)::value>(
-            packed, val, blocks, wb, x, ld, out, col_stride, panel_rows, ypan);
+            packed, val, blocks, wb, x, ld, out, col_stride, slots, ypan);
     };
     // a block spans fewer than 65,536 columns: 32-bit byte offsets below this stride
     if (ld * (int64_t)sizeof(VecT) < 65536) {
@@ -657,22 +657,26 @@ __global__ __launch_bounds__(BLOCK) void mv_bucket_cols(
     }
 }
 
-// y[caller row] = sum over the panel's workgroups of their partials.  Internal
-// row r belongs to panel r mod npanels, at panel-local row r / npanels; a
+// y[caller row] = sum over the panel's workgroups of their partials, 2^cs of each (the row's
+// copies).  Internal row r belongs to panel r mod npanels, at panel-local row r / npanels; a
 // workgroup takes 32 consecutive rows of one panel, eight threads a row: thread t
-// adds workgroups t, t+8, t+16, ... in ascending order with up to sixteen loads in
+// adds partials t, t+8, t+16, ... in ascending order with up to sixteen loads in
 // flight (a chain of dependent trips to memory bounds this kernel, not its
 // bytes), then the eight sums are combined pairwise, so the order of every
-// addition is fixed.  FEW: panels of at most eight workgroups, where one thread takes a
+// addition is fixed.  FEW: at most eight partials a row, where one thread takes a
 // whole row, in the same order, and the panels are one sequence of rows, so that small
 // ones fill a workgroup too (2e6 x 2e6 in 98 panels of two or three workgroups: 83 us with
-// eight threads a row, five of them idle, now 43; 500,000 rows in 49 panels 32 and 17).  Column blockIdx.y: its partials start col_stride doubles
+// eight threads a row, five of them idle, now 43; 500,000 rows in 49 panels 32 and 17).  Hot rows (hot_mask's bits) are left to workgroups of
+// their own, before the others: thread t adds partial sums t, t+256, ... of all of the
+// row's slots, and the 256 sums are combined in a fixed tree.  Column blockIdx.y: its partials start col_stride doubles
 // further, its output is out.u[column].
 constexpr int MV_FEW = 8;
 template <typename VecT, bool FEW>
-__global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ partial, int panel_rows, int panel_blocks,
-                                                 const PanelDesc *__restrict__ panels, int npanels,
-                                                 const int32_t *__restrict__ inv, ColOut<VecT> out, int64_t col_stride)
+__global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ partial, int slots, int cs, int panel_rows,
+                                                 int panel_blocks, const PanelDesc *__restrict__ panels, int npanels,
+                                                 const HotRow *__restrict__ hot, int nhot,
+                                                 const uint32_t *__restrict__ hot_mask, const int32_t *__restrict__ inv,
+                                                 ColOut<VecT> out, int64_t col_stride)
 {
     __shared__ double sums[8][32];
     VecT *y = out.u[0];
@@ -682,19 +686,50 @@ __global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ part
         y = blockIdx.y == c ? out.u[c] : y;
         ldy = blockIdx.y == c ? out.ld[c] : ldy;
     }
+    if ((int)blockIdx.x < nhot) {
+        const HotRow h = hot[blockIdx.x];
+        const PanelDesc pd = panels[h.panel];
+        const double *src = partial + blockIdx.y * col_stride + (int64_t)pd.wg0 * slots;
+        const int each = (1 << cs) + h.more, n = pd.nwg * each;
+        double s = 0.0;
+        for (int w = threadIdx.x; w < n; w += 256 * 8) {
+            double a[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int at = min(w + 256 * i, n - 1), wg = at / each, c = at - wg * each;
+                a[i] = src[(int64_t)wg * slots + (c < (1 << cs) ? c * panel_rows + h.local : h.first + c - (1 << cs))];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (w + 256 * i < n) s += a[i];
+        }
+#pragma unroll
+        for (int off = 1; off < WAVE; off <<= 1) s += __shfl_xor(s, off, WAVE);
+        if (threadIdx.x % WAVE == 0) sums[0][threadIdx.x / WAVE] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const int64_t r = (int64_t)h.local * npanels + h.panel;
+            y[(int64_t)(inv ? inv[r] : r) * ldy] = (VecT)((sums[0][0] + sums[0][1]) + (sums[0][2] + sums[0][3]));
+        }
+        return;
+    }
+    const int block = (int)blockIdx.x - nhot;
     int p, local, t = 0;
     if constexpr (FEW) {
-        const uint32_t g = blockIdx.x * 256u + threadIdx.x;
+        const uint32_t g = (uint32_t)block * 256u + threadIdx.x;
         p = (int)min(g / (uint32_t)panel_rows, (uint32_t)npanels - 1u);
         local = (int)(g - (uint32_t)p * (uint32_t)panel_rows);
     } else {
-        p = blockIdx.x / panel_blocks;
-        local = (blockIdx.x - p * panel_blocks) * 32 + (threadIdx.x & 31);
+        p = block / panel_blocks;
+        local = (block - p * panel_blocks) * 32 + (threadIdx.x & 31);
         t = threadIdx.x >> 5;
     }
     const PanelDesc pd = panels[p];
-    const bool live = local < pd.rows;
-    const double *src = partial + blockIdx.y * col_stride + (int64_t)pd.wg0 * panel_rows + local;
+    bool live = local < pd.rows;
+    if (hot_mask && live) live = !((hot_mask[p * ((panel_rows + 31) / 32) + local / 32] >> (local % 32)) & 1u);
+    const double *base = partial + blockIdx.y * col_stride + (int64_t)pd.wg0 * slots + local;
+    const int n = pd.nwg << cs;                    // partials of a row
+    auto src = [&](int i) { return base[(int64_t)(i >> cs) * slots + (i & ((1 << cs) - 1)) * panel_rows]; };
     const int64_t r = (int64_t)local * npanels + p;
     int64_t to = r;
     if (inv && t == 0 && live) to = inv[r];       // beside the partial sums, not after them
@@ -702,7 +737,7 @@ __global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ part
         if (!live) return;
         double a[MV_FEW];
 #pragma unroll
-        for (int i = 0; i < MV_FEW; ++i) a[i] = i < pd.nwg ? src[(int64_t)i * panel_rows] : 0.0;
+        for (int i = 0; i < MV_FEW; ++i) a[i] = i < n ? src(i) : 0.0;
         y[to * ldy] = (VecT)(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
         return;
     }
@@ -710,16 +745,16 @@ __global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ part
     if (live) {
         auto add = [&](auto loads) __attribute__((always_inline)) {
             constexpr int U = decltype(loads)::value;
-            for (int w = t; w < pd.nwg; w += 8 * U) {
+            for (int w = t; w < n; w += 8 * U) {
                 double a[U];
 #pragma unroll
-                for (int i = 0; i < U; ++i) a[i] = w + 8 * i < pd.nwg ? src[(int64_t)(w + 8 * i) * panel_rows] : 0.0;
+                for (int i = 0; i < U; ++i) a[i] = w + 8 * i < n ? src(w + 8 * i) : 0.0;
 #pragma unroll
                 for (int i = 0; i < U; ++i)
-                    if (w + 8 * i < pd.nwg) s += a[i];
+                    if (w + 8 * i < n) s += a[i];
             }
         };
-        if (pd.nwg <= 8 * 4) add(IntC<4>());
+        if (n <= 8 * 4) add(IntC<4>());
         else add(IntC<16>());
     }
     sums[t][threadIdx.x & 31] = s;
@@ -985,12 +1020,16 @@ int launch_mv_reduce(const spw_matrix_s &A, const double *partial, int k, const 
                      hipStream_t stream)
 {
     ProfScope ps(stream, "mv_reduce");
+    int cs = 0;
+    while ((1 << cs) < A.row_copies) ++cs;
     auto run = [&](auto kernel, unsigned blocks, unsigned panel_blocks) {
-        return launch_kernel(kernel, dim3(blocks, (unsigned)k), dim3(256), 0, stream, last ? take_stop() : nullptr, partial,
-                             (int)A.panel_rows, (int)panel_blocks, A.d_panels, (int)A.n_panels,
-                             A.relabeled ? A.d_inv : nullptr, out, A.mv_wgs * A.panel_rows);
+        return launch_kernel(kernel, dim3(blocks + (unsigned)A.n_hot_rows, (unsigned)k), dim3(256), 0, stream,
+                             last ? take_stop() : nullptr, partial, (int)A.panel_slots, cs, (int)A.panel_rows,
+                             (int)panel_blocks, A.d_panels, (int)A.n_panels, A.d_hot, (int)A.n_hot_rows, A.d_hot_mask,
+                             A.relabeled ? A.d_inv : nullptr, out, A.mv_wgs * A.panel_slots);
     };
-    if (A.panel_wgs <= MV_FEW) return run(mv_reduce<VecT, true>, blocks_for(A.n_panels * A.panel_rows, 256), 0u);
+    if (A.panel_wgs * A.row_copies <= MV_FEW)
+        return run(mv_reduce<VecT, true>, blocks_for(A.n_panels * A.panel_rows, 256), 0u);
     const unsigned panel_blocks = blocks_for(A.panel_rows, 32);
     return run(mv_reduce<VecT, false>, (unsigned)A.n_panels * panel_blocks, panel_blocks);
 }
@@ -998,7 +1037,7 @@ int launch_mv_reduce(const spw_matrix_s &A, const double *partial, int k, const 
 // Columns of one launch that share an LDS panel: as many as fit, at most MV_COLS.
 int mv_cols_together(const spw_matrix_s &A)
 {
-    return (int)std::max<int64_t>(1, std::min<int64_t>(MV_COLS, mv_lds_rows_limit(SPW_F64, 1) / A.panel_rows));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(MV_COLS, mv_lds_rows_limit(SPW_F64, 1) / A.panel_slots));
 }
 
 // One launch of the scatter kernel for k <= MULTI_MAX columns with their own
@@ -1033,9 +1072,9 @@ int mv_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const Col
         }
         ProfScope ps(stream, "mv_bucket");
         hipLaunchKernelGGL((mv_bucket_cols<MV_BLOCK, ValT, VecT>), dim3((unsigned)(8 * ng * ((W + 7) / 8))),
-                           dim3(MV_BLOCK), (size_t)A.panel_rows * 8 * (size_t)widest, stream,
+                           dim3(MV_BLOCK), (size_t)A.panel_slots * 8 * (size_t)widest, stream,
                            (const uint32_t *)A.d_mpacked, (const ValT *)A.d_mval, (const int2 *)A.d_mblocks,
-                           A.d_wg_blk, A.d_wg_order, gr, ng, A.scratch.partial_cols, (int)A.panel_rows, W);
+                           A.d_wg_blk, A.d_wg_order, gr, ng, A.scratch.partial_cols, (int)A.panel_slots, W);
         if ((e = (int)hipGetLastError())) return e;
     }
     return launch_mv_reduce<VecT>(A, A.scratch.partial_cols, k, out, last, stream);
@@ -1069,11 +1108,11 @@ int mv_typed(const spw_matrix_s &A, int32_t k, const VecT *x, int64_t ldx, VecT 
     for (int32_t c = 0; c < k; ++c) {
         if (A.mv_wgs > 0) {
             ProfScope ps(stream, "mv_bucket");
-            const size_t lds = (size_t)A.panel_rows * 8;
+            const size_t lds = (size_t)A.panel_slots * 8;
             hipLaunchKernelGGL((mv_bucket<MV_BLOCK, ValT, VecT>), dim3((unsigned)A.mv_wgs), dim3(MV_BLOCK), lds,
                                stream, (const uint32_t *)A.d_mpacked, (const ValT *)A.d_mval,
                                (const int2 *)A.d_mblocks, A.d_wg_blk, A.d_wg_order, x + c, ldx, A.scratch.partial,
-                               (int)A.panel_rows);
+                               (int)A.panel_slots);
             if ((e = (int)hipGetLastError())) return e;
         }
         ColOut<VecT> out{};
