@@ -252,9 +252,12 @@ void free_one(spw_matrix_s &A, void *p)
 // Frees the device arrays of a column-dot storage and resets it.
 void free_coldot(spw_matrix_s &A, ColDot &C)
 {
-    for (void *p : {C.d_idx, C.d_val, (void *)C.d_empty, (void *)C.d_empty_of[1], (void *)C.d_zone_col, (void *)C.d_zone_first,
-                    (void *)C.d_zone_last, (void *)C.d_wchunks, (void *)C.d_heads, (void *)C.d_cinfo,
-                    (void *)C.d_segcol})
+    // lists of empty columns may be one another
+    if (C.d_empty_of[2] == C.d_empty_of[1] || C.d_empty_of[2] == C.d_empty) C.d_empty_of[2] = nullptr;
+    if (C.d_empty_of[1] == C.d_empty) C.d_empty_of[1] = nullptr;
+    for (void *p : {C.d_idx, C.d_val, (void *)C.d_empty, (void *)C.d_empty_of[1], (void *)C.d_empty_of[2],
+                    (void *)C.d_zone_col, (void *)C.d_zone_first, (void *)C.d_zone_last, (void *)C.d_wchunks,
+                    (void *)C.d_heads, (void *)C.d_cinfo, (void *)C.d_segcol})
         free_one(A, p);
     C = ColDot();
 }
@@ -593,6 +596,16 @@ spw_status build_coldot(spw_matrix_s &A, ColDot &C, int64_t rows, int64_t cols, 
     build_zone_plan(cols, ptr, WCH, C.zp);
     C.n_zones = (int64_t)C.zp.zone_col.size();
     {
+        std::vector<int32_t> empty;
+        for (int64_t j = 0; j < cols; ++j)
+            if (ptr[j + 1] == ptr[j]) empty.push_back((int32_t)j);
+        C.n_empty = (int64_t)empty.size();
+        if ((st = dev_alloc(A, &C.d_empty, std::max<int64_t>(C.n_empty, 1), "empty columns"))) return st;
+        if ((st = h2d(C.d_empty, empty.data(), empty.size() * 4, "empty columns"))) return st;
+        C.d_empty_of[0] = C.d_empty;
+        C.n_empty_of[0] = C.n_empty;
+    }
+    {
         // Column-start bits (bit i of lane l of chunk c: position c*W + l*I + i
         // is the first nonzero of its column) and per-chunk descriptions: the
         // column of the first position, the chunk's runs ("segments") of
@@ -630,26 +643,45 @@ spw_status build_coldot(spw_matrix_s &A, ColDot &C, int64_t rows, int64_t cols, 
         // the first column, in long gaps, and after segments of chunks that are not staged
         // or have no empty column inside.
         {
-            const int64_t cap = vtm_stage_cap(WCH);
-            int64_t filled = 0;
+            int64_t filled = 0, many = 0, full = 0, holed = 0;
             for (int64_t j = 0; j < cols; ++j) filled += ptr[j] < ptr[j + 1];
-            C.gap_max = cols - filled <= GAP_SHARE * filled ? GAP_MAX : 0;
-            std::vector<int32_t> far;
-            auto add = [&](int64_t a, int64_t b) {
-                for (int64_t j = a; j < b; ++j) far.push_back((int32_t)j);
-            };
-            if (nch > 0) add(0, segcol[0]);
             for (int64_t c = 0; c < nch; ++c) {
-                const int32_t *ci = &cinfo[(size_t)(4 * c)];
-                const bool staged = (c + 1) * WCH <= nnz && ci[2] <= cap && !(ci[3] & 4);
-                for (int64_t t = 0; t < ci[2]; ++t) {
-                    const int64_t j = segcol[(size_t)(ci[1] + t)], nx = segcol[(size_t)(ci[1] + t + 1)];
-                    if (!staged || nx - j - 1 > C.gap_max) add(j + 1, nx);
-                }
+                many += cinfo[(size_t)(4 * c + 2)] > 256;
+                full += (c + 1) * WCH <= nnz;
+                holed += (c + 1) * WCH <= nnz && !(cinfo[(size_t)(4 * c + 3)] & 4);
             }
-            C.n_empty_of[1] = (int64_t)far.size();
-            if ((st = dev_alloc(A, &C.d_empty_of[1], std::max<int64_t>(C.n_empty_of[1], 1), "empty columns"))) return st;
-            if ((st = h2d(C.d_empty_of[1], far.data(), far.size() * 4, "empty columns"))) return st;
+            C.gap_max = cols - filled <= GAP_SHARE * filled ? GAP_MAX : 0;
+            C.stage64 = WCH == 512 && 8 * many > nch ? 512 : 256;
+            C.gaps = 2 * holed >= full && holed > 0;
+            for (int set = 1; set <= (WCH == 512 ? 2 : 1); ++set) {
+                const int64_t cap = set == 1 ? C.stage64 : 512;
+                if (set == 2 && cap == C.stage64) {
+                    C.d_empty_of[2] = C.d_empty_of[1];
+                    C.n_empty_of[2] = C.n_empty_of[1];
+                    break;
+                }
+                std::vector<int32_t> far;
+                auto add = [&](int64_t a, int64_t b) {
+                    for (int64_t j = a; j < b; ++j) far.push_back((int32_t)j);
+                };
+                if (nch > 0) add(0, segcol[0]);
+                for (int64_t c = 0; c < nch; ++c) {
+                    const int32_t *ci = &cinfo[(size_t)(4 * c)];
+                    const bool staged = (c + 1) * WCH <= nnz && ci[2] <= cap && !(ci[3] & 4);
+                    for (int64_t t = 0; t < ci[2]; ++t) {
+                        const int64_t j = segcol[(size_t)(ci[1] + t)], nx = segcol[(size_t)(ci[1] + t + 1)];
+                        if (!staged || nx - j - 1 > C.gap_max) add(j + 1, nx);
+                    }
+                }
+                C.n_empty_of[set] = (int64_t)far.size();
+                if (C.n_empty_of[set] == C.n_empty) {       // all of them
+                    C.d_empty_of[set] = C.d_empty;
+                    continue;
+                }
+                if ((st = dev_alloc(A, &C.d_empty_of[set], std::max<int64_t>(C.n_empty_of[set], 1), "empty columns")))
+                    return st;
+                if ((st = h2d(C.d_empty_of[set], far.data(), far.size() * 4, "empty columns"))) return st;
+            }
         }
         if (segcol.size() >= ((size_t)1 << 31)) return fail(SPW_ERR_UNSUPPORTED, "segment table exceeds 2^31 entries");
         if ((st = dev_alloc(A, &C.d_heads, (int64_t)heads.size(), "column-start bits"))) return st;
@@ -659,16 +691,6 @@ spw_status build_coldot(spw_matrix_s &A, ColDot &C, int64_t rows, int64_t cols, 
         if ((st = dev_alloc(A, &C.d_segcol, std::max<int64_t>((int64_t)segcol.size(), 1), "segment columns")))
             return st;
         if ((st = h2d(C.d_segcol, segcol.data(), segcol.size() * 4, "segment columns"))) return st;
-    }
-    {
-        std::vector<int32_t> empty;
-        for (int64_t j = 0; j < cols; ++j)
-            if (ptr[j + 1] == ptr[j]) empty.push_back((int32_t)j);
-        C.n_empty = (int64_t)empty.size();
-        if ((st = dev_alloc(A, &C.d_empty, std::max<int64_t>(C.n_empty, 1), "empty columns"))) return st;
-        if ((st = h2d(C.d_empty, empty.data(), empty.size() * 4, "empty columns"))) return st;
-        C.d_empty_of[0] = C.d_empty;
-        C.n_empty_of[0] = C.n_empty;
     }
     if ((st = dev_alloc(A, &C.d_zone_col, std::max<int64_t>(C.n_zones, 1), "zone table"))) return st;
     if ((st = dev_alloc(A, &C.d_zone_first, std::max<int64_t>(C.n_zones, 1), "zone table"))) return st;

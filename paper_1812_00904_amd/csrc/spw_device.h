@@ -344,21 +344,11 @@ __device__ __forceinline__ void buf_store_nt(double x, __amdgpu_buffer_rsrc_t r,
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(spw_u32x2, x), r, (int)off, 0, 2);
 }
 
-// Segments of one chunk a wave stages in LDS before writing them out; chunks
-// with more segments take the general path.  Chunks of 512 stage all they can hold
-// (that size is taken for short columns); chunks of 1,024 stage 256 for binary64
-// vectors, and none for binary32 ones, whose LDS is worth more as hot rows of v.
-template <int ITEMS, typename VecT> constexpr int stage_cap()
-{
-    return ITEMS == 8 ? 512 : sizeof(VecT) == 8 ? 256 : 0;
-}
-// ... plus one spare slot per lane
-template <int ITEMS, typename VecT> constexpr int stage_stride()
-{
-    return stage_cap<ITEMS, VecT>() ? stage_cap<ITEMS, VecT>() + 64 : 0;
-}
+// A wave's LDS for the segments of one chunk (CAP at most; chunks with more take the general
+// path) before they are written out, plus one spare slot per lane.  CAP 0: no stage.
+constexpr int stage_stride(int cap) { return cap ? cap + WAVE : 0; }
 
-// Reduces one full chunk (all 64*ITEMS positions are nonzeros) with at most stage_cap
+// Reduces one full chunk (all 64*ITEMS positions are nonzeros) with at most CAP
 // segments.  Same additions in the same order as
 // vtm_reduce_chunk, with the per-position branches replaced by selects.  Every
 // segment's sum goes to this wave's LDS stage at its segment index (writes
@@ -373,14 +363,13 @@ template <int ITEMS, typename VecT> constexpr int stage_stride()
 //     before took its store per position under a branch, and the empty columns a kernel
 //     of scattered zeros: 8e6 nonzeros in 1.1e7 columns 162 -> 66 us.
 // The caller guarantees nseg * ldu * sizeof(VecT) < 2^31.
-template <int ITEMS, typename VecT>
+template <int ITEMS, int CAP, typename VecT>
 __device__ __forceinline__ void vtm_reduce_staged(const double *prod, uint32_t mask, int4 ci,
                                                   const int32_t *__restrict__ segcol, int64_t c, int lane,
                                                   VecT *__restrict__ u, int64_t ldu, double *__restrict__ carry,
                                                   int kk, int col, __attribute__((address_space(3))) double *stage,
                                                   int gap_max)
 {
-    constexpr int CAP = stage_cap<ITEMS, VecT>();
     const uint32_t after_s = lane == 0 ? (mask & ~1u) : mask;
     const int cnt = __popc(after_s);
     const int incl = wave_prefix_sum(cnt);

@@ -73,9 +73,12 @@ struct ColDot {
     ZonePlan zp;
     int32_t *d_empty = nullptr;         // the columns without nonzeros
     int64_t n_empty = 0;
-    // by what the column dots write themselves: [0] nothing (all of them), [1] the gaps of staged chunks
-    int32_t *d_empty_of[2] = {nullptr, nullptr};
-    int64_t n_empty_of[2] = {0, 0};
+    // by what the column dots write themselves: [0] nothing (all of them), the gaps of chunks
+    // staged for [1] binary64 vectors, [2] binary32 ones
+    int32_t *d_empty_of[3] = {nullptr, nullptr, nullptr};
+    int64_t n_empty_of[3] = {0, 0, 0};
+    int stage64 = 256;                  // segments staged for binary64 vectors
+    bool gaps = false;                  // half of the full chunks or more have empty columns inside
     int gap_max = 0;                    // gaps up to this are written by the staged chunks
     int32_t *d_zone_col = nullptr, *d_zone_first = nullptr, *d_zone_last = nullptr;
     int64_t n_zones = 0;
@@ -253,8 +256,6 @@ int64_t vtm_chunk_default();
 bool vtm_chunk_supported(int64_t chunk);
 // Waves the single-vector column-dot kernel runs for nchunks chunks on device.
 int64_t vtm_workers(int device, int64_t nchunks);
-// Segments of a chunk that its wave stages (binary64 vectors; binary32 ones only with chunks of 512).
-int64_t vtm_stage_cap(int64_t chunk);
 // The longest gap of empty columns that a staged chunk fills with zeros itself, and the
 // most empty columns per other one for which chunks do so: past that the lanes' loops over
 // the gaps cost more than a kernel over a list (8e6 nonzeros, seven empty columns in ten:

@@ -48,7 +48,8 @@ template <typename IdxT, typename ValT, int ITEMS> struct VtmChunk {
 // wchunks: NULL, or per worker (wave) the first chunk of its run, P+1 entries
 // (column partitioning: worker w reduces chunks wchunks[w] .. wchunks[w+1]-1
 // in order instead of every P-th chunk).
-template <int BLOCK, int ITEMS, typename IdxT, typename ValT, typename VecT, bool MULTI>
+// CAP: segments of a chunk that a wave stages (vtm_stage); gap_max: see vtm_reduce_staged.
+template <int BLOCK, int ITEMS, int CAP, typename IdxT, typename ValT, typename VecT, bool MULTI>
 __global__ __launch_bounds__(BLOCK) void vtm_wave(
     const IdxT *__restrict__ idx, const ValT *__restrict__ val, const uint16_t *__restrict__ heads,
     const int4 *__restrict__ cinfo, const int32_t *__restrict__ segcol, int64_t nnz, int64_t nchunks,
@@ -61,7 +62,7 @@ __global__ __launch_bounds__(BLOCK) void vtm_wave(
     constexpr int WCH = WAVE * ITEMS;
     extern __shared__ double lds[];
     // LDS: each wave's segment stage, then the hot rows of v
-    constexpr int STAGED = stage_stride<ITEMS, VecT>();
+    constexpr int STAGED = stage_stride(CAP);
     VecT *vh = reinterpret_cast<VecT *>(lds + NW * STAGED);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     __attribute__((address_space(3))) double *stage =
@@ -149,10 +150,10 @@ __global__ __launch_bounds__(BLOCK) void vtm_wave(
             // full chunk, output view within 2^31 bytes, and its segments fit the stage (none
             // empty inside, without one)
             if constexpr (STAGED > 0) {
-                const bool staged = e - s == WCH && ci.z <= stage_cap<ITEMS, VecT>() &&
+                const bool staged = e - s == WCH && ci.z <= CAP &&
                                     ldu <= (int64_t)(1 << 28) / (WCH * (int64_t)sizeof(VecT));
                 if (staged)
-                    vtm_reduce_staged<ITEMS, VecT>(prod, C.mask, ci, segcol, cc, lane, uc, ldu, carry, k, col, stage,
+                    vtm_reduce_staged<ITEMS, CAP, VecT>(prod, C.mask, ci, segcol, cc, lane, uc, ldu, carry, k, col, stage,
                                                    gap_max);
                 else
                     vtm_reduce_chunk<ITEMS, VecT>(prod, C.mask, s, e, ci, segcol, cc, lane, uc, ldu, carry, k, col);
@@ -808,17 +809,15 @@ __global__ void gather_tab(const int32_t *__restrict__ inv, int64_t rows, int k,
 // each with half the LDS.
 int vtm_wgs_per_cu(int block) { return block >= VTM_BLOCK ? VTM_WG_PER_CU : VTM_BLOCK / block; }
 // LDS of one column-dot workgroup outside the hot rows: the waves' segment stages.
-template <int ITEMS, typename VecT>
-int64_t vtm_stage_bytes(int block)
+int64_t vtm_stage_bytes(int block, int cap)
 {
-    return (int64_t)(block / WAVE) * stage_stride<ITEMS, VecT>() * (int64_t)sizeof(double);
+    return (int64_t)(block / WAVE) * stage_stride(cap) * (int64_t)sizeof(double);
 }
 // Hot rows of v that fit beside the stages, for k columns.
-template <int ITEMS, typename VecT>
-int64_t hot_rows_limit(int64_t k, int block)
+template <typename VecT>
+int64_t hot_rows_limit(int64_t k, int block, int cap)
 {
-    return (LDS_BYTES / vtm_wgs_per_cu(block) - 256 - vtm_stage_bytes<ITEMS, VecT>(block)) /
-           ((int64_t)sizeof(VecT) * k);
+    return (LDS_BYTES / vtm_wgs_per_cu(block) - 256 - vtm_stage_bytes(block, cap)) / ((int64_t)sizeof(VecT) * k);
 }
 
 // Whether the single-vector column dots fit 16 waves per CU (128 registers
@@ -845,7 +844,28 @@ int vtm_block_for(const spw_matrix_s &A, bool colpart)
     return b;
 }
 
-template <int ITEMS, typename IdxT, typename ValT, typename VecT, bool MULTI>
+// The segments of a chunk that the column dots stage for these vectors.  A stage takes LDS from
+// the hot rows of v, so it is as large as the columns need:
+// - binary64 vectors 256, or 512 where more than one chunk in eight has more than 256 (columns
+//   of one or two nonzeros; chunks of 512 only);
+// - binary32 vectors none with chunks of 1,024, and with chunks of 512 only where columns are
+//   short (fewer than two nonzeros: 8e6, one a column, binary32 values, us without and with, one vector 39 / 30, three 132 / 76)
+//   or have empty ones among them all over (3 a column 36 / 32, 97 / 87) and, for one
+//   vector, all of v still fits: sixteen waves' stages take 19,000 of 40,000 hot rows (50,000 rows, uniform,
+//   2.9e7 nonzeros, binary32 values: 66 us without, 100 with them; no empty columns, 20,000 rows,
+//   eight vectors at 5e7 595 and 665).
+template <typename ValT, typename VecT>
+int vtm_stage(const spw_matrix_s &A, int k)
+{
+    const ColDot &C = A.cd;
+    if (sizeof(VecT) == 8) return C.stage64;
+    if (C.zp.chunk != 512) return 0;
+    if (C.nnz < 2 * (C.cols - C.n_empty)) return 512;
+    const bool fits = k > 1 || A.rows <= hot_rows_limit<VecT>(1, vtm_block_for<8, ValT, VecT>(A, C.d_wchunks), 512);
+    return C.gaps && fits ? 512 : 0;
+}
+
+template <int ITEMS, int CAP, typename IdxT, typename ValT, typename VecT, bool MULTI>
 int launch_vtm_wave_items(const spw_matrix_s &A, const VecT *vin, int k, const ColOut<VecT> &out,
                           hipStream_t stream, void *stop)
 {
@@ -854,8 +874,8 @@ int launch_vtm_wave_items(const spw_matrix_s &A, const VecT *vin, int k, const C
     // column partitioning: one wave per worker of the plan (single-vector calls)
     const int32_t *wch = (!MULTI && C.d_wchunks) ? C.d_wchunks : nullptr;
     const int block = MULTI ? VTM_BLOCK : vtm_block_for<ITEMS, ValT, VecT>(A, wch != nullptr);
-    const int vhot = (int)std::min<int64_t>(A.rows, hot_rows_limit<ITEMS, VecT>(k, block));
-    const size_t lds = (size_t)vtm_stage_bytes<ITEMS, VecT>(block) + (size_t)vhot * k * sizeof(VecT);
+    const int vhot = (int)std::min<int64_t>(A.rows, hot_rows_limit<VecT>(k, block, CAP));
+    const size_t lds = (size_t)vtm_stage_bytes(block, CAP) + (size_t)vhot * k * sizeof(VecT);
     auto run = [&](auto kernel) -> int {
         const int nw = block / WAVE;
         const int64_t wgs_needed = (C.zp.n_chunks + nw - 1) / nw;
@@ -868,40 +888,44 @@ int launch_vtm_wave_items(const spw_matrix_s &A, const VecT *vin, int k, const C
     };
     if constexpr (!MULTI && vtm_fits_1024<ITEMS, ValT, VecT>()) {
         if (block == 1024) {
-            static const bool attr_w = allow_full_lds(vtm_wave<1024, ITEMS, IdxT, ValT, VecT, MULTI>);
+            static const bool attr_w = allow_full_lds(vtm_wave<1024, ITEMS, CAP, IdxT, ValT, VecT, MULTI>);
             (void)attr_w;
-            return run(vtm_wave<1024, ITEMS, IdxT, ValT, VecT, MULTI>);
+            return run(vtm_wave<1024, ITEMS, CAP, IdxT, ValT, VecT, MULTI>);
         }
     }
     if constexpr (!MULTI) {
         if (block == 256) {
-            static const bool attr_q = allow_full_lds(vtm_wave<256, ITEMS, IdxT, ValT, VecT, MULTI>);
+            static const bool attr_q = allow_full_lds(vtm_wave<256, ITEMS, CAP, IdxT, ValT, VecT, MULTI>);
             (void)attr_q;
-            return run(vtm_wave<256, ITEMS, IdxT, ValT, VecT, MULTI>);
+            return run(vtm_wave<256, ITEMS, CAP, IdxT, ValT, VecT, MULTI>);
         }
     }
-    static const bool attr = allow_full_lds(vtm_wave<VTM_BLOCK, ITEMS, IdxT, ValT, VecT, MULTI>);
+    static const bool attr = allow_full_lds(vtm_wave<VTM_BLOCK, ITEMS, CAP, IdxT, ValT, VecT, MULTI>);
     (void)attr;
-    return run(vtm_wave<VTM_BLOCK, ITEMS, IdxT, ValT, VecT, MULTI>);
+    return run(vtm_wave<VTM_BLOCK, ITEMS, CAP, IdxT, ValT, VecT, MULTI>);
 }
 
-// Chunks of 1,024 (16 positions per lane) or 512 (8 per lane) nonzeros.
+// Chunks of 1,024 (16 positions per lane) or 512 (8 per lane) nonzeros; stage: vtm_stage.
 template <typename IdxT, typename ValT, typename VecT, bool MULTI>
-int launch_vtm_wave(const spw_matrix_s &A, const VecT *vin, int k, const ColOut<VecT> &out, hipStream_t stream,
-                    void *stop)
+int launch_vtm_wave(const spw_matrix_s &A, int stage, const VecT *vin, int k, const ColOut<VecT> &out,
+                    hipStream_t stream, void *stop)
 {
-    if (A.cd.zp.chunk == 1024) return launch_vtm_wave_items<16, IdxT, ValT, VecT, MULTI>(A, vin, k, out, stream, stop);
-    if (A.cd.zp.chunk == 512) return launch_vtm_wave_items<8, IdxT, ValT, VecT, MULTI>(A, vin, k, out, stream, stop);
+    constexpr int SMALL = sizeof(VecT) == 8 ? 256 : 0;
+    if (A.cd.zp.chunk == 1024)
+        return launch_vtm_wave_items<16, SMALL, IdxT, ValT, VecT, MULTI>(A, vin, k, out, stream, stop);
+    if (A.cd.zp.chunk == 512 && stage == 512)
+        return launch_vtm_wave_items<8, 512, IdxT, ValT, VecT, MULTI>(A, vin, k, out, stream, stop);
+    if (A.cd.zp.chunk == 512)
+        return launch_vtm_wave_items<8, SMALL, IdxT, ValT, VecT, MULTI>(A, vin, k, out, stream, stop);
     return (int)hipErrorNotSupported;
 }
 
 // Which list of empty columns the column-dot kernel leaves to zero_cols: 0 all of them, 1 those
-// not written with the segments of staged chunks.  Where chunks are not staged (1,024
-// nonzeros with binary32 vectors) it is all.
+// not written with the segments of chunks staged for binary64 vectors, 2 for binary32 ones.
 template <typename VecT>
-int empty_set(const ColDot &C)
+int empty_set(int stage)
 {
-    return C.zp.chunk == 512 || sizeof(VecT) == 8 ? 1 : 0;
+    return stage == 0 ? 0 : sizeof(VecT) == 8 ? 1 : 2;
 }
 // The largest output stride of the staged copy (the kernel's own condition).
 template <typename VecT>
@@ -918,7 +942,8 @@ int vtm_typed(const spw_matrix_s &A, const VecT *v, VecT *u, bool renumbered, hi
     if (C.cols == 0) return 0;
     // the kernel writes the empty columns between a staged chunk's segments itself, unless
     // there is nothing else to do
-    const int set = C.nnz == 0 ? 0 : empty_set<VecT>(C);
+    const int stage = vtm_stage<ValT, VecT>(A, 1);
+    const int set = C.nnz == 0 ? 0 : empty_set<VecT>(stage);
     const int64_t n_empty = C.n_empty_of[set];
     if (n_empty > 0) {
         ProfScope ps(stream, "zero_cols");
@@ -942,8 +967,8 @@ int vtm_typed(const spw_matrix_s &A, const VecT *v, VecT *u, bool renumbered, hi
         out.u[0] = u;
         out.ld[0] = 1;
         void *stop = C.n_zones > 0 ? nullptr : take_stop();
-        e = C.idx_kind == IdxKind::U16 ? launch_vtm_wave<uint16_t, ValT, VecT, false>(A, vin, 1, out, stream, stop)
-                                       : launch_vtm_wave<int32_t, ValT, VecT, false>(A, vin, 1, out, stream, stop);
+        e = C.idx_kind == IdxKind::U16 ? launch_vtm_wave<uint16_t, ValT, VecT, false>(A, stage, vin, 1, out, stream, stop)
+                                       : launch_vtm_wave<int32_t, ValT, VecT, false>(A, stage, vin, 1, out, stream, stop);
         if (e) return e;
     }
     if (C.n_zones > 0) {
@@ -966,7 +991,8 @@ int vtm_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const Co
     if (C.cols == 0) return 0;
     bool wide = false;                            // an output stride the staged copy does not take
     for (int c = 0; c < k; ++c) wide = wide || out.ld[c] > staged_ld_limit<VecT>(C);
-    const int set = C.nnz == 0 || wide ? 0 : empty_set<VecT>(C);
+    const int stage = vtm_stage<ValT, VecT>(A, k);
+    const int set = C.nnz == 0 || wide ? 0 : empty_set<VecT>(stage);
     const int64_t n_empty = C.n_empty_of[set];
     if (n_empty > 0) {
         ProfScope ps(stream, "zero_cols");
@@ -986,8 +1012,8 @@ int vtm_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const Co
     {
         ProfScope ps(stream, "vtm_wave_multi");
         void *stop = C.n_zones > 0 || !last ? nullptr : take_stop();
-        e = C.idx_kind == IdxKind::U16 ? launch_vtm_wave<uint16_t, ValT, VecT, true>(A, vp, k, out, stream, stop)
-                                       : launch_vtm_wave<int32_t, ValT, VecT, true>(A, vp, k, out, stream, stop);
+        e = C.idx_kind == IdxKind::U16 ? launch_vtm_wave<uint16_t, ValT, VecT, true>(A, stage, vp, k, out, stream, stop)
+                                       : launch_vtm_wave<int32_t, ValT, VecT, true>(A, stage, vp, k, out, stream, stop);
         if (e) return e;
     }
     if (C.n_zones > 0) {
@@ -1141,7 +1167,6 @@ int64_t vtm_workers(int device, int64_t nchunks)
                                                                (nchunks + nw - 1) / nw));
     return wgs * nw;
 }
-int64_t vtm_stage_cap(int64_t chunk) { return chunk == 512 ? stage_cap<8, double>() : stage_cap<16, double>(); }
 
 int device_cu_count(int device)
 {
