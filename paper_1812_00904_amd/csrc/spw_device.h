@@ -533,10 +533,17 @@ __device__ __forceinline__ void vtm_reduce_chunk(const double *prod, uint32_t ma
 // The sum of column cc's carries over a zone's chunks a .. b (k columns): the right one
 // of a, then the left ones, in ascending chunk order, with eight loads in flight (the chain
 // of dependent trips to memory is what bounds the zone kernels: a zone has up to a hundred
-// chunks).
+// chunks).  Most zones are a column that one chunk boundary cuts: those load what they add (64
+// columns, 5e7 nonzeros, us with eight loads for each of them and now: chunks of 512 59 / 47, 1,024 32 / 26).
 __device__ __forceinline__ double zone_sum(const double *__restrict__ carry, int a, int b, int64_t k, int cc)
 {
     double s = carry[(2 * (int64_t)a + 1) * k + cc];
+    if (b - a <= 2) {
+        const double t0 = carry[2 * (int64_t)min(a + 1, b) * k + cc], t1 = carry[2 * (int64_t)b * k + cc];
+        if (a < b) s += t0;
+        if (a + 1 < b) s += t1;
+        return s;
+    }
     for (int c = a + 1; c <= b; c += 8) {
         double t[8];
 #pragma unroll
