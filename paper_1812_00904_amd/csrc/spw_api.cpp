@@ -637,6 +637,7 @@ spw_status build_coldot(spw_matrix_s &A, ColDot &C, int64_t rows, int64_t cols, 
             ci[1] = (int32_t)seg0;
             ci[2] = (int32_t)nseg;
             ci[3] = flags;
+            C.most_segs = std::max(C.most_segs, (int32_t)nseg);
         }
         segcol.push_back((int32_t)cols);          // after the last chunk's segments
         // The empty columns that a staged chunk does not write (vtm_reduce_staged): those before

@@ -79,6 +79,7 @@ struct ColDot {
     int64_t n_empty_of[3] = {0, 0, 0};
     int stage64 = 256;                  // segments staged for binary64 vectors
     bool gaps = false;                  // half of the full chunks or more have empty columns inside
+    int32_t most_segs = 0;              // segments of the chunk that has most
     int gap_max = 0;                    // gaps up to this are written by the staged chunks
     int32_t *d_zone_col = nullptr, *d_zone_first = nullptr, *d_zone_last = nullptr;
     int64_t n_zones = 0;
@@ -234,7 +235,8 @@ void *take_stop();
 // short streams win, 500 and 520), and over the transpose for both types where the caller's
 // rows are whole 16-byte groups.  Binary32 over the matrix's own storage stays with the tile
 // (k = 16 452 and 498, 32 650 and 932): a gather is half as wide there, and the starts of
-// columns weigh more.
+// columns weigh more.  Nor where one chunk's column starts, which its wave walks one after the
+// other, would take long beside the whole call (columns ordered by length).
 bool coldot_run_takes(const spw_matrix_s &A, const ColDot &C, spw_dtype vdt, int32_t k, int64_t ldv);
 int launch_coldot_run(const spw_matrix_s &A, const ColDot &C, const int32_t *inv, spw_dtype vdt, int32_t k, const void *V,
                       int64_t ldv, void *U, int64_t ldu, void *stream, bool out_f64);

@@ -458,6 +458,13 @@ int run_transpose(const spw_matrix_s &A, const ColDot &C, int k, const VecT *V, 
 bool coldot_run_takes(const spw_matrix_s &A, const ColDot &C, spw_dtype vdt, int32_t k, int64_t ldv)
 {
     if (k <= 8) return false;
+    // A wave takes about 0.16 us a column start.  Where a few chunks have most of the starts (columns
+    // by descending length: up to the whole chunk's, 160 us) their waves are the last to end, however
+    // even the others are: not worth it past about a third of the call, 6.5e-7 us a nonzero and column
+    // (binary64, 5,000 rows, 35 a column on average, ordered / not, us, tile and run: 4e6 k = 16 65 and
+    // 162 / 62 and 50, 1.25e7 k = 32 231 and 281 / 220 and 192, k = 64 454 and 407 / 423 and 310; 2.5e7 k = 16 293 and
+    // 316 / 302 and 221, k = 32 478 and 442).  Chunks of up to 48 starts are no longer than their gathers.
+    if (C.most_segs > 48 && (int64_t)C.most_segs * 700000 > C.nnz * k) return false;
     if (&C == &A.cd) {
         if (vdt != SPW_F64) return false;
         // A wave walks its chunk's column starts one after the other, where the tile's lanes take
