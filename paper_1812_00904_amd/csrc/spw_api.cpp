@@ -642,8 +642,9 @@ spw_status build_coldot(spw_matrix_s &A, ColDot &C, int64_t rows, int64_t cols, 
         segcol.push_back((int32_t)cols);          // after the last chunk's segments
         // The empty columns that a staged chunk does not write (vtm_reduce_staged): those before
         // the first column, in long gaps, and after segments of chunks that are not staged
-        // or have no empty column inside.
-        {
+        // or have no empty column inside.  The single-vector kernels read these, which run over
+        // the matrix's own storage only.
+        if (&C == &A.cd) {
             int64_t filled = 0, many = 0, full = 0, holed = 0;
             for (int64_t j = 0; j < cols; ++j) filled += ptr[j] < ptr[j + 1];
             for (int64_t c = 0; c < nch; ++c) {
