@@ -787,23 +787,11 @@ spw_status plan_workers(spw_matrix_s &A, ColDot &C, const int64_t *ptr, spw_part
 //   16 a column three 67 / 69, and at 5e7, 10 a column, 124 / 135).  With 4- or 2-byte values or
 //   vectors several vectors at once pay for the shorter chunks there (9e6, 8 a column, three
 //   vectors 60 / 68).
-// Column partitioning has no rounds: a wave reduces the chunks of its own columns one after the
-// other, and the one with most decides, so that a shorter chunk only adds its cost once more where one has
-// many (19,996 x 1.36e6, 9e6 nonzeros, one vector 86 / 105, columns by descending length 4,610 / 6,300).
-// There, 512 only for the first two reasons, and where no wave has more than twice the
-// average (6e6, two a column 38 / 31).
-int64_t auto_chunk(int64_t cols, const int64_t *ptr, spw_dtype storage, spw_partition part)
+int64_t auto_chunk(int64_t cols, const int64_t *ptr, spw_dtype storage)
 {
     const int64_t nnz = ptr[cols];
     int64_t filled = 0;
     for (int64_t j = 0; j < cols; ++j) filled += ptr[j] < ptr[j + 1];
-    if (part == SPW_PART_COLUMN) {
-        const int64_t P = 2048;
-        int64_t most = 0;
-        for (int64_t w = 0; w < P; ++w) most = std::max(most, ptr[cols * (w + 1) / P] - ptr[cols * w / P]);
-        const bool even = most * P <= 2 * nnz || most <= 1024;
-        return even && (4 * nnz < 3 * (int64_t)1024 * P || nnz < 3 * filled) ? 512 : vtm_chunk_default();
-    }
     const int64_t waves = (int64_t)1024 * 2048;             // one chunk of 1,024 for each of 2,048 waves
     const bool tiny = 4 * nnz < 3 * waves;
     const bool uneven = storage == SPW_F64 && nnz < 5 * waves && nnz < 8 * filled;
@@ -1746,7 +1734,7 @@ static spw_status spw_create_impl(spw_matrix *out, spw_format fmt, int64_t m, in
             for (int64_t p = a; p < b; ++p) rowi[(size_t)p] = rl ? rank[(size_t)idx[p]] : idx[p];
         });
     }
-    if (opts.chunk_nnz == 0) chunk = auto_chunk(cols, ptr, A->value_storage, A->partition);
+    if (opts.chunk_nnz == 0) chunk = auto_chunk(cols, ptr, A->value_storage);
     A->vtm_block[0] = A->vtm_block[1] = opts.wg_size;
     A->autotune = opts.autotune;
     A->fingerprint = matrix_fingerprint(fmt, opts.value_storage, m, n, nnz, ptr, idx);

@@ -107,18 +107,3 @@ def test_automatic_chunk(spw, n, mean, storage, chunk):
     M = spw.SpwMatrix(spw.SPW_CSC, A.m, A.n, A.ptr, A.idx, A.val, value_storage=storage)
     assert M.info()["chunk_nnz"] == chunk
     M.close()
-
-
-@pytest.mark.parametrize("partition,n,mean,longest,chunk", [
-    (1, 700_000, 7, 0, 1024), (2, 700_000, 7, 0, 512), (1, 190_000, 7, 0, 512), (1, 190_000, 7, 3_000, 1024),
-    (1, 900_000, 2, 0, 512), (1, 900_000, 2, 3_000, 1024), (1, 900_000, 2, 700, 512)])
-def test_automatic_chunk_of_partitions(spw, partition, n, mean, longest, chunk):
-    # column partitioning: no rule about rounds, and the full chunk where one wave's columns hold far
-    # more nonzeros than the average wave's
-    lengths = np.full(n, mean)
-    if longest:
-        lengths[n // 2] = longest
-    A = synth.from_lengths(3_000, lengths, 9)
-    M = spw.SpwMatrix(spw.SPW_CSC, A.m, A.n, A.ptr, A.idx, A.val, partition=partition)
-    assert M.info()["chunk_nnz"] == chunk
-    M.close()
