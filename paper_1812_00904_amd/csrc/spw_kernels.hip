@@ -45,9 +45,10 @@ template <typename IdxT, typename ValT, int ITEMS> struct VtmChunk {
 // once and reduced once per column with exactly the single-vector arithmetic,
 // so every column equals the single-vector result bit for bit.  The hot rows
 // are staged in LDS as vh[r*k + col].
-// wchunks: NULL, or per worker (wave) the first chunk of its run, P+1 entries
-// (column partitioning: worker w reduces chunks wchunks[w] .. wchunks[w+1]-1
-// in order instead of every P-th chunk).
+// wchunks: NULL, or per worker the first chunk of its run, P+1 entries
+// (column and merge-path partitioning: worker w reduces chunks wchunks[w] .. wchunks[w+1]-1
+// instead of every P-th chunk).  A worker is a wave, or the two waves of a 1,024-thread
+// workgroup that take its chunks in turn (chunks of 512: vtm_block_for).
 // CAP: segments of a chunk that a wave stages (vtm_stage); gap_max: see vtm_reduce_staged.
 template <int BLOCK, int ITEMS, int CAP, typename IdxT, typename ValT, typename VecT, bool MULTI>
 __global__ __launch_bounds__(BLOCK) void vtm_wave(
@@ -85,9 +86,11 @@ __global__ __launch_bounds__(BLOCK) void vtm_wave(
     int64_t c = (int64_t)blockIdx.x * NW + wave;
     int64_t cend = nchunks;
     if (wchunks) {
-        cend = wchunks[c + 1];
-        c = wchunks[c];
-        stride = 1;
+        constexpr int WAVES = BLOCK > VTM_BLOCK ? BLOCK / VTM_BLOCK : 1;     // of one worker
+        const int64_t w = c / WAVES;
+        cend = wchunks[w + 1];
+        c = wchunks[w] + c % WAVES;
+        stride = WAVES;
     }
     if (c >= cend) return;
 
@@ -832,12 +835,19 @@ constexpr bool vtm_fits_1024()
 // The column-dot workgroup size for a single-vector call: the matrix's choice
 // for the vector type (spw_create_opts.wg_size or the tuner's), else 1,024
 // threads for binary32 vectors with 4- or 2-byte values (16 waves hide more
-// latency) and 512 otherwise.  1,024 needs few enough registers (above); a
-// column partition keeps 512 (its worker table assumes it).
+// latency) and 512 otherwise.  1,024 needs few enough registers (above).  The worker
+// tables of the column and merge-path partitions assume eight workers a workgroup: 512 threads,
+// and under column partitioning 1,024 with chunks of 512 where one worker has more than twice the average
+// nonzeros, two waves a worker.  There it alone decides, and its chunks of 512 take one wave
+// 0.97 us each, of 1,024 1.42 (19,996 x 1.36e6, 9e6 nonzeros, one vector, us: chunks of 1,024 86, of 512 105
+// and by two waves 71; columns by descending length 4,600, 6,300, 3,880).  The chunks, and so the
+// results, are those of the other modes.
 template <int ITEMS, typename ValT, typename VecT>
 int vtm_block_for(const spw_matrix_s &A, bool colpart)
 {
-    if (colpart) return VTM_BLOCK;
+    const bool pairs = ITEMS == 8 && A.partition == SPW_PART_COLUMN &&
+                       A.cd.worker_max_nnz * A.cd.n_workers > 2 * A.cd.nnz;
+    if (colpart) return pairs ? 2 * VTM_BLOCK : VTM_BLOCK;
     int b = A.vtm_block[sizeof(VecT) == 8 ? 0 : 1];
     if (b == 0) b = (sizeof(VecT) == 4 && sizeof(ValT) <= 4) ? VTM_BLOCK_F32 : VTM_BLOCK;
     if (b == 1024 && !vtm_fits_1024<ITEMS, ValT, VecT>()) b = VTM_BLOCK;
@@ -880,7 +890,7 @@ int launch_vtm_wave_items(const spw_matrix_s &A, const VecT *vin, int k, const C
         const int nw = block / WAVE;
         const int64_t wgs_needed = (C.zp.n_chunks + nw - 1) / nw;
         const unsigned grid =
-            wch ? (unsigned)(C.n_workers / nw)
+            wch ? (unsigned)(C.n_workers / (VTM_BLOCK / WAVE))
                 : (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * vtm_wgs_per_cu(block), wgs_needed));
         return launch_kernel(kernel, dim3(grid), dim3(block), lds, stream, stop, (const IdxT *)C.d_idx,
                              (const ValT *)C.d_val, C.d_heads, (const int4 *)C.d_cinfo, C.d_segcol, C.nnz,
