@@ -42,3 +42,49 @@ def test_panels_by_column_order(spw, order, partition, panels):
     y = M.mv(torch.from_numpy(x).cuda()).cpu().numpy()
     assert np.all(np.abs(y - ref) <= 1e-13 * d)
     M.close()
+
+
+@pytest.mark.parametrize("rows", [5_000, 60_000])
+def test_columns_by_length_in_blocks(spw, rows):
+    # the ranges of most columns first, dealt over the chip: every column of a block the same bits alone,
+    # one panel and several
+    rng = np.random.Generator(np.random.PCG64(8))
+    lengths = np.sort(np.r_[np.full(60_000, 1), rng.integers(2, 55, 140_000)])[::-1]
+    A = synth.from_lengths(rows, lengths, 11, row_alpha=0.5)
+    X = synth.vector(A.n * 5, 3, 1).reshape(A.n, 5)
+    ref, d = oracle.mv_csc_batch(A.m, A.n, A.ptr, A.idx, A.val, X, with_d=True)
+    M = spw.SpwMatrix(spw.SPW_CSC, A.m, A.n, A.ptr, A.idx, A.val, transpose=0)
+    assert M.info()["n_panels"] == {5_000: 1, 60_000: 6}[rows]
+    Xd = torch.from_numpy(X).cuda()
+    Y = M.mv_batch(Xd)
+    assert np.all(np.abs(Y.cpu().numpy() - ref) <= 1e-13 * d)
+    for c in range(5):
+        assert torch.equal(Y[:, c], M.mv(Xd[:, c].contiguous())), c
+    M.close()
+
+
+def test_blocks_cost_no_more_by_length(spw):
+    # four columns at once over the ordered columns against the same columns unordered: the widest range
+    # makes a single product about 1.4 times as long, and a block no more so, where the wide ranges
+    # are spread over the chip (1.7 times where they share an eighth of it)
+    rng = np.random.Generator(np.random.PCG64(9))
+    lengths = np.r_[np.full(1_000_000, 1), rng.integers(20, 60, 300_000)]
+    best = []
+    for order in (rng.permutation(lengths), np.sort(lengths)[::-1]):
+        A = synth.from_lengths(20_000, order, 11)
+        M = spw.SpwMatrix(spw.SPW_CSC, A.m, A.n, A.ptr, A.idx, A.val, transpose=0, panel_rows=20_000)
+        X = torch.rand((A.n, 4), dtype=torch.float64, device="cuda")
+        Y = torch.empty((A.m, 4), dtype=torch.float64, device="cuda")
+        times = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                M.mv_batch(X, Y)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 200)
+        best.append(min(times))
+        M.close()
+    print("four columns, one panel, unordered and by length, us: %s" % best, flush=True)
+    assert best[1] < 1.4 * best[0]
