@@ -859,7 +859,7 @@ int vtm_block_for(const spw_matrix_s &A, bool colpart)
 // - binary64 vectors 256, or 512 where more than one chunk in eight has more than 256 (columns
 //   of one or two nonzeros; chunks of 512 only);
 // - binary32 vectors none with chunks of 1,024, and with chunks of 512 only where columns are
-//   short (fewer than two nonzeros: 8e6, one a column, binary32 values, us without and with, one vector 39 / 30, three 132 / 76)
+//   short (fewer than two nonzeros, two and a half for several vectors: 8e6, one a column, binary32 values, us without and with, one vector 39 / 30, three 132 / 76)
 //   or have empty ones among them all over (3 a column 36 / 32, 97 / 87) and, for one
 //   vector, all of v still fits: sixteen waves' stages take 19,000 of 40,000 hot rows (50,000 rows, uniform,
 //   2.9e7 nonzeros, binary32 values: 66 us without, 100 with them; no empty columns, 20,000 rows,
@@ -870,7 +870,7 @@ int vtm_stage(const spw_matrix_s &A, int k)
     const ColDot &C = A.cd;
     if (sizeof(VecT) == 8) return C.stage64;
     if (C.zp.chunk != 512) return 0;
-    if (C.nnz < 2 * (C.cols - C.n_empty)) return 512;
+    if (2 * C.nnz < (k > 1 ? 5 : 4) * (C.cols - C.n_empty)) return 512;
     const bool fits = k > 1 || A.rows <= hot_rows_limit<VecT>(1, vtm_block_for<8, ValT, VecT>(A, C.d_wchunks), 512);
     return C.gaps && fits ? 512 : 0;
 }
