@@ -968,8 +968,12 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     //    per CU in total.  Two per CU where the panels are small enough were no
     //    faster anywhere: they double the partial sums (1,000 x 1e5 with 1e6
     //    nonzeros 18.6 us at two, 13.3 us at one; 20,000 x 5e6 with 5e7 nonzeros
-    //    in four panels 131 and 119 us).
-    const int64_t target = device_cu_count(A.device);
+    //    in four panels 131 and 119 us).  But two with panels of at most 512 rows that the caller
+    //    asked for: their partial sums are small, and with one per CU many panels have one range
+    //    or two, of uneven length (20,000 x 200,000 with 4e6 nonzeros in panels of 60 and of 100
+    //    rows 42 and 38 us at one, 34 and 32 at two; with 2e7 149 and 130, 128 and 115).
+    const int64_t cus = device_cu_count(A.device);
+    const int64_t target = panel_rows_opt > 0 && R <= 512 && P <= 2 * cus ? 2 * cus : cus;
     struct WgRange {
         int32_t panel;
         int64_t a, b;      // panel-ordered positions
@@ -1002,7 +1006,7 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     int64_t copies = 1;
     const int64_t beside = std::max<int64_t>(1, std::min<int64_t>(4, limit / R));    // columns beside one another in the LDS
     while (copies < 16 && 2 * copies * R * beside <= limit && 2 * copies * target <= 512 * P &&
-           error.of(P, target, copies) > 0.9 * error.least &&
+           error.of(P, target, copies) > (panel_rows_opt > 0 ? 1.05 : 0.9) * error.least &&
            error.of(P, target, 2 * copies) < 0.9 * error.of(P, target, copies))
         copies *= 2;
     //    More slots: a row with more than 64 nonzeros a slot and four times the average row's
@@ -1118,11 +1122,19 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     // Launch order: the ranges by their first column, so that the panels of one
     // column region are neighbours, and the x-th eighth of that sequence on XCD x
     // (workgroup ids are dealt to the 8 XCDs round-robin): the panels of a region then
-    // read its entries of x through one L2 at about the same time.
+    // read its entries of x through one L2 at about the same time.  Ranges of uneven length, two
+    // on a CU: the longest first, then the shortest (id b and b + the CUs' number share a CU).
     std::vector<int32_t> wg_order((size_t)std::max<int64_t>(W, 1), 0);
     std::vector<int32_t> seq((size_t)W);
     std::iota(seq.begin(), seq.end(), 0);
-    if (read > cols) {
+    int64_t longest = 0;
+    for (const WgRange &g : wr) longest = std::max(longest, g.b - g.a);
+    if (W > cus && W <= 2 * cus && 5 * longest * W > 6 * nnz) {
+        std::stable_sort(seq.begin(), seq.end(), [&](int32_t a, int32_t b) {
+            return wr[(size_t)a].b - wr[(size_t)a].a > wr[(size_t)b].b - wr[(size_t)b].a;
+        });
+        for (int64_t b = 0; b < W; ++b) wg_order[(size_t)b] = seq[(size_t)(b < cus ? b : W - 1 - (b - cus))];
+    } else if (read > cols) {
         // Ranges that span uneven numbers of columns (columns by length): those of most columns first, whose
         // x decides, the P of a region on one XCD and the regions dealt to the XCDs in turn.  In eighths
         // all of them would be on one XCD, which with several groups of columns ends long after the
