@@ -862,20 +862,21 @@ int64_t mv_read_cols(int64_t cols, const int64_t *ptr, spw_partition part, int64
 
 // The expected squared rounding error of a row's sum of N nonzeros (random signs; in units
 // of N times one rounding's), for P panels over W ranges with `copies` sums a row and
-// range: each sum runs over n = N P / (W copies) nonzeros and adds n / 2, the eight chains of
-// mv_reduce add W copies / (16 P) (N / 16 at most) and their tree 3.  More panels make longer
-// sums, so that without copies a dense matrix loses (2-norm against 80-bit sums in the fewest
-// panels, in the rule's and in those with copies: 4,000 x 3,000 two thirds full 3.0e-16, 5.7e-16,
-// 2.2e-16; 2,000 x 30,000 with 548 a column 3.3e-16, 6.3e-16, 3.0e-16).  The copies cost what their partial sums
-// take (those matrices 20.4 -> 22.7 us, 39.9 -> 42.3; 50,000 x 50,000 with 100 a column 22.2 -> 24.4).
+// range: each sum runs over n = N P / (W copies) nonzeros and adds n / 2, the tree over the
+// copies one for each of its levels, the eight chains of mv_reduce W / (16 P) (N / 16 at most)
+// and their tree 3.  More panels make longer sums, so that without copies a dense matrix loses
+// (2-norm against 80-bit sums in the fewest panels, in the rule's and in those with copies: 4,000 x
+// 3,000 two thirds full 3.0e-16, 5.7e-16, 2.0e-16; 2,000 x 30,000 with 548 a column 3.3e-16, 6.3e-16,
+// 2.7e-16).  The copies are added when a range ends, so that they cost the LDS and nothing else
+// (as partial sums of their own 7,608 x 80,062 with 3.4e7 nonzeros took 57 us of A x, like this 50, without copies 50 too).
 // least: the fewest panels that the LDS takes, one workgroup a CU or two where it takes them,
 // one sum a row.
 struct MvError {
     double N = 0, least = 0;
     double of(int64_t P, int64_t W, int64_t copies) const
     {
-        const double sums = std::max((double)W / (double)P, 1.0) * (double)copies;
-        return N / sums / 2 + std::min(sums, N) / 16 + 3;
+        const double sums = std::max((double)W / (double)P, 1.0), each = N / (sums * (double)copies);
+        return each / 2 + std::log2((double)copies) * std::min(1.0, 2 * each) + std::min(sums, N) / 16 + 3;
     }
 };
 
@@ -1001,17 +1002,16 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     }
     // 3. Slots of the LDS panel: `copies` of every row's, and more of the rows with very many
     //    nonzeros.  A nonzero goes to one of its row's slots by its column.
-    //    Copies: the fewest that keep the sums as exact as in the fewest panels (MvError), at
-    //    most 512 partial sums a row (their reduction takes longer than it gains from there on).
+    //    Copies: the fewest that keep the sums as exact as in the fewest panels (MvError).
     int64_t copies = 1;
     const int64_t beside = std::max<int64_t>(1, std::min<int64_t>(4, limit / R));    // columns beside one another in the LDS
-    while (copies < 16 && 2 * copies * R * beside <= limit && 2 * copies * target <= 512 * P &&
+    while (copies < 16 && 2 * copies * R * beside <= limit &&
            error.of(P, target, copies) > (panel_rows_opt > 0 ? 1.05 : 0.9) * error.least &&
            error.of(P, target, 2 * copies) < 0.9 * error.of(P, target, copies))
         copies *= 2;
     //    More slots: a row with more than 64 nonzeros a slot and four times the average row's
     //    has about one for every 64, or for as many more as the room beside the others
-    //    allows, 64 or 4,096 partial sums over the panel's ranges at most.  Its one running sum would be
+    //    allows, 64 at most.  Its one running sum would be
     //    the product's largest error and one wave's work: 30,011 x 2e6 with 12e6 nonzeros and
     //    Zipf(0.8) rows, error in the 2-norm against 80-bit sums 6.6e-16 in two panels,
     //    9.9e-16 in six and 2.8e-16 in six with these slots; with Zipf(2) rows 66 us of A x in
@@ -1019,10 +1019,12 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     const std::vector<int64_t> rc = count_rows(rows, nnz, rowi);
     std::vector<uint32_t> spread((size_t)rows, 0);          // (first of them << 8) | their number
     std::vector<HotRow> hot;
+    std::vector<int32_t> hot_at((size_t)P + 1, 0);          // a panel's first
     int64_t extra = 0;                                      // of any panel
     {
         const int64_t room = std::min(limit / beside - copies * R, std::max<int64_t>(R / 32, std::min<int64_t>(R, 32)));
         for (int64_t q = 0; q < P && room > 0; ++q) {
+            hot_at[(size_t)q] = (int32_t)hot.size();
             const int64_t nw = pnw[(size_t)q] * copies;     // partial sums of a row
             std::vector<int32_t> rs;
             for (int64_t r = q; r < rows; r += P)
@@ -1030,9 +1032,8 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
             if (rs.empty()) continue;
             std::stable_sort(rs.begin(), rs.end(), [&](int32_t x, int32_t y) { return rc[(size_t)x] > rc[(size_t)y]; });
             auto more = [&](int32_t r, int64_t per) {
-                const int64_t c = std::min(std::min<int64_t>(64, std::max<int64_t>(4096 / pnw[(size_t)q], 2)),
-                                           copies * ((rc[(size_t)r] + per * nw - 1) / (per * nw)));
-                return std::max<int64_t>(c - copies, 0);
+                return std::max<int64_t>(
+                    std::min<int64_t>(64, copies * ((rc[(size_t)r] + per * nw - 1) / (per * nw))) - copies, 0);
             };
             int64_t per = 64, n;
             for (;; per *= 2) {
@@ -1045,16 +1046,16 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
                 const int64_t c = more(r, per);
                 if (c < 1) break;
                 spread[(size_t)r] = (uint32_t)(first << 8) | (uint32_t)c;
-                hot.push_back(HotRow{(int32_t)q, (int32_t)(r / P), (int32_t)first, (int32_t)c});
+                hot.push_back(HotRow{(int32_t)(r / P), (int32_t)first, (int32_t)c});
                 first += c;
             }
             extra = std::max(extra, n);
         }
     }
+    hot_at[(size_t)P] = (int32_t)hot.size();
     const int64_t V = copies * R + extra;
     A.panel_slots = V;
-    A.row_copies = copies;
-    A.n_hot_rows = (int64_t)hot.size();
+    while (((int64_t)1 << A.row_copies_log) < copies) ++A.row_copies_log;
     // Deal each panel's slots to the NB waves, heaviest first onto the lightest wave.
     std::vector<uint8_t> wave_of((size_t)(P * V), 0);       // [panel * V + slot]
     for (int64_t q = 0; q < P; ++q) {
@@ -1272,14 +1273,16 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     if ((st = dev_alloc(A, &A.d_panels, P, "panels"))) return st;
     if ((st = h2d(A.d_panels, A.panels.data(), A.panels.size() * sizeof(PanelDesc), "panels"))) return st;
     if (!hot.empty()) {
-        // one bit a row: summed by a workgroup of its own
-        const int64_t words = (R + 31) / 32;
-        std::vector<uint32_t> mask((size_t)(P * words), 0);
-        for (const HotRow &h : hot) mask[(size_t)(h.panel * words + h.local / 32)] |= 1u << (h.local % 32);
-        if ((st = dev_alloc(A, &A.d_hot, (int64_t)hot.size(), "rows of several slots"))) return st;
-        if ((st = h2d(A.d_hot, hot.data(), hot.size() * sizeof(HotRow), "rows of several slots"))) return st;
-        if ((st = dev_alloc(A, &A.d_hot_mask, (int64_t)mask.size(), "rows of several slots"))) return st;
-        if ((st = h2d(A.d_hot_mask, mask.data(), mask.size() * 4, "rows of several slots"))) return st;
+        std::vector<int32_t> of((size_t)(2 * W));           // per range: its panel's first, and how many
+        for (int64_t w = 0; w < W; ++w) {
+            const size_t q = (size_t)wr[(size_t)w].panel;
+            of[(size_t)(2 * w)] = hot_at[q];
+            of[(size_t)(2 * w + 1)] = hot_at[q + 1] - hot_at[q];
+        }
+        if ((st = dev_alloc(A, &A.d_hot, (int64_t)hot.size(), "rows of more slots"))) return st;
+        if ((st = h2d(A.d_hot, hot.data(), hot.size() * sizeof(HotRow), "rows of more slots"))) return st;
+        if ((st = dev_alloc(A, &A.d_wg_hot, 2 * W, "rows of more slots"))) return st;
+        if ((st = h2d(A.d_wg_hot, of.data(), of.size() * 4, "rows of more slots"))) return st;
     }
     return SPW_OK;
 }
@@ -1298,7 +1301,7 @@ spw_status grow_scratch(spw_matrix_s &A, int32_t k)
     spw_status st;
     if (!A.scratch.partial) {
         // partial sums of the scatter product: one column at a time
-        if ((st = dev_alloc(A, &A.scratch.partial, std::max<int64_t>(A.mv_wgs, 1) * A.panel_slots, "partial sums")))
+        if ((st = dev_alloc(A, &A.scratch.partial, std::max<int64_t>(A.mv_wgs, 1) * A.panel_rows, "partial sums")))
             return st;
     }
     const int64_t nch = std::max<int64_t>(A.cd.zp.n_chunks, A.cdt.zp.n_chunks);
@@ -1508,7 +1511,7 @@ spw_status grow_partial_cols(spw_matrix_s &A, int32_t cols)
         A.scratch.pcols = 0;
     }
     spw_status st;
-    if ((st = dev_alloc(A, &A.scratch.partial_cols, (int64_t)cols * A.mv_wgs * A.panel_slots, "multi-column partial sums")))
+    if ((st = dev_alloc(A, &A.scratch.partial_cols, (int64_t)cols * A.mv_wgs * A.panel_rows, "multi-column partial sums")))
         return st;
     A.scratch.pcols = cols;
     return SPW_OK;

@@ -50,10 +50,10 @@ struct PanelDesc {
     int32_t row0, rows, wg0, nwg;
 };
 
-// A row with more slots of its LDS panel than the others: besides row_copies (at local,
-// local + panel_rows, ...) slots [first, first + more).
+// A row with more slots of its LDS panel than the others: besides its own (panel-local row
+// `local` and its copies) [first, first + more).
 struct HotRow {
-    int32_t panel, local, first, more;
+    int32_t local, first, more;
 };
 
 // ------------------------------------------------------------ device handle
@@ -103,8 +103,8 @@ struct CglsScratch {
 };
 
 struct Scratch {
-    double *partial = nullptr;    // mv_wgs * panel_slots  (binary64 partial sums of one column)
-    double *partial_cols = nullptr;   // pcols * mv_wgs * panel_slots (multi-column scatter launches)
+    double *partial = nullptr;    // mv_wgs * panel_rows  (binary64 partial sums of one column)
+    double *partial_cols = nullptr;   // pcols * mv_wgs * panel_rows (multi-column scatter launches)
     int32_t pcols = 0;
     double *carry = nullptr;      // 2 * max chunks * kcap
     int64_t carry_chunks = 0;     // the chunk count the carries were sized for
@@ -147,11 +147,12 @@ struct spw_matrix_s {
     // scatter-product storage: row panels; inside a panel, per workgroup column
     // range and per wave (a set of the panel's rows), blocks of 512 nonzeros
     int64_t panel_rows = 0, n_panels = 0;
-    // entries of an LDS panel and of a range's partial sums: row_copies (a power of two) of panel_rows,
-    // then the ones that rows with very many nonzeros have besides (hot rows)
-    int64_t panel_slots = 0, row_copies = 1, n_hot_rows = 0;
-    spw::HotRow *d_hot = nullptr;
-    uint32_t *d_hot_mask = nullptr;     // per panel and 32 of its rows: one bit a hot row
+    // entries of an LDS panel: 2^row_copies_log of every one of panel_rows rows, then the ones that rows with
+    // very many nonzeros have besides (hot rows)
+    int64_t panel_slots = 0;
+    int row_copies_log = 0;
+    spw::HotRow *d_hot = nullptr;       // panel by panel; d_wg_hot: per workgroup range its panel's first, and how many
+    int32_t *d_wg_hot = nullptr;        // (NULL: no such rows)
     uint32_t *d_mpacked = nullptr;      // (panel slot << 16) | (column - block column base)
     void *d_mval = nullptr;             // values in the storage type, interleaved like d_mpacked
     int32_t *d_mblocks = nullptr;       // per block: column base, count

@@ -234,7 +234,7 @@ __global__ void gather_vec(const int32_t *__restrict__ inv, int64_t len, const V
 //   blocks : (column base, count) per block
 //   wg_blk : per workgroup, NW+1 offsets into blocks: wave w owns [wg_blk[w], wg_blk[w+1])
 //   x      : input, entry j at x[j*ldx]
-//   partial: per-workgroup partial sums, one per slot
+//   partial: per-workgroup partial sums, one per row
 // The loop keeps two blocks of words/values and one block of x gathers in
 // flight.  Dynamic LDS: one double per slot.
 // ------------------------------------------------------------------------
@@ -264,17 +264,84 @@ __device__ __forceinline__ void mv_load(MvBlk<ValT> &B, const uint32_t *__restri
     B.a.template load<NT>(val + base, lane);
 }
 
+// The LDS panel's shape: slots of all, rows, and 2^cs copies of each row in front; hot, nhot: the
+// rows with more slots (of this range's panel).
+struct MvPanel {
+    int slots, rows, cs, nhot;
+    const HotRow *hot;
+};
+__device__ __forceinline__ MvPanel mv_panel(int slots, int rows, int cs, const HotRow *__restrict__ hot,
+                                            const int2 *__restrict__ wg_hot, int range)
+{
+    const int2 h = wg_hot ? wg_hot[range] : make_int2(0, 0);
+    return MvPanel{slots, rows, cs, h.y, hot + h.x};
+}
+
+// KC panels to their partial sums, one a row: the slots that a row has more are added to its first,
+// four running sums of them, then the row's copies pairwise.  All of the workgroup's waves come here
+// with their adds to the panel made or under way.  The descriptors of the rows with more slots are
+// read before the barrier, and without copies the columns' loads are independent of one another: in
+// small products the end of a range counts (29,966 x 2.5e6 with 257,000 nonzeros, twelve columns:
+// 78 us of mv_bucket with a test for the copies at every element, 71 like this).
+template <int BLOCK, int KC>
+__device__ __forceinline__ void mv_write_panel(double *ypan, const MvPanel &pn, double *__restrict__ out,
+                                               int64_t col_stride)
+{
+    const int rows = pn.rows, cs = pn.cs, tid = threadIdx.x;
+    HotRow h = {};
+    if (tid < pn.nhot * KC) h = pn.hot[tid / KC];
+    __syncthreads();
+    if (pn.nhot > 0) {
+        for (int i = tid; i < pn.nhot * KC; i += BLOCK) {
+            if (i != tid) h = pn.hot[i / KC];
+            double *y = ypan + (i % KC) * pn.slots, a[4] = {y[h.local], 0.0, 0.0, 0.0};
+            for (int j = 0; j < h.more; j += 4)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (j + t < h.more) a[(t + 1) & 3] += y[h.first + j + t];
+            y[h.local] = (a[0] + a[1]) + (a[2] + a[3]);
+        }
+        __syncthreads();
+    }
+    if (cs == 0) {
+#pragma unroll
+        for (int c = 0; c < KC; ++c)
+            for (int i = tid; i < rows; i += BLOCK) out[c * col_stride + i] = ypan[c * pn.slots + i];
+        return;
+    }
+    for (int i = tid; i < rows; i += BLOCK) {
+        double s[KC];
+        auto each = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < KC; ++c) f(s[c], ypan + c * pn.slots + i);
+        };
+        each([&](double &t, const double *p) { t = p[0] + p[rows]; });
+        if (cs >= 2) each([&](double &t, const double *p) { t += p[2 * rows] + p[3 * rows]; });
+        if (cs >= 3)
+            each([&](double &t, const double *p) {
+                t += (p[4 * rows] + p[5 * rows]) + (p[6 * rows] + p[7 * rows]);
+            });
+        if (cs >= 4)
+            each([&](double &t, const double *p) {
+                t += ((p[8 * rows] + p[9 * rows]) + (p[10 * rows] + p[11 * rows])) +
+                     ((p[12 * rows] + p[13 * rows]) + (p[14 * rows] + p[15 * rows]));
+            });
+#pragma unroll
+        for (int c = 0; c < KC; ++c) out[c * col_stride + i] = s[c];
+    }
+}
+
 // One workgroup range of the scatter product into the LDS panel ypan, written
-// to out (one double per slot).
+// to out (mv_write_panel).
 template <int BLOCK, typename ValT, typename VecT, bool NT>
 __device__ __forceinline__ void mv_range(const uint32_t *__restrict__ packed, const ValT *__restrict__ val,
                                          const int2 *__restrict__ blocks, const int32_t *__restrict__ wg_blk,
                                          int range, const VecT *__restrict__ x, int64_t ldx,
-                                         double *__restrict__ out, int slots, double *ypan)
+                                         double *__restrict__ out, const MvPanel &pn, double *ypan)
 {
     constexpr int NW = BLOCK / WAVE;
     const int tid = threadIdx.x, wave = tid / WAVE, lane = tid & (WAVE - 1);
-    for (int i = tid; i < slots; i += BLOCK) ypan[i] = 0.0;
+    for (int i = tid; i < pn.slots; i += BLOCK) ypan[i] = 0.0;
     __syncthreads();
 
     const int32_t *wb = wg_blk + (int64_t)range * (NW + 1);
@@ -355,20 +422,21 @@ __device__ __forceinline__ void mv_range(const uint32_t *__restrict__ packed, co
             if (b + 2 >= b1) break;
         }
     }
-    __syncthreads();
-    for (int i = tid; i < slots; i += BLOCK) out[i] = ypan[i];
+    mv_write_panel<BLOCK, 1>(ypan, pn, out, 0);
 }
 
 template <int BLOCK, typename ValT, typename VecT>
 __global__ __launch_bounds__(BLOCK) void mv_bucket(
     const uint32_t *__restrict__ packed, const ValT *__restrict__ val, const int2 *__restrict__ blocks,
     const int32_t *__restrict__ wg_blk, const int32_t *__restrict__ wg_order, const VecT *__restrict__ x, int64_t ldx,
-    double *__restrict__ partial, int slots)
+    double *__restrict__ partial, int slots, int rows, int cs, const HotRow *__restrict__ hot,
+    const int2 *__restrict__ wg_hot)
 {
     extern __shared__ double ypan[];
     const int range = wg_order[blockIdx.x];
     mv_range<BLOCK, ValT, VecT, true>(packed, val, blocks, wg_blk, range, x, ldx,
-                                      partial + (int64_t)range * slots, slots, ypan);
+                                      partial + (int64_t)range * rows, mv_panel(slots, rows, cs, hot, wg_hot, range),
+                                      ypan);
 }
 
 // ------------------------------------------------------------------------
@@ -497,8 +565,9 @@ template <int BLOCK, typename ValT, typename VecT, int KC, bool WIDE>
 __device__ __forceinline__ void mv_range_cols(const uint32_t *__restrict__ packed, const ValT *__restrict__ val,
                                               const int2 *__restrict__ blocks, const int32_t *__restrict__ wb,
                                               const VecT *__restrict__ x, int64_t ldx, double *__restrict__ out,
-                                              int64_t col_stride, int slots, double *ypan)
+                                              int64_t col_stride, const MvPanel &pn, double *ypan)
 {
+    const int slots = pn.slots;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
     for (int i = tid; i < KC * slots; i += BLOCK) ypan[i] = 0.0;
@@ -606,9 +675,7 @@ __device__ __forceinline__ void mv_range_cols(const uint32_t *__restrict__ packe
             if (b + 2 >= b1) break;
         }
     }
-    __syncthreads();
-    for (int c = 0; c < KC; ++c)
-        for (int i = tid; i < slots; i += BLOCK) out[c * col_stride + i] = ypan[c * slots + i];
+    mv_write_panel<BLOCK, KC>(ypan, pn, out, col_stride);
 }
 
 // Groups of columns in one launch: workgroup (group, range).  The groups of one
@@ -617,12 +684,13 @@ __device__ __forceinline__ void mv_range_cols(const uint32_t *__restrict__ packe
 // so they share the blocks and the lines of X through its L2 (ordinary loads: the lines
 // stay for the others).  The tables are picked by a chain of selects on the group,
 // so they stay in kernel arguments.  Column c of the launch keeps its partial
-// sums in slot c (W ranges of one double per slot each).
+// sums in slot c (W ranges of one double per row each).
 template <int BLOCK, typename ValT, typename VecT>
 __global__ __launch_bounds__(BLOCK) void mv_bucket_cols(
     const uint32_t *__restrict__ packed, const ValT *__restrict__ val, const int2 *__restrict__ blocks,
     const int32_t *__restrict__ wg_blk, const int32_t *__restrict__ wg_order, MvGroups<VecT> groups, int ngroups,
-    double *__restrict__ partial, int slots, int W)
+    double *__restrict__ partial, int slots, int rows, int cs, const HotRow *__restrict__ hot,
+    const int2 *__restrict__ wg_hot, int W)
 {
     constexpr int NW = BLOCK / WAVE;
     extern __shared__ double ypan[];
@@ -640,12 +708,13 @@ __global__ __launch_bounds__(BLOCK) void mv_bucket_cols(
         kc = g == t ? groups.kc[t] : kc;
         slot = g == t ? groups.slot[t] : slot;
     }
-    const int64_t col_stride = (int64_t)W * slots;
-    double *out = partial + slot * col_stride + (int64_t)range * slots;
+    const int64_t col_stride = (int64_t)W * rows;
+    double *out = partial + slot * col_stride + (int64_t)range * rows;
+    const MvPanel pn = mv_panel(slots, rows, cs, hot, wg_hot, range);
     const int32_t *wb = wg_blk + (int64_t)range * (NW + 1);
     auto run = [&](auto cols, auto wide) {
         mv_range_cols<BLOCK, ValT, VecT, decltype(cols)::value, decltype(wide)::value>(
-            packed, val, blocks, wb, x, ld, out, col_stride, slots, ypan);
+            packed, val, blocks, wb, x, ld, out, col_stride, pn, ypan);
     };
     // a block spans fewer than 65,536 columns: 32-bit byte offsets below this stride
     if (ld * (int64_t)sizeof(VecT) < 65536) {
@@ -661,26 +730,21 @@ __global__ __launch_bounds__(BLOCK) void mv_bucket_cols(
     }
 }
 
-// y[caller row] = sum over the panel's workgroups of their partials, 2^cs of each (the row's
-// copies).  Internal row r belongs to panel r mod npanels, at panel-local row r / npanels; a
+// y[caller row] = sum over the panel's workgroups of their partials.  Internal row r belongs to panel r mod npanels, at panel-local row r / npanels; a
 // workgroup takes 32 consecutive rows of one panel, eight threads a row: thread t
 // adds partials t, t+8, t+16, ... in ascending order with up to sixteen loads in
 // flight (a chain of dependent trips to memory bounds this kernel, not its
 // bytes), then the eight sums are combined pairwise, so the order of every
-// addition is fixed.  FEW: at most eight partials a row, where one thread takes a
+// addition is fixed.  FEW: panels of at most eight workgroups, where one thread takes a
 // whole row, in the same order, and the panels are one sequence of rows, so that small
 // ones fill a workgroup too (2e6 x 2e6 in 98 panels of two or three workgroups: 83 us with
-// eight threads a row, five of them idle, now 43; 500,000 rows in 49 panels 32 and 17).  Hot rows (hot_mask's bits) are left to workgroups of
-// their own, before the others: thread t adds partial sums t, t+256, ... of all of the
-// row's slots, and the 256 sums are combined in a fixed tree.  Column blockIdx.y: its partials start col_stride doubles
+// eight threads a row, five of them idle, now 43; 500,000 rows in 49 panels 32 and 17).  Column blockIdx.y: its partials start col_stride doubles
 // further, its output is out.u[column].
 constexpr int MV_FEW = 8;
 template <typename VecT, bool FEW>
-__global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ partial, int slots, int cs, int panel_rows,
-                                                 int panel_blocks, const PanelDesc *__restrict__ panels, int npanels,
-                                                 const HotRow *__restrict__ hot, int nhot,
-                                                 const uint32_t *__restrict__ hot_mask, const int32_t *__restrict__ inv,
-                                                 ColOut<VecT> out, int64_t col_stride)
+__global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ partial, int panel_rows, int panel_blocks,
+                                                 const PanelDesc *__restrict__ panels, int npanels,
+                                                 const int32_t *__restrict__ inv, ColOut<VecT> out, int64_t col_stride)
 {
     __shared__ double sums[8][32];
     VecT *y = out.u[0];
@@ -690,50 +754,19 @@ __global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ part
         y = blockIdx.y == c ? out.u[c] : y;
         ldy = blockIdx.y == c ? out.ld[c] : ldy;
     }
-    if ((int)blockIdx.x < nhot) {
-        const HotRow h = hot[blockIdx.x];
-        const PanelDesc pd = panels[h.panel];
-        const double *src = partial + blockIdx.y * col_stride + (int64_t)pd.wg0 * slots;
-        const int each = (1 << cs) + h.more, n = pd.nwg * each;
-        double s = 0.0;
-        for (int w = threadIdx.x; w < n; w += 256 * 8) {
-            double a[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int at = min(w + 256 * i, n - 1), wg = at / each, c = at - wg * each;
-                a[i] = src[(int64_t)wg * slots + (c < (1 << cs) ? c * panel_rows + h.local : h.first + c - (1 << cs))];
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (w + 256 * i < n) s += a[i];
-        }
-#pragma unroll
-        for (int off = 1; off < WAVE; off <<= 1) s += __shfl_xor(s, off, WAVE);
-        if (threadIdx.x % WAVE == 0) sums[0][threadIdx.x / WAVE] = s;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const int64_t r = (int64_t)h.local * npanels + h.panel;
-            y[(int64_t)(inv ? inv[r] : r) * ldy] = (VecT)((sums[0][0] + sums[0][1]) + (sums[0][2] + sums[0][3]));
-        }
-        return;
-    }
-    const int block = (int)blockIdx.x - nhot;
     int p, local, t = 0;
     if constexpr (FEW) {
-        const uint32_t g = (uint32_t)block * 256u + threadIdx.x;
+        const uint32_t g = blockIdx.x * 256u + threadIdx.x;
         p = (int)min(g / (uint32_t)panel_rows, (uint32_t)npanels - 1u);
         local = (int)(g - (uint32_t)p * (uint32_t)panel_rows);
     } else {
-        p = block / panel_blocks;
-        local = (block - p * panel_blocks) * 32 + (threadIdx.x & 31);
+        p = blockIdx.x / panel_blocks;
+        local = (blockIdx.x - p * panel_blocks) * 32 + (threadIdx.x & 31);
         t = threadIdx.x >> 5;
     }
     const PanelDesc pd = panels[p];
-    bool live = local < pd.rows;
-    if (hot_mask && live) live = !((hot_mask[p * ((panel_rows + 31) / 32) + local / 32] >> (local % 32)) & 1u);
-    const double *base = partial + blockIdx.y * col_stride + (int64_t)pd.wg0 * slots + local;
-    const int n = pd.nwg << cs;                    // partials of a row
-    auto src = [&](int i) { return base[(int64_t)(i >> cs) * slots + (i & ((1 << cs) - 1)) * panel_rows]; };
+    const bool live = local < pd.rows;
+    const double *src = partial + blockIdx.y * col_stride + (int64_t)pd.wg0 * panel_rows + local;
     const int64_t r = (int64_t)local * npanels + p;
     int64_t to = r;
     if (inv && t == 0 && live) to = inv[r];       // beside the partial sums, not after them
@@ -741,7 +774,7 @@ __global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ part
         if (!live) return;
         double a[MV_FEW];
 #pragma unroll
-        for (int i = 0; i < MV_FEW; ++i) a[i] = i < n ? src(i) : 0.0;
+        for (int i = 0; i < MV_FEW; ++i) a[i] = i < pd.nwg ? src[(int64_t)i * panel_rows] : 0.0;
         y[to * ldy] = (VecT)(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
         return;
     }
@@ -749,16 +782,16 @@ __global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ part
     if (live) {
         auto add = [&](auto loads) __attribute__((always_inline)) {
             constexpr int U = decltype(loads)::value;
-            for (int w = t; w < n; w += 8 * U) {
+            for (int w = t; w < pd.nwg; w += 8 * U) {
                 double a[U];
 #pragma unroll
-                for (int i = 0; i < U; ++i) a[i] = w + 8 * i < n ? src(w + 8 * i) : 0.0;
+                for (int i = 0; i < U; ++i) a[i] = w + 8 * i < pd.nwg ? src[(int64_t)(w + 8 * i) * panel_rows] : 0.0;
 #pragma unroll
                 for (int i = 0; i < U; ++i)
-                    if (w + 8 * i < n) s += a[i];
+                    if (w + 8 * i < pd.nwg) s += a[i];
             }
         };
-        if (n <= 8 * 4) add(IntC<4>());
+        if (pd.nwg <= 8 * 4) add(IntC<4>());
         else add(IntC<16>());
     }
     sums[t][threadIdx.x & 31] = s;
@@ -1056,16 +1089,12 @@ int launch_mv_reduce(const spw_matrix_s &A, const double *partial, int k, const 
                      hipStream_t stream)
 {
     ProfScope ps(stream, "mv_reduce");
-    int cs = 0;
-    while ((1 << cs) < A.row_copies) ++cs;
     auto run = [&](auto kernel, unsigned blocks, unsigned panel_blocks) {
-        return launch_kernel(kernel, dim3(blocks + (unsigned)A.n_hot_rows, (unsigned)k), dim3(256), 0, stream,
-                             last ? take_stop() : nullptr, partial, (int)A.panel_slots, cs, (int)A.panel_rows,
-                             (int)panel_blocks, A.d_panels, (int)A.n_panels, A.d_hot, (int)A.n_hot_rows, A.d_hot_mask,
-                             A.relabeled ? A.d_inv : nullptr, out, A.mv_wgs * A.panel_slots);
+        return launch_kernel(kernel, dim3(blocks, (unsigned)k), dim3(256), 0, stream, last ? take_stop() : nullptr, partial,
+                             (int)A.panel_rows, (int)panel_blocks, A.d_panels, (int)A.n_panels,
+                             A.relabeled ? A.d_inv : nullptr, out, A.mv_wgs * A.panel_rows);
     };
-    if (A.panel_wgs * A.row_copies <= MV_FEW)
-        return run(mv_reduce<VecT, true>, blocks_for(A.n_panels * A.panel_rows, 256), 0u);
+    if (A.panel_wgs <= MV_FEW) return run(mv_reduce<VecT, true>, blocks_for(A.n_panels * A.panel_rows, 256), 0u);
     const unsigned panel_blocks = blocks_for(A.panel_rows, 32);
     return run(mv_reduce<VecT, false>, (unsigned)A.n_panels * panel_blocks, panel_blocks);
 }
@@ -1110,7 +1139,8 @@ int mv_cols_typed(const spw_matrix_s &A, int k, const ColIn<VecT> &in, const Col
         hipLaunchKernelGGL((mv_bucket_cols<MV_BLOCK, ValT, VecT>), dim3((unsigned)(8 * ng * ((W + 7) / 8))),
                            dim3(MV_BLOCK), (size_t)A.panel_slots * 8 * (size_t)widest, stream,
                            (const uint32_t *)A.d_mpacked, (const ValT *)A.d_mval, (const int2 *)A.d_mblocks,
-                           A.d_wg_blk, A.d_wg_order, gr, ng, A.scratch.partial_cols, (int)A.panel_slots, W);
+                           A.d_wg_blk, A.d_wg_order, gr, ng, A.scratch.partial_cols, (int)A.panel_slots,
+                           (int)A.panel_rows, A.row_copies_log, A.d_hot, (const int2 *)A.d_wg_hot, W);
         if ((e = (int)hipGetLastError())) return e;
     }
     return launch_mv_reduce<VecT>(A, A.scratch.partial_cols, k, out, last, stream);
@@ -1148,7 +1178,7 @@ int mv_typed(const spw_matrix_s &A, int32_t k, const VecT *x, int64_t ldx, VecT 
             hipLaunchKernelGGL((mv_bucket<MV_BLOCK, ValT, VecT>), dim3((unsigned)A.mv_wgs), dim3(MV_BLOCK), lds,
                                stream, (const uint32_t *)A.d_mpacked, (const ValT *)A.d_mval,
                                (const int2 *)A.d_mblocks, A.d_wg_blk, A.d_wg_order, x + c, ldx, A.scratch.partial,
-                               (int)A.panel_slots);
+                               (int)A.panel_slots, (int)A.panel_rows, A.row_copies_log, A.d_hot, (const int2 *)A.d_wg_hot);
             if ((e = (int)hipGetLastError())) return e;
         }
         ColOut<VecT> out{};
