@@ -247,7 +247,7 @@ template <typename ValT> struct MvBlk {
     int2 bd;
 };
 
-template <bool NT, typename ValT>
+template <typename ValT>
 __device__ __forceinline__ void mv_load(MvBlk<ValT> &B, const uint32_t *__restrict__ packed,
                                         const ValT *__restrict__ val, const int2 *__restrict__ blocks, int b, int lane)
 {
@@ -255,13 +255,13 @@ __device__ __forceinline__ void mv_load(MvBlk<ValT> &B, const uint32_t *__restri
     const int64_t base = (int64_t)b * MV_BLK;
 #pragma unroll
     for (int g = 0; g < MV_ITEMS / 4; ++g) {
-        const u32x4_t q = ld_stream<NT>(reinterpret_cast<const u32x4_t *>(packed + base + (int64_t)(g * 64 + lane) * 4));
+        const u32x4_t q = ld_stream<true>(reinterpret_cast<const u32x4_t *>(packed + base + (int64_t)(g * 64 + lane) * 4));
         B.w[4 * g] = q.x;
         B.w[4 * g + 1] = q.y;
         B.w[4 * g + 2] = q.z;
         B.w[4 * g + 3] = q.w;
     }
-    B.a.template load<NT>(val + base, lane);
+    B.a.template load<true>(val + base, lane);
 }
 
 // The LDS panel's shape: slots of all, rows, and 2^cs copies of each row in front; hot, nhot: the
@@ -333,7 +333,7 @@ __device__ __forceinline__ void mv_write_panel(double *ypan, const MvPanel &pn, 
 
 // One workgroup range of the scatter product into the LDS panel ypan, written
 // to out (mv_write_panel).
-template <int BLOCK, typename ValT, typename VecT, bool NT>
+template <int BLOCK, typename ValT, typename VecT>
 __device__ __forceinline__ void mv_range(const uint32_t *__restrict__ packed, const ValT *__restrict__ val,
                                          const int2 *__restrict__ blocks, const int32_t *__restrict__ wg_blk,
                                          int range, const VecT *__restrict__ x, int64_t ldx,
@@ -388,9 +388,9 @@ __device__ __forceinline__ void mv_range(const uint32_t *__restrict__ packed, co
     // the compiler keeps the two in place instead of copying between them).
     // Ranges of one or two blocks (small matrices) skip those repeats.
     if (b0 < b1 && b1 - b0 <= 2) {
-        mv_load<NT>(B0, packed, val, blocks, b0, lane);
+        mv_load(B0, packed, val, blocks, b0, lane);
         gather(B0, x0);
-        if (b1 - b0 == 2) mv_load<NT>(B1, packed, val, blocks, b0 + 1, lane);
+        if (b1 - b0 == 2) mv_load(B1, packed, val, blocks, b0 + 1, lane);
         double p[MV_ITEMS];
         uint32_t row[MV_ITEMS];
         add_block(B0, x0, p, row);
@@ -402,22 +402,22 @@ __device__ __forceinline__ void mv_range(const uint32_t *__restrict__ packed, co
         }
     } else if (b0 < b1) {
         const int last = b1 - 1;
-        mv_load<NT>(B0, packed, val, blocks, b0, lane);
+        mv_load(B0, packed, val, blocks, b0, lane);
         gather(B0, x0);
-        mv_load<NT>(B1, packed, val, blocks, min(b0 + 1, last), lane);
+        mv_load(B1, packed, val, blocks, min(b0 + 1, last), lane);
         for (int b = b0;; b += 2) {
             double p[MV_ITEMS];
             uint32_t row[MV_ITEMS];
             add_block(B0, x0, p, row);
             int cnt = B0.bd.y;
             gather(B1, x1);
-            mv_load<NT>(B0, packed, val, blocks, min(b + 2, last), lane);
+            mv_load(B0, packed, val, blocks, min(b + 2, last), lane);
             commit(cnt, p, row);
             if (b + 1 >= b1) break;
             add_block(B1, x1, p, row);
             cnt = B1.bd.y;
             gather(B0, x0);
-            mv_load<NT>(B1, packed, val, blocks, min(b + 3, last), lane);
+            mv_load(B1, packed, val, blocks, min(b + 3, last), lane);
             commit(cnt, p, row);
             if (b + 2 >= b1) break;
         }
@@ -434,7 +434,7 @@ __global__ __launch_bounds__(BLOCK) void mv_bucket(
 {
     extern __shared__ double ypan[];
     const int range = wg_order[blockIdx.x];
-    mv_range<BLOCK, ValT, VecT, true>(packed, val, blocks, wg_blk, range, x, ldx,
+    mv_range<BLOCK, ValT, VecT>(packed, val, blocks, wg_blk, range, x, ldx,
                                       partial + (int64_t)range * rows, mv_panel(slots, rows, cs, hot, wg_hot, range),
                                       ypan);
 }
