@@ -747,8 +747,10 @@ def bench_batched(args):
             by1 = model_bytes(A.m, A.n, A.nnz, k=1, sv=sx, sx=sx)
             pmv, _ = M.batch_plan(SPW_OP_MV, vdt, k)
             pvtm, _ = M.batch_plan(SPW_OP_VTM, vdt, k)
+            tiles = [plan == 3 and tile_kernel(fn) for plan, fn in
+                     ((pmv, lambda: M.mv_batch(X, Y)), (pvtm, lambda: M.vtm_batch(V, U)))]
             row = {"dtype": "f64" if sx == 8 else "f32", "k": k,
-                   "plan": batch_plan(info, k, pmv, pvtm, sx), "create_with_tuning_s": round(t_create, 2),
+                   "plan": batch_plan(info, k, pmv, pvtm, sx, tiles), "create_with_tuning_s": round(t_create, 2),
                    "first_calls_with_tuning_s": round(t_tune, 3),
                    "mv_batch_ms": round(t_mv, 4), "vtm_batch_ms": round(t_vtm, 4),
                    "mv_plain_k_calls_ms": round(t_pmv, 4), "vtm_plain_k_calls_ms": round(t_pvtm, 4),
@@ -977,17 +979,41 @@ def bench_serving(args):
     return res
 
 
-def batch_plan(info, k, plan_mv, plan_vtm, sx):
+def tile_kernel(fn):
+    """The column-dot kernel (cdot_tile or cdot_run) that a call of the tiled plan runs."""
+    import torch
+    from paper_1812_00904_amd import spw_profile_enable, spw_profile_read, spw_profile_reset, spw_profile_select
+    spw_profile_reset()
+    spw_profile_select(None)
+    spw_profile_enable(True)
+    fn()
+    torch.cuda.synchronize()
+    spw_profile_enable(False)
+    ran = set(spw_profile_read()) & {"cdot_tile", "cdot_run"}
+    spw_profile_reset()
+    return ran.pop()
+
+
+def batch_plan(info, k, plan_mv, plan_vtm, sx, tiles):
     """The kernel configuration a k-wide block runs with (the tuned plan per
-    direction, the tuned column-dot chunk and workgroup sizes)."""
+    direction, the tuned column-dot chunk and workgroup sizes; tiles: per
+    direction the kernel of the tiled plan)."""
     L = 2
     while L < k:
         L *= 2
     chunk = info["chunk_nnz"]
     wg = info["wg_size_f64"] if sx == 8 else info["wg_size_f32"]
-    def tile(ch):
-        return ("tiled column dots: chunks of %d nonzeros, one chunk per wave, %d column lanes x %d position "
-                "sub-groups of %d nonzeros, batches of 8, 256-thread workgroups" % (ch, L, 64 // L, (ch // 64) * L))
+    def tile(ch, kernel):
+        if kernel == "cdot_run":
+            cw = 4 if sx == 4 and k > 16 else 2
+            lanes = max(L, 16) // cw
+            return ("run column dots: chunks of %d nonzeros, one chunk per wave, %d lanes of %d columns x %d positions "
+                    "of a run, 256 positions staged at a time, 256-thread workgroups" % (ch, lanes, cw, 64 // lanes))
+        cw = 2 if sx == 8 else min(4, L)
+        lanes = L // cw
+        return ("tiled column dots: chunks of %d nonzeros, one chunk per wave, %d lanes of %d columns x %d position "
+                "sub-groups of %d nonzeros, batches of 8, 256-thread workgroups"
+                % (ch, lanes, cw, 64 // lanes, (ch // 64) * lanes))
     scatter = ("scatter product: %d row panel(s) of %d rows in LDS, %d workgroup ranges x 4 waves per column, "
                "blocks of 1024 nonzeros" % (info["n_panels"], info["panel_rows"], info["mv_workgroups"]))
     names = {1: "single", 2: "passes", 3: "tile"}
@@ -997,10 +1023,10 @@ def batch_plan(info, k, plan_mv, plan_vtm, sx):
     else:
         mv = {1: "%d single-column passes of the " % k + scatter,
               2: "passes of up to 8 columns of the " + scatter,
-              3: tile(1024) + ", over the kept transpose"}[plan_mv]
+              3: tile(1024, tiles[0]) + ", over the kept transpose"}[plan_mv]
         vtm = {1: "%d single-column passes of the column dots (chunks of %d)" % (k, chunk),
                2: "column-dot passes of up to 8 columns, each chunk (of %d) loaded once per pass" % chunk,
-               3: tile(chunk)}[plan_vtm]
+               3: tile(chunk, tiles[1])}[plan_vtm]
     return {"mv": mv, "vtm": vtm, "mv_plan": names.get(plan_mv, "single"), "vtm_plan": names.get(plan_vtm, "single"),
             "chunk_nnz": chunk, "coldot_wg_size": wg, "tuned": bool(info["tuned"])}
 

@@ -79,8 +79,8 @@ typedef struct spw_matrix_s *spw_matrix;
  *                   that overflows the storage type is SPW_ERR_BAD_MATRIX.
  *                   Products promote stored values exactly to binary64.
  *   chunk_nnz     : nonzeros per column-dot chunk: 0 = automatic (1024; 512 for small
- *                   matrices and for short columns; the tuner's choice with
- *                   autotune), 512 or 1024; any other value is
+ *                   matrices and for short columns, the same in every partition
+ *                   mode; the tuner's choice with autotune), 512 or 1024; any other value is
  *                   SPW_ERR_UNSUPPORTED.  Smaller chunks give small matrices more
  *                   workers (Section II's P grows as the chunk shrinks).
  *   relabel       : -1 automatic, 0 off, 1 on.  On: rows are renumbered inside
@@ -171,7 +171,8 @@ typedef struct {
     int64_t device_bytes;         /* device memory held by the handle */
     int32_t has_transpose;        /* the transpose is kept (see spw_create_opts.transpose) */
     spw_partition partition;
-    int64_t workers;              /* P: workers of the single-vector column dots (waves) */
+    int64_t workers;              /* P: workers of the single-vector column dots (waves, or pairs of waves where */
+                                  /* column partitioning gives one worker over twice the average nonzeros) */
     int64_t worker_max_nnz;       /* nonzeros owned by the busiest / idlest of them; the paper's */
     int64_t worker_min_nnz;       /* imbalance is P * (max - min) / nnz (Section VI) */
     int32_t wg_size_f64;          /* column-dot workgroup size used with binary64 vectors */
