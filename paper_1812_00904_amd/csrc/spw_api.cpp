@@ -1975,11 +1975,15 @@ spw_status spw_info(spw_matrix A, spw_matrix_info *o)
 namespace spw {
 namespace {
 
-// The fixed rule (see spw_plan in spw.h).  Scatter direction: passes of up to
-// 8 columns below 16 columns (they beat the tiled column dots over the
-// transpose there, whose gathers of the caller's k-wide rows of X cross cache
-// lines unless k is a power of two), tiles from 16.  Column dots: each chunk
-// read once and reduced per column up to 6 columns, tiles from about 7 on.
+// The fixed rule (see spw_plan in spw.h).  Scatter direction: passes of up to 8 columns below
+// 16 columns, column dots over the transpose from 16, whose gathers of the caller's k-wide rows of X
+// need whole 16-byte groups of columns and a width near the next power of two (us, passes and
+// transpose, binary64, k = 9 / 12 / 14 / 16: 20,000 x 5e6 with 5e7 nonzeros 996 and 1,676 / 1,134 and
+// 1,292 / 1,527 and 1,514 / 1,613 and 954; 5,000 x 1e5 with 4e6 69 and 112 / 76 and 80 / 88 and 96 / 99
+// and 68; binary32 k = 14 and 16 987 and 1,598, 1,061 and 904; 74 and 100, 81 and 52).  The line is one for
+// all sizes: with 1e6 nonzeros the transpose is ahead from even k = 10 on (36 and 25, binary32 k = 12 35 and
+// 21), and with 50,000 rows of 400 nonzeros passes still are at k = 24 (539 and 676; binary32 475 and 442).
+// Column dots: each chunk read once and reduced per column up to 6 columns, tiles from about 7 on.
 static int32_t rule_plan(const spw_matrix_s &A, bool scatter, int32_t k, int64_t ldo)
 {
     if (scatter) return (k < 16 || !A.cdt.built) ? SPW_PLAN_PASSES : SPW_PLAN_TILE;
