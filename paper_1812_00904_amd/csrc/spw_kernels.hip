@@ -277,29 +277,39 @@ __device__ __forceinline__ MvPanel mv_panel(int slots, int rows, int cs, const H
     return MvPanel{slots, rows, cs, h.y, hot + h.x};
 }
 
-// KC panels to their partial sums, one a row: the slots that a row has more are added to its first,
-// four running sums of them, then the row's copies pairwise.  All of the workgroup's waves come here
-// with their adds to the panel made or under way.  The descriptors of the rows with more slots are
-// read before the barrier, and without copies the columns' loads are independent of one another: in
-// small products the end of a range counts (29,966 x 2.5e6 with 257,000 nonzeros, twelve columns:
-// 78 us of mv_bucket with a test for the copies at every element, 71 like this).
+// A thread's first row of mv_write_panel's: read when the range begins, not when it ends.
+constexpr int HOT_LANES = 8;
+template <int KC> __device__ __forceinline__ HotRow mv_hot(const MvPanel &pn)
+{
+    return (int)threadIdx.x < pn.nhot * KC * HOT_LANES ? pn.hot[threadIdx.x / (HOT_LANES * KC)] : HotRow{};
+}
+
+// KC panels to their partial sums, one a row: the slots that a row has more (63 at most) are added to
+// its first by eight threads a row, then the row's copies pairwise.  All of the workgroup's waves come
+// here with their adds to the panel made or under way.  The end of a range counts, in small products
+// most of all, so its loads don't wait for one another: 29,966 x 2.5e6 with 257,000 nonzeros, twelve
+// columns, 78 us of mv_bucket with a test for the copies at every element, 71 like this; with a
+// thread a row and its descriptor read at the end, a single product of 2e8 nonzeros and of 1e7 took
+// 0.5 us more and four columns over 5e7 1 us.
 template <int BLOCK, int KC>
-__device__ __forceinline__ void mv_write_panel(double *ypan, const MvPanel &pn, double *__restrict__ out,
+__device__ __forceinline__ void mv_write_panel(double *ypan, const MvPanel &pn, HotRow h, double *__restrict__ out,
                                                int64_t col_stride)
 {
     const int rows = pn.rows, cs = pn.cs, tid = threadIdx.x;
-    HotRow h = {};
-    if (tid < pn.nhot * KC) h = pn.hot[tid / KC];
     __syncthreads();
     if (pn.nhot > 0) {
-        for (int i = tid; i < pn.nhot * KC; i += BLOCK) {
-            if (i != tid) h = pn.hot[i / KC];
-            double *y = ypan + (i % KC) * pn.slots, a[4] = {y[h.local], 0.0, 0.0, 0.0};
-            for (int j = 0; j < h.more; j += 4)
+        const int n = pn.nhot * KC * HOT_LANES, lane = tid % HOT_LANES;
+        for (int i = tid; i < n; i += BLOCK) {
+            const int g = i / HOT_LANES;
+            if (i != tid) h = pn.hot[g / KC];
+            double *y = ypan + (g % KC) * pn.slots, a[8];
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    if (j + t < h.more) a[(t + 1) & 3] += y[h.first + j + t];
-            y[h.local] = (a[0] + a[1]) + (a[2] + a[3]);
+            for (int t = 0; t < 8; ++t) a[t] = lane + HOT_LANES * t < h.more ? y[h.first + lane + HOT_LANES * t] : 0.0;
+            double s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+            s += __shfl_xor(s, 1);
+            s += __shfl_xor(s, 2);
+            s += __shfl_xor(s, 4);
+            if (lane == 0) y[h.local] += s;
         }
         __syncthreads();
     }
@@ -341,6 +351,7 @@ __device__ __forceinline__ void mv_range(const uint32_t *__restrict__ packed, co
 {
     constexpr int NW = BLOCK / WAVE;
     const int tid = threadIdx.x, wave = tid / WAVE, lane = tid & (WAVE - 1);
+    const HotRow hot = mv_hot<1>(pn);
     for (int i = tid; i < pn.slots; i += BLOCK) ypan[i] = 0.0;
     __syncthreads();
 
@@ -422,7 +433,7 @@ __device__ __forceinline__ void mv_range(const uint32_t *__restrict__ packed, co
             if (b + 2 >= b1) break;
         }
     }
-    mv_write_panel<BLOCK, 1>(ypan, pn, out, 0);
+    mv_write_panel<BLOCK, 1>(ypan, pn, hot, out, 0);
 }
 
 template <int BLOCK, typename ValT, typename VecT>
@@ -570,6 +581,7 @@ __device__ __forceinline__ void mv_range_cols(const uint32_t *__restrict__ packe
     const int slots = pn.slots;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const HotRow hot = mv_hot<KC>(pn);
     for (int i = tid; i < KC * slots; i += BLOCK) ypan[i] = 0.0;
     __syncthreads();
     const int b0 = __builtin_amdgcn_readfirstlane(wb[wave]), b1 = __builtin_amdgcn_readfirstlane(wb[wave + 1]);
@@ -675,7 +687,7 @@ __device__ __forceinline__ void mv_range_cols(const uint32_t *__restrict__ packe
             if (b + 2 >= b1) break;
         }
     }
-    mv_write_panel<BLOCK, KC>(ypan, pn, out, col_stride);
+    mv_write_panel<BLOCK, KC>(ypan, pn, hot, out, col_stride);
 }
 
 // Groups of columns in one launch: workgroup (group, range).  The groups of one
