@@ -288,9 +288,9 @@ template <int KC> __device__ __forceinline__ HotRow mv_hot(const MvPanel &pn)
 // its first by eight threads a row, then the row's copies pairwise.  All of the workgroup's waves come
 // here with their adds to the panel made or under way.  The end of a range counts, in small products
 // most of all, so its loads don't wait for one another: 29,966 x 2.5e6 with 257,000 nonzeros, twelve
-// columns, 78 us of mv_bucket with a test for the copies at every element, 71 like this; with a
-// thread a row and its descriptor read at the end, a single product of 2e8 nonzeros and of 1e7 took
-// 0.5 us more and four columns over 5e7 1 us.
+// columns, 78 us of mv_bucket with a test for the copies at every element, 71 like this.  The slots
+// cost, against one sum a row, 0.7 us of a pair of 74 (9e6 nonzeros, 19,996 rows) and 2.2 us of 242 for
+// four columns over 5e7 with a thread a row and its descriptor read at the end, 0.6 and 1.7 like this.
 template <int BLOCK, int KC>
 __device__ __forceinline__ void mv_write_panel(double *ypan, const MvPanel &pn, HotRow h, double *__restrict__ out,
                                                int64_t col_stride)
@@ -742,7 +742,8 @@ __global__ __launch_bounds__(BLOCK) void mv_bucket_cols(
     }
 }
 
-// y[caller row] = sum over the panel's workgroups of their partials.  Internal row r belongs to panel r mod npanels, at panel-local row r / npanels; a
+// y[caller row] = sum over the panel's workgroups of their partials.  Internal row r
+// belongs to panel r mod npanels, at panel-local row r / npanels; a
 // workgroup takes 32 consecutive rows of one panel, eight threads a row: thread t
 // adds partials t, t+8, t+16, ... in ascending order with up to sixteen loads in
 // flight (a chain of dependent trips to memory bounds this kernel, not its
@@ -750,8 +751,8 @@ __global__ __launch_bounds__(BLOCK) void mv_bucket_cols(
 // addition is fixed.  FEW: panels of at most eight workgroups, where one thread takes a
 // whole row, in the same order, and the panels are one sequence of rows, so that small
 // ones fill a workgroup too (2e6 x 2e6 in 98 panels of two or three workgroups: 83 us with
-// eight threads a row, five of them idle, now 43; 500,000 rows in 49 panels 32 and 17).  Column blockIdx.y: its partials start col_stride doubles
-// further, its output is out.u[column].
+// eight threads a row, five of them idle, now 43; 500,000 rows in 49 panels 32 and 17).
+// Column blockIdx.y: its partials start col_stride doubles further, its output is out.u[column].
 constexpr int MV_FEW = 8;
 template <typename VecT, bool FEW>
 __global__ __launch_bounds__(256) void mv_reduce(const double *__restrict__ partial, int panel_rows, int panel_blocks,
@@ -904,7 +905,8 @@ int vtm_block_for(const spw_matrix_s &A, bool colpart)
 // - binary64 vectors 256, or 512 where more than one chunk in eight has more than 256 (columns
 //   of one or two nonzeros; chunks of 512 only);
 // - binary32 vectors none with chunks of 1,024, and with chunks of 512 only where columns are
-//   short (fewer than two nonzeros, two and a half for several vectors: 8e6, one a column, binary32 values, us without and with, one vector 39 / 30, three 132 / 76)
+//   short (fewer than two nonzeros, two and a half for several vectors: 8e6, one a column, binary32
+//   values, us without and with, one vector 39 / 30, three 132 / 76)
 //   or have empty ones among them all over (3 a column 36 / 32, 97 / 87) and, for one
 //   vector, all of v still fits: sixteen waves' stages take 19,000 of 40,000 hot rows (50,000 rows, uniform,
 //   2.9e7 nonzeros, binary32 values: 66 us without, 100 with them; no empty columns, 20,000 rows,

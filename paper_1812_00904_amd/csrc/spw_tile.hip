@@ -510,7 +510,6 @@ int launch_tile_items(const spw_matrix_s &A, const ColDot &C, int k, const VecT 
 }
 
 // Chunks of 1,024 or 512 nonzeros (16 or 8 positions per layout lane).
-// Chunks of 1,024 or 512 nonzeros.
 template <typename IdxT, typename ValT, typename VecT, typename OutT>
 int launch_tile(const spw_matrix_s &A, const ColDot &C, int k, const VecT *V, int64_t ldv, OutT *U, int64_t ldu,
                 bool wide, hipStream_t stream)
