@@ -868,7 +868,8 @@ int64_t mv_read_cols(int64_t cols, const int64_t *ptr, spw_partition part, int64
 // (2-norm against 80-bit sums in the fewest panels, in the rule's and in those with copies: 4,000 x
 // 3,000 two thirds full 3.0e-16, 5.7e-16, 2.0e-16; 2,000 x 30,000 with 548 a column 3.3e-16, 6.3e-16,
 // 2.7e-16).  The copies are added when a range ends, so that they cost the LDS and nothing else
-// (as partial sums of their own 7,608 x 80,062 with 3.4e7 nonzeros took 57 us of A x, like this 50, without copies 50 too).
+// (as partial sums of their own 7,608 x 80,062 with 3.4e7 nonzeros took 57 us of A x, like this 50,
+// without copies 50 too).
 // least: the fewest panels that the LDS takes, one workgroup a CU or two where it takes them,
 // one sum a row.
 struct MvError {
@@ -1004,7 +1005,8 @@ spw_status build_mv_storage(spw_matrix_s &A, const int64_t *ptr, const int32_t *
     //    nonzeros.  A nonzero goes to one of its row's slots by its column.
     //    Copies: the fewest that keep the sums as exact as in the fewest panels (MvError).
     int64_t copies = 1;
-    const int64_t beside = std::max<int64_t>(1, std::min<int64_t>(4, limit / R));    // columns beside one another in the LDS
+    // columns beside one another in the LDS
+    const int64_t beside = std::max<int64_t>(1, std::min<int64_t>(4, limit / R));
     while (copies < 16 && 2 * copies * R * beside <= limit &&
            error.of(P, target, copies) > (panel_rows_opt > 0 ? 1.05 : 0.9) * error.least &&
            error.of(P, target, 2 * copies) < 0.9 * error.of(P, target, copies))
