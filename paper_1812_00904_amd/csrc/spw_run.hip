@@ -21,14 +21,17 @@ namespace {
 // join a queue).  Finished columns are added across the S position rows of the wave
 // four at a time (two for S = 2) and go out in one store.
 //
-// What bounds it: the L1.  A gather of 64 x 16 bytes takes 16 cycles to read out and, where
+// What bounds it: over the matrix's own storage, whose V mostly comes from the L2 (63 to 82 % hits),
+// the L1.  A gather of 64 x 16 bytes takes 16 cycles to read out and, where
 // its lines miss (nearly all: V is far larger), as many to fill, whatever its lanes read, so
 // a lane reads 16 bytes where the block is wide enough; after that the column starts, about
 // 15 vector and 25 scalar instructions each.  A fill and a read of every gathered byte at 64
 // bytes a cycle and CU are 1.3 ms for k = 64 on 20,000 x 5e6 with 5e7 nonzeros, where this
 // takes 1.75 (cdot_tile, whose lanes test every position: 2.18); k = 16 0.56 (0.77), k = 32
 // 0.94 (1.21).  Over the blocked transpose of 20,000 x 2e6 with 2e7: binary64 k = 16 0.35
-// (0.57), k = 64 1.37 (1.53), binary32 k = 16 0.32 (0.40), k = 32 0.33 (0.51).
+// (0.57), k = 64 1.37 (1.53), binary32 k = 16 0.32 (0.40), k = 32 0.33 (0.51).  There nearly every
+// gathered row comes from beyond the L2 (8 to 18 % hits), and the rate of that is the bound: 20,000 x
+// 5e6, 5e7 nonzeros, k = 64 25.3 GB in 3.42 ms, binary32 k = 16 5.9 GB in 0.80 ms, 7.4 TB/s.
 //
 // The indices and values go through LDS, 256 positions at a time: a batch of 16 (8
 // for S = 2) consecutive positions is stored as [s][t], so that a lane reads its
